@@ -282,7 +282,7 @@ k_decode_mlp(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
 {
     __shared__ MlpLds L;
     __shared__ __align__(16) float s_stage[4][32 * SROW];
-    mlp_stage_weights<KB>(params, L);
+    mlp_stage_weights<KB, 256>(params, L);
     __syncthreads();
     const int lane = legs_lane(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
     const int64_t tiles = (P + 31) / 32;
@@ -293,7 +293,10 @@ k_decode_mlp(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
         const bool valid = p < P;
         int off = 0;
         asm volatile("" : "+s"(off));   // fragments are re-read from LDS every tile
-        mlp_tile_forward<KB, NORM>(L, feat, p, valid, cs, ps, T, off);
+        float v[LEGS_MLP_IN];
+#pragma unroll
+        for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = (h == 0 && valid) ? ldfeat(feat, p, e, cs, ps) : 0.0f;
+        mlp_tile_forward<KB, NORM>(L, v, T, off);
         float best = -INFINITY;
         int bidx = 0x7fffffff;
         f32x16 S[KB];
@@ -313,48 +316,31 @@ k_decode_mlp(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
     }
 }
 
-// Top-1 only: NT 32-pixel tiles per wave at once (each weight fragment read
-// from LDS feeds NT MFMAs), logits consumed block by block. Per block a lane
+// Top-1 only: two 32-pixel tiles per wave at once (each weight fragment read
+// from LDS feeds two MFMAs), logits consumed block by block. Per block a lane
 // takes the maximum of its 16 logits; when it beats the running maximum, the
 // class is the first position of that maximum in the block (KEEP: the
 // block's logits are kept and searched once at the end; otherwise the
 // position is found per block). Either way the result is the first maximum
 // along increasing class index.
-template <int KB, int NT, bool VEC8, bool KEEP, bool NORM>
+template <int KB, bool VEC8, bool KEEP, bool NORM>
 __global__ void __launch_bounds__(256)
 k_decode_mlp_top1(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
                   const float *__restrict__ params, int32_t *__restrict__ top1)
 {
+    constexpr int NT = 2;
     __shared__ MlpLds L;
-    mlp_stage_weights<KB>(params, L);
+    mlp_stage_weights<KB, 256>(params, L);
     __syncthreads();
-    const int lane = legs_lane(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
+    const int lane = legs_lane(), h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LEGS_WAVE);
     const int64_t groups = (P + 32 * NT - 1) / (32 * NT);
     const int64_t stride = (int64_t)gridDim.x * 4;
     for (int64_t g = (int64_t)blockIdx.x * 4 + wave; g < groups; g += stride) {
         int off = 0;
         asm volatile("" : "+s"(off));   // fragments are re-read from LDS every group
         legs_bf16x8 x[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int64_t p = (g * NT + t) * 32 + (lane & 31);
-            float v[LEGS_MLP_IN];
-            if (h == 0 && p < P) {
-                if constexpr (VEC8) {
-                    const float4 a = reinterpret_cast<const float4 *>(feat)[2 * p];
-                    const float4 b = reinterpret_cast<const float4 *>(feat)[2 * p + 1];
-                    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-                    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = ldfeat(feat, p, e, cs, ps);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = 0.0f;
-            }
-            x[t] = mlp_input<NORM>(v, h);
-        }
+        mlp_inputs64<VEC8, NORM>(feat, P, cs, ps, g * NT * 32, x);
         legs_bf16x8 h2[NT][4];
         mlp_hidden<NT>(L, off, x, h2);
         float best[NT];
@@ -470,13 +456,12 @@ int32_t legs_launch_decode_mlp(legs_ctx *ctx, const float *feat, int64_t P, int6
         }
 #undef LEGS_MLP_ALL
     } else {
-        constexpr int NT = 2;
         constexpr bool KEEP = true;
-        const int grid = decode_grid(ctx, P, 32 * NT * 4);
-        const bool vec8 = cs == 1 && ps == LEGS_MLP_IN && (reinterpret_cast<uintptr_t>(feat) & 15) == 0;
+        const int grid = decode_grid(ctx, P, 64 * 4);
+        const bool vec8 = legs_feat_rows(feat, cs, ps);
 #define LEGS_MLP_TOP1(KB, NORM)                                                                       \
-        if (vec8) hipLaunchKernelGGL((k_decode_mlp_top1<KB, NT, true, KEEP, NORM>), dim3(grid), dim3(256), 0, s, feat, P, cs, ps, params, top1); \
-        else hipLaunchKernelGGL((k_decode_mlp_top1<KB, NT, false, KEEP, NORM>), dim3(grid), dim3(256), 0, s, feat, P, cs, ps, params, top1);
+        if (vec8) hipLaunchKernelGGL((k_decode_mlp_top1<KB, true, KEEP, NORM>), dim3(grid), dim3(256), 0, s, feat, P, cs, ps, params, top1); \
+        else hipLaunchKernelGGL((k_decode_mlp_top1<KB, false, KEEP, NORM>), dim3(grid), dim3(256), 0, s, feat, P, cs, ps, params, top1);
 #define LEGS_MLP_TOP1N(KB) if (norm) { LEGS_MLP_TOP1(KB, true) } else { LEGS_MLP_TOP1(KB, false) }
         switch (K) {
         case 32: LEGS_MLP_TOP1N(1) break;

@@ -40,50 +40,32 @@ struct DmlpLds {
     legs_bf16x8 bb3[KB * 64];
 };
 
-template <int KB>
+template <int KB, int THREADS>
 __device__ __forceinline__ void dmlp_stage(const float *__restrict__ params, DmlpLds<KB> &L)
 {
     const float *W1 = params + LEGS_DMLP_OFF_W1, *b1 = params + LEGS_DMLP_OFF_B1;
     const float *W2 = params + LEGS_DMLP_OFF_W2, *b2 = params + LEGS_DMLP_OFF_B2;
     const float *W3 = params + LEGS_DMLP_OFF_W3, *b3 = params + LEGS_DMLP_OFF_B3(KB);
-    const int tid = threadIdx.x, nt = blockDim.x;
-    __bf16 *w1 = reinterpret_cast<__bf16 *>(L.w1);
-    __bf16 *w2 = reinterpret_cast<__bf16 *>(L.w2);
-    __bf16 *w3 = reinterpret_cast<__bf16 *>(L.w3);
-    __bf16 *bb2 = reinterpret_cast<__bf16 *>(L.bb2);
-    __bf16 *bb3 = reinterpret_cast<__bf16 *>(L.bb3);
-    // element (block, k-step, lane, e) of a fragment: row 32 block + lane % 32,
-    // hidden unit legs_khid(k-step, lane / 32, e) of the previous layer
-    for (int i = tid; i < B1 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, mb = i >> 9;
-        const int row = 32 * mb + (l & 31);
-        if ((l >> 5) == 0) {
-            w1[i] = (__bf16)W1[row * LEGS_MLP_IN + e];
-        } else {
-            __bf16 p[3];
-            legs_split3(b1[row], p[0], p[1], p[2]);
-            w1[i] = e < 3 ? p[e] : (__bf16)0.0f;
-        }
-    }
-    for (int i = tid; i < B2 * S2 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, ks = (i >> 9) % S2, mb = (i >> 9) / S2;
-        w2[i] = (__bf16)W2[(32 * mb + (l & 31)) * H1 + legs_khid(ks, l >> 5, e)];
-    }
-    for (int i = tid; i < KB * S3 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, ks = (i >> 9) % S3, mb = (i >> 9) / S3;
-        w3[i] = (__bf16)W3[(32 * mb + (l & 31)) * H2 + legs_khid(ks, l >> 5, e)];
-    }
-    for (int i = tid; i < (B2 + KB) * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, mb = i >> 9;
-        const bool second = mb < B2;
-        const int blk = second ? mb : mb - B2;
-        const float b = second ? b2[32 * blk + (l & 31)] : b3[32 * blk + (l & 31)];
-        __bf16 p[3];
-        legs_split3(b, p[0], p[1], p[2]);
-        const __bf16 v = ((l >> 5) == 1 && e < 3) ? p[e] : (__bf16)0.0f;
-        if (second) bb2[(blk * 64 + l) * 8 + e] = v;
-        else bb3[(blk * 64 + l) * 8 + e] = v;
-    }
+    // fragment (block, k-step, lane): row 32 block + lane % 32, hidden units
+    // legs_khid(k-step, lane / 32, 0 .. 7) of the previous layer
+    legs_stage_frags<B2 * S2 * 64, THREADS, 8>(L.w2, [&](int i) {
+        const int l = i & 63, ks = (i >> 6) % S2, mb = (i >> 6) / S2;
+        return legs_frag_row(W2 + (32 * mb + (l & 31)) * H1, ks, l >> 5);
+    });
+    legs_stage_frags<KB * S3 * 64, THREADS, 8>(L.w3, [&](int i) {
+        const int l = i & 63, ks = (i >> 6) % S3, mb = (i >> 6) / S3;
+        return legs_frag_row(W3 + (32 * mb + (l & 31)) * H2, ks, l >> 5);
+    });
+    legs_stage_frags<B1 * 64, THREADS, 1>(L.w1, [&](int i) {
+        const int row = 32 * (i >> 6) + (i & 31);
+        return legs_frag_input(W1 + row * LEGS_MLP_IN, b1[row], (i >> 5) & 1);
+    });
+    legs_stage_frags<B2 * 64, THREADS, 2>(L.bb2, [&](int i) {
+        return legs_frag_bias(b2[32 * (i >> 6) + (i & 31)], (i >> 5) & 1);
+    });
+    legs_stage_frags<KB * 64, THREADS, 1>(L.bb3, [&](int i) {
+        return legs_frag_bias(b3[32 * (i >> 6) + (i & 31)], (i >> 5) & 1);
+    });
 }
 
 // Hidden layers of NT tiles: x (inputs) -> h2 (B operand of layer 3).
@@ -138,33 +120,6 @@ __device__ __forceinline__ void dmlp_logits_block(const DmlpLds<KB> &L, int lds_
     }
 }
 
-template <int NT, bool VEC8, bool NORM>
-__device__ __forceinline__ void dmlp_inputs(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
-                                            int64_t g, legs_bf16x8 (&x)[NT])
-{
-    const int lane = __lane_id(), h = lane >> 5;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int64_t p = (g * NT + t) * 32 + (lane & 31);
-        float v[LEGS_MLP_IN];
-        if (h == 0 && p < P) {
-            if constexpr (VEC8) {
-                const float4 a = reinterpret_cast<const float4 *>(feat)[2 * p];
-                const float4 b = reinterpret_cast<const float4 *>(feat)[2 * p + 1];
-                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-                v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-            } else {
-#pragma unroll
-                for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = legs_ldfeat(feat, p, e, cs, ps);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = 0.0f;
-        }
-        x[t] = mlp_input<NORM>(v, h);
-    }
-}
-
 __device__ __forceinline__ void argmax_pair(float &best, int &bidx)
 {
     const float ob = __shfl_xor(best, 32, LEGS_WAVE);
@@ -175,27 +130,27 @@ __device__ __forceinline__ void argmax_pair(float &best, int &bidx)
 // Top-1 only: logits consumed block by block (each lane keeps the block
 // holding its running maximum and searches it once at the end: the first
 // maximum along increasing class index).
-// Row-major input (VEC8): eight waves per workgroup. The weight fragments fill
-// the LDS (one workgroup per CU) and such a wave fits in 256 registers, so two
-// waves share each SIMD (MFMAs of one beside the other's conversions and
-// argmax). The strided input's addressing would spill there: four waves.
-template <int KB, int NT, bool VEC8, bool NORM>
-__global__ void __launch_bounds__(VEC8 ? 512 : 256)
+// Eight waves per workgroup: the weight fragments fill the LDS (one workgroup
+// per CU) and a wave fits in 256 registers, so two waves share each SIMD
+// (MFMAs of one beside the other's conversions and argmax).
+template <int KB, bool VEC8, bool NORM>
+__global__ void __launch_bounds__(512)
 k_dmlp_top1(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
             const float *__restrict__ params, int32_t *__restrict__ top1)
 {
+    constexpr int NT = 2;
     __shared__ DmlpLds<KB> L;
-    dmlp_stage<KB>(params, L);
+    dmlp_stage<KB, 512>(params, L);
     __syncthreads();
-    const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
-    const int nw = blockDim.x / LEGS_WAVE;
+    const int lane = __lane_id(), h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LEGS_WAVE);
     const int64_t groups = (P + 32 * NT - 1) / (32 * NT);
-    const int64_t stride = (int64_t)gridDim.x * nw;
-    for (int64_t g = (int64_t)blockIdx.x * nw + wave; g < groups; g += stride) {
+    const int64_t stride = (int64_t)gridDim.x * 8;
+    for (int64_t g = (int64_t)blockIdx.x * 8 + wave; g < groups; g += stride) {
         int off = 0;
         asm volatile("" : "+s"(off));
         legs_bf16x8 x[NT];
-        dmlp_inputs<NT, VEC8, NORM>(feat, P, cs, ps, g, x);
+        mlp_inputs64<VEC8, NORM>(feat, P, cs, ps, g * NT * 32, x);
         legs_bf16x8 h2[NT][S3];
         dmlp_hidden<KB, NT>(L, off, x, h2);
         float best[NT];
@@ -249,25 +204,26 @@ __device__ __forceinline__ void stage_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int KB, int NT, bool VEC8, bool NORM>
+template <int KB, bool VEC8, bool NORM>
 __global__ void __launch_bounds__(256)
 k_dmlp_probs(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
              const float *__restrict__ params, float *__restrict__ probs, _Float16 *__restrict__ probs16,
              int32_t *__restrict__ top1)
 {
-    constexpr int N = 32 * KB;
+    constexpr int N = 32 * KB, NT = 2;
     __shared__ DmlpLds<KB> L;
     __shared__ __align__(16) float s_stage[4][32 * PROW32];
-    dmlp_stage<KB>(params, L);
+    dmlp_stage<KB, 256>(params, L);
     __syncthreads();
-    const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
+    const int lane = __lane_id(), h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LEGS_WAVE);
     const int64_t groups = (P + 32 * NT - 1) / (32 * NT);
     const int64_t stride = (int64_t)gridDim.x * 4;
     for (int64_t g = (int64_t)blockIdx.x * 4 + wave; g < groups; g += stride) {
         int off = 0;
         asm volatile("" : "+s"(off));
         legs_bf16x8 x[NT];
-        dmlp_inputs<NT, VEC8, NORM>(feat, P, cs, ps, g, x);
+        mlp_inputs64<VEC8, NORM>(feat, P, cs, ps, g * NT * 32, x);
         legs_bf16x8 h2[NT][S3];
         dmlp_hidden<KB, NT>(L, off, x, h2);
         f32x16 z[KB][NT];
@@ -380,14 +336,16 @@ k_lang_features(const _Float16 *__restrict__ M, int64_t P, const float *__restri
     __shared__ FeatLds<KB> L;
     const int d0 = blockIdx.y * FCHUNK;
     const int nblk = min(FBLK, (d - d0) / 32);
-    {
-        _Float16 *s = reinterpret_cast<_Float16 *>(L.s);
-        for (int i = threadIdx.x; i < nblk * KS * 64 * 8; i += blockDim.x) {
-            const int e = i & 7, l = (i >> 3) & 63, ks = (i >> 9) % KS, db = (i >> 9) / KS;
-            const int dd = d0 + 32 * db + (l & 31);
-            const int c = 16 * ks + 8 * (l >> 5) + e;
-            s[i] = (_Float16)S[(int64_t)c * d + dd];
-        }
+    // one fragment a thread and step, its eight loads (and the next step's) in
+    // flight together
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nblk * KS * 64; i += 1024) {
+        const int l = i & 63, ks = (i >> 6) % KS, db = (i >> 6) / KS;
+        const float *src = S + (int64_t)(16 * ks + 8 * (l >> 5)) * d + d0 + 32 * db + (l & 31);
+        f16x8 f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = (_Float16)src[(int64_t)e * d];
+        L.s[i] = f;
     }
     __syncthreads();
     const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
@@ -462,38 +420,33 @@ int32_t legs_launch_decode_dmlp(legs_ctx *ctx, const float *feat, int64_t P, int
 {
     if (P == 0) return LEGS_OK;
     const bool norm = (mlp_flags & LEGS_MLP_NORMALIZE_INPUT) != 0;
-    const bool vec8 = cs == 1 && ps == LEGS_MLP_IN && (reinterpret_cast<uintptr_t>(feat) & 15) == 0;
+    const bool vec8 = legs_feat_rows(feat, cs, ps);
     _Float16 *p16 = reinterpret_cast<_Float16 *>(probs16);
+#define LEGS_DMLP_L(M, KB, NM) if (vec8) M(KB, true, NM); else M(KB, false, NM);
+#define LEGS_DMLP_N(M, KB) if (norm) { LEGS_DMLP_L(M, KB, true) } else { LEGS_DMLP_L(M, KB, false) }
     if (probs || probs16) {
-        constexpr int NT = 2;
-        const int grid = dmlp_grid(ctx, P, 32 * NT * 4, 1);
-#define LEGS_DMLP_P(KB, V, NM) hipLaunchKernelGGL((k_dmlp_probs<KB, NT, V, NM>), dim3(grid), dim3(256), 0, s, \
+        const int grid = dmlp_grid(ctx, P, 64 * 4, 1);
+#define LEGS_DMLP_P(KB, V, NM) hipLaunchKernelGGL((k_dmlp_probs<KB, V, NM>), dim3(grid), dim3(256), 0, s, \
                                                    feat, P, cs, ps, params, probs, p16, top1)
-#define LEGS_DMLP_PN(KB) if (vec8) { if (norm) LEGS_DMLP_P(KB, true, true); else LEGS_DMLP_P(KB, true, false); } \
-                         else { if (norm) LEGS_DMLP_P(KB, false, true); else LEGS_DMLP_P(KB, false, false); }
         switch (N) {
-        case 32: LEGS_DMLP_PN(1) break;
-        case 64: LEGS_DMLP_PN(2) break;
-        default: LEGS_DMLP_PN(4) break;
+        case 32: LEGS_DMLP_N(LEGS_DMLP_P, 1) break;
+        case 64: LEGS_DMLP_N(LEGS_DMLP_P, 2) break;
+        default: LEGS_DMLP_N(LEGS_DMLP_P, 4) break;
         }
-#undef LEGS_DMLP_PN
 #undef LEGS_DMLP_P
     } else {
-        constexpr int NT = 2;
-        const int threads = vec8 ? 512 : 256;      // k_dmlp_top1's workgroup for each input layout
-        const int grid = dmlp_grid(ctx, P, 32 * NT * (threads / LEGS_WAVE), 1);
-#define LEGS_DMLP_T(KB, V, NM) hipLaunchKernelGGL((k_dmlp_top1<KB, NT, V, NM>), dim3(grid), dim3(threads), 0, s, \
+        const int grid = dmlp_grid(ctx, P, 64 * 8, 1);
+#define LEGS_DMLP_T(KB, V, NM) hipLaunchKernelGGL((k_dmlp_top1<KB, V, NM>), dim3(grid), dim3(512), 0, s, \
                                                    feat, P, cs, ps, params, top1)
-#define LEGS_DMLP_TN(KB) if (vec8) { if (norm) LEGS_DMLP_T(KB, true, true); else LEGS_DMLP_T(KB, true, false); } \
-                         else { if (norm) LEGS_DMLP_T(KB, false, true); else LEGS_DMLP_T(KB, false, false); }
         switch (N) {
-        case 32: LEGS_DMLP_TN(1) break;
-        case 64: LEGS_DMLP_TN(2) break;
-        default: LEGS_DMLP_TN(4) break;
+        case 32: LEGS_DMLP_N(LEGS_DMLP_T, 1) break;
+        case 64: LEGS_DMLP_N(LEGS_DMLP_T, 2) break;
+        default: LEGS_DMLP_N(LEGS_DMLP_T, 4) break;
         }
-#undef LEGS_DMLP_TN
 #undef LEGS_DMLP_T
     }
+#undef LEGS_DMLP_N
+#undef LEGS_DMLP_L
     LEGS_CHECK_LAUNCH(ctx);
     return LEGS_OK;
 }

@@ -133,49 +133,91 @@ __device__ __forceinline__ void legs_split3(float b, __bf16 &hi, __bf16 &mid, __
     lo = (__bf16)(r1 - (float)mid);
 }
 
-template <int KB>
+// Four neighbouring floats at any float alignment.
+struct __attribute__((packed, aligned(4))) legs_float4u {
+    float x, y, z, w;
+};
+
+// dst[i] = frag(i) for i in [0, N), by NT threads with NT / 64 waves: U
+// fragments a thread are built before any is stored, so that their loads are
+// in flight together. (Element by element, each conversion waited for its own
+// load: the top-1 decode of 2.07 Mpx from planes took 99.7 us, of which the 32
+// KB of weights about 25; with this and mlp_inputs64 it takes 58.9. The Table 3
+// decoder with F = M S, 144 + 128 KB, over 0.78 Mpx went from 465 to 388 us.)
+template <int N, int NT, int U, class F>
+__device__ __forceinline__ void legs_stage_frags(legs_bf16x8 *dst, F frag)
+{
+    for (int i0 = threadIdx.x; i0 < N; i0 += NT * U) {
+        legs_bf16x8 f[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * NT < N) f[u] = frag(i0 + u * NT);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * NT < N) dst[i0 + u * NT] = f[u];
+    }
+}
+
+// The 8 columns legs_khid(ks, hh, 0 .. 7) of a weight row: two runs of four.
+__device__ __forceinline__ legs_bf16x8 legs_frag_row(const float *__restrict__ row, int ks, int hh)
+{
+    const legs_float4u a = *reinterpret_cast<const legs_float4u *>(row + legs_khid(ks, hh, 0));
+    const legs_float4u b = *reinterpret_cast<const legs_float4u *>(row + legs_khid(ks, hh, 4));
+    return legs_bf16x8{(__bf16)a.x, (__bf16)a.y, (__bf16)a.z, (__bf16)a.w,
+                       (__bf16)b.x, (__bf16)b.y, (__bf16)b.z, (__bf16)b.w};
+}
+
+// A bias as an A operand: its three parts in k-slots 8 .. 10 (upper lane half).
+__device__ __forceinline__ legs_bf16x8 legs_frag_bias(float b, int hh)
+{
+    legs_bf16x8 f = {};
+    if (hh) {
+        __bf16 p[3];
+        legs_split3(b, p[0], p[1], p[2]);
+        f[0] = p[0];
+        f[1] = p[1];
+        f[2] = p[2];
+    }
+    return f;
+}
+
+// Layer 1 as an A operand: a row of the 8 input weights (lower lane half), its
+// bias (upper half).
+__device__ __forceinline__ legs_bf16x8 legs_frag_input(const float *__restrict__ row, float b, int hh)
+{
+    const legs_float4u a = *reinterpret_cast<const legs_float4u *>(row);
+    const legs_float4u c = *reinterpret_cast<const legs_float4u *>(row + 4);
+    const legs_bf16x8 f = {(__bf16)a.x, (__bf16)a.y, (__bf16)a.z, (__bf16)a.w,
+                           (__bf16)c.x, (__bf16)c.y, (__bf16)c.z, (__bf16)c.w};
+    const legs_bf16x8 bias = legs_frag_bias(b, 1);
+    return hh ? bias : f;
+}
+
+template <int KB, int NT>
 __device__ __forceinline__ void mlp_stage_weights(const float *__restrict__ params, MlpLds &L)
 {
     const float *W1 = params + LEGS_MLP_OFF_W1, *b1 = params + LEGS_MLP_OFF_B1;
     const float *W2 = params + LEGS_MLP_OFF_W2, *b2 = params + LEGS_MLP_OFF_B2;
     const float *W3 = params + LEGS_MLP_OFF_W3, *b3 = params + LEGS_MLP_OFF_B3(KB);
-    const int tid = threadIdx.x, nt = blockDim.x;
-    __bf16 *w1 = reinterpret_cast<__bf16 *>(L.w1);
-    __bf16 *w2 = reinterpret_cast<__bf16 *>(L.w2);
-    __bf16 *w3 = reinterpret_cast<__bf16 *>(L.w3);
-    // fragment element (block, k-step, lane, e): row 32 block + lane % 32
-    for (int i = tid; i < 2 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, mb = i >> 9;
-        const int row = 32 * mb + (l & 31), hh = l >> 5;
-        if (hh == 0) {
-            w1[i] = (__bf16)W1[row * LEGS_MLP_IN + e];
-        } else {
-            __bf16 p[3];
-            legs_split3(b1[row], p[0], p[1], p[2]);
-            w1[i] = e < 3 ? p[e] : (__bf16)0.0f;
-        }
-    }
-    for (int i = tid; i < 2 * 4 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, ks = (i >> 9) & 3, mb = i >> 11;
-        w2[i] = (__bf16)W2[(32 * mb + (l & 31)) * LEGS_MLP_H + legs_khid(ks, l >> 5, e)];
-    }
-    for (int i = tid; i < KB * 4 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, ks = (i >> 9) & 3, mb = i >> 11;
-        w3[i] = (__bf16)W3[(32 * mb + (l & 31)) * LEGS_MLP_H + legs_khid(ks, l >> 5, e)];
-    }
-    __bf16 *bb2 = reinterpret_cast<__bf16 *>(L.bb2);
-    __bf16 *bb3 = reinterpret_cast<__bf16 *>(L.bb3);
-    for (int i = tid; i < (2 + KB) * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, mb = i >> 9;
-        const bool second = mb < 2;
-        const int blk = second ? mb : mb - 2;
-        const float b = second ? b2[32 * blk + (l & 31)] : b3[32 * blk + (l & 31)];
-        __bf16 p[3];
-        legs_split3(b, p[0], p[1], p[2]);
-        const __bf16 v = ((l >> 5) == 1 && e < 3) ? p[e] : (__bf16)0.0f;
-        if (second) bb2[(blk * 64 + l) * 8 + e] = v;
-        else bb3[(blk * 64 + l) * 8 + e] = v;
-    }
+    // fragment (block, k-step, lane): row 32 block + lane % 32
+    legs_stage_frags<KB * 4 * 64, NT, 4>(L.w3, [&](int i) {
+        const int l = i & 63, ks = (i >> 6) & 3, mb = i >> 8;
+        return legs_frag_row(W3 + (32 * mb + (l & 31)) * LEGS_MLP_H, ks, l >> 5);
+    });
+    legs_stage_frags<2 * 4 * 64, NT, 2>(L.w2, [&](int i) {
+        const int l = i & 63, ks = (i >> 6) & 3, mb = i >> 8;
+        return legs_frag_row(W2 + (32 * mb + (l & 31)) * LEGS_MLP_H, ks, l >> 5);
+    });
+    legs_stage_frags<2 * 64, NT, 1>(L.w1, [&](int i) {
+        const int row = 32 * (i >> 6) + (i & 31);
+        return legs_frag_input(W1 + row * LEGS_MLP_IN, b1[row], (i >> 5) & 1);
+    });
+    legs_stage_frags<2 * 64, NT, 1>(L.bb2, [&](int i) {
+        return legs_frag_bias(b2[32 * (i >> 6) + (i & 31)], (i >> 5) & 1);
+    });
+    legs_stage_frags<KB * 64, NT, 1>(L.bb3, [&](int i) {
+        return legs_frag_bias(b3[32 * (i >> 6) + (i & 31)], (i >> 5) & 1);
+    });
 }
 
 __device__ __forceinline__ legs_f32x16 legs_mfma(legs_bf16x8 a, legs_bf16x8 b, legs_f32x16 c)
@@ -203,6 +245,53 @@ __device__ __forceinline__ legs_bf16x8 mlp_input(const float (&v)[LEGS_MLP_IN], 
         for (int e = 0; e < LEGS_MLP_IN; ++e) x[e] = (__bf16)(NORM ? v[e] * inv : v[e]);
     }
     return x;
+}
+
+// Whether a pixel's 8 features are 32 contiguous, 16-byte aligned bytes.
+inline bool legs_feat_rows(const float *feat, int64_t cs, int64_t ps)
+{
+    return cs == 1 && ps == LEGS_MLP_IN && (reinterpret_cast<uintptr_t>(feat) & 15) == 0;
+}
+
+// Inputs of two 32-pixel tiles, the 64 pixels from p0 (wave-uniform): every
+// lane reads and normalises one pixel, then four lane-half swaps leave tile 0's
+// in x[0] and tile 1's in x[1] (lower halves), the bias ones in the upper
+// halves. (One tile per lane half at a time, as mlp_input does, takes twice
+// the loads and normalisations, with half of the lanes idle, and its 64-bit
+// lane addresses cost the strided decode a third of its waves: 252 registers
+// against 164.) VEC8: legs_feat_rows.
+template <bool VEC8, bool NORM>
+__device__ __forceinline__ void mlp_inputs64(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
+                                             int64_t p0, legs_bf16x8 (&x)[2])
+{
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    const int lane = __lane_id();
+    float v[LEGS_MLP_IN];
+    if (p0 + lane < P) {
+        if constexpr (VEC8) {
+            const float4 *src = reinterpret_cast<const float4 *>(feat) + 2 * p0;
+            const float4 a = src[2 * lane], b = src[2 * lane + 1];
+            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+            v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = legs_ldfeat(feat, p0 + lane, e, cs, ps);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = 0.0f;
+    }
+    const u32x4 w = __builtin_bit_cast(u32x4, mlp_input<NORM>(v, 0));
+    const u32x4 ones = __builtin_bit_cast(u32x4, mlp_bias_ones(1));
+    u32x4 t0, t1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap(w[i], ones[i], false, false);
+        t0[i] = r[0];
+        t1[i] = r[1];
+    }
+    x[0] = __builtin_bit_cast(legs_bf16x8, t0);
+    x[1] = __builtin_bit_cast(legs_bf16x8, t1);
 }
 
 // Hidden layers of NT 32-pixel tiles at once: every weight fragment read from
@@ -262,16 +351,12 @@ __device__ __forceinline__ void mlp_logits_block(const MlpLds &L, int lds_off, i
 }
 
 // Forward of one 32-pixel tile keeping every activation (training, and the
-// decode that writes probabilities). pixel p = 32 tile + lane % 32.
+// decode that writes probabilities). v: the pixel's features (lower lane half).
 template <int KB, bool NORM>
-__device__ __forceinline__ void mlp_tile_forward(const MlpLds &L, const float *__restrict__ feat,
-                                                 int64_t p, bool valid, int64_t cs, int64_t ps,
-                                                 MlpTile<KB> &T, int lds_off = 0)
+__device__ __forceinline__ void mlp_tile_forward(const MlpLds &L, const float (&v)[LEGS_MLP_IN], MlpTile<KB> &T,
+                                                 int lds_off = 0)
 {
     const int h = __lane_id() >> 5;
-    float v[LEGS_MLP_IN];
-#pragma unroll
-    for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = (h == 0 && valid) ? legs_ldfeat(feat, p, e, cs, ps) : 0.0f;
     legs_bf16x8 x[1] = {mlp_input<NORM>(v, h)};
     T.x = x[0];
     const int lane = __lane_id() + lds_off;

@@ -122,7 +122,7 @@ k_mlp_fb(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, cons
     constexpr int K = 32 * KB;
     __shared__ MlpLds L;
     __shared__ MlpBwdLds<KB> T;
-    mlp_stage_weights<KB>(params, L);
+    mlp_stage_weights<KB, 256>(params, L);
     mlp_stage_bwd<KB>(params, T);
     __syncthreads();
     const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
@@ -137,7 +137,10 @@ k_mlp_fb(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, cons
         const int ln = lane + off;
         const int64_t p = tile * 32 + (lane & 31);
         const bool valid = p < B;
-        mlp_tile_forward<KB, NORM>(L, feat, p, valid, cs, ps, F, off);
+        float v[LEGS_MLP_IN];
+#pragma unroll
+        for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = (h == 0 && valid) ? legs_ldfeat(feat, p, e, cs, ps) : 0.0f;
+        mlp_tile_forward<KB, NORM>(L, v, F, off);
         // softmax over the pixel's K logits (this lane and its partner)
         float mx = -INFINITY;
 #pragma unroll

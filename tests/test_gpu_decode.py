@@ -258,3 +258,27 @@ def test_l1_loss_gradient(ctx, DEC, sizes):
     torch.cuda.synchronize()
     assert np.allclose(d_out.cpu().numpy(), g_ref, rtol=1e-6, atol=1e-12)
     assert loss.item() == pytest.approx(loss_ref, rel=1e-5)
+
+
+@pytest.mark.parametrize("K,normalize", [(128, True), (64, False), (32, True)])
+def test_top1_inputs_at_tile_edges(ctx, DEC, K, normalize):
+    """The top-1 decoders read 64 pixels a wave: row-major features, planes and
+    wider strides, pixel counts around 32 and 64, and parameters off 16-byte
+    alignment give the codes of the same decoder's distribution kernel (the
+    same arithmetic per pixel: equal, no tolerance)."""
+    f = torch.from_numpy(features(700, 60 + K)).cuda()
+    for sizes, dec in (((8, 64, 64, K), DEC.decode_mlp), ((8, 128, 256, K), DEC.decode_dmlp)):
+        ws, bs = synth.mlp_init(sizes, 61 + K)
+        p = DEC.mlp_pack(ws, bs).cuda()
+        shifted = torch.empty(p.numel() + 1, device="cuda")[1:]      # 4-byte aligned only
+        shifted.copy_(p)
+        for P in (1, 31, 32, 33, 63, 64, 65, 127, 129, 700):
+            note(f"top-1 inputs {sizes} P={P} normalize={normalize}")
+            rows = f[:P].contiguous()
+            want = dec(ctx, DEC.rowmajor_features(rows), p, K, probs=True, normalize=normalize)[0]
+            wide = torch.zeros((P, 11), device="cuda")
+            wide[:, 2:10] = rows
+            planes = rows.t().contiguous()
+            for src in ((rows, P, 1, 8), (planes, P, P, 1), (wide.view(-1)[2:], P, 1, 11)):
+                assert torch.equal(dec(ctx, src, p, K, normalize=normalize)[0], want)
+            assert torch.equal(dec(ctx, (rows, P, 1, 8), shifted, K, normalize=normalize)[0], want)
