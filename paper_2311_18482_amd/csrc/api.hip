@@ -558,8 +558,8 @@ int32_t legs_semantic_loss_grad_noalloc(legs_ctx *ctx, const float *feat, const 
     float *ws = ctx->device < kScratchDevices ? g_scratch[ctx->device].load() : nullptr;
     if (!ws) return legs_set_error(ctx, LEGS_ERR_HIP, "no scratch address for device %d", ctx->device);
     // Every workspace element the kernels read is written earlier in the same
-    // call (forward rows, then the hidden-layer gradients), so the array needs
-    // no clearing between calls.
+    // call (the training kernel's partial results), so the array needs no
+    // clearing between calls.
     return legs_semantic_loss_grad(ctx, feat, ru, P, c_stride, p_stride, labels, K, mlp_flags, params,
                                    lambda_ce, lambda_u, inv_hw, ws, grad, d_feat, d_c_stride,
                                    d_p_stride, d_ru, loss, stream);

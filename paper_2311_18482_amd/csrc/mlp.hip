@@ -4,24 +4,26 @@
 // 0.999)) used for both the decoder and the per-Gaussian parameters.
 //
 // Every contraction runs on v_mfma_f32_32x32x16_bf16 with float32 accumulation:
-//   k_mlp_fb     per 32-pixel tile: the inference forward (so training sees
-//                exactly the activations inference produces), softmax, CE,
+//   k_mlp_train  per 32-pixel tile and wave: the inference forward (so training
+//                sees exactly the activations inference produces), softmax, CE,
 //                dz3 = (p - onehot) w_p, then the backward through the layers
 //                (dh2 = W3^T dz3, dz2 = dh2 [h2 > 0], dh1 = W2^T dz2, dz1 =
 //                dh1 [h1 > 0], and the input gradient W1^T dz1) with the
 //                upstream gradient split into two bf16 parts (hi + lo, 16
 //                significant bits) and the W^T fragments in LDS next to the
-//                forward ones; straight through the bf16 roundings. Writes
-//                the layer inputs (bf16) and the dz (float32) unit-major
-//                ([unit][pixel]) into the workspace.
-//   k_mlp_wg     dW_l = sum_p dz_l h_(l-1)^T and db_l = sum_p dz_l: the pixels
-//                are the MFMA contraction, read straight from the unit-major
-//                planes (8 consecutive pixels of one unit = one fragment; dz
-//                split into bf16 hi + lo as it is loaded); split over pixel
-//                chunks (x) and layers (y), float atomics into the gradient.
-// Workspace, Bp = B rounded up to 64 pixels: X [16][Bp] bf16 (the decoder
-// input, then a row of ones), H1, H2 [64][Bp] bf16, DZ1, DZ2 [64][Bp] and
-// DZ3 [K][Bp] float32: 200 + K floats per pixel.
+//                forward ones; straight through the bf16 roundings. The weight
+//                gradients dW_l = sum_p dz_l h_(l-1)^T contract over the
+//                pixels, which lie along the lanes: both operands are turned
+//                by an MFMA against the identity (exact) and the products
+//                accumulate in registers over all of a wave's tiles; the bias
+//                sums accumulate in LDS in float32.
+//   k_mlp_reduce the sum of the workgroups' partial results.
+// One pass over the inputs, nothing per pixel in memory but the outputs.
+// Writing the layer inputs and dz to memory for a second kernel that contracts
+// them (1.3 KB a pixel each way, then float atomics) took 740 us for the
+// semantic loss of 1080 x 720 pixels at K = 128 and 163 us for a decoder step
+// of 65,536; this takes 224 and 43.
+// Workspace: the partial results, 53 KB a workgroup at K = 128.
 #include "legs_internal.h"
 #include "legs_decode_internal.h"
 
@@ -31,7 +33,6 @@ typedef legs_f32x16 f32x16;
 typedef legs_bf16x8 bf16x8;
 
 constexpr int MH = LEGS_MLP_H;                     // 64 hidden units
-static_assert(LEGS_MLP_WS_PER_PIXEL(0) == 8 + 32 + 32 + 64 + 64, "workspace layout");
 
 // Per-pixel weighting of the cross-entropy. ru == NULL: the mean over the
 // batch (Eq. 9). Otherwise the uncertainty-weighted loss of Eqs. 10-12:
@@ -52,26 +53,6 @@ struct InputGrad {
     int64_t dcs, dps;
 };
 
-struct MlpPlanes {
-    int64_t Bp;
-    __bf16 *X, *H1, *H2;
-    float *D1, *D2, *D3;
-};
-
-MlpPlanes mlp_planes(void *ws, int64_t B, int32_t K)
-{
-    MlpPlanes P;
-    P.Bp = (B + 63) / 64 * 64;
-    char *c = static_cast<char *>(ws);
-    P.X = reinterpret_cast<__bf16 *>(c);                  c += 16 * P.Bp * 2;
-    P.H1 = reinterpret_cast<__bf16 *>(c);                 c += MH * P.Bp * 2;
-    P.H2 = reinterpret_cast<__bf16 *>(c);                 c += MH * P.Bp * 2;
-    P.D1 = reinterpret_cast<float *>(c);                  c += MH * P.Bp * 4;
-    P.D2 = reinterpret_cast<float *>(c);                  c += MH * P.Bp * 4;
-    P.D3 = reinterpret_cast<float *>(c);
-    return P;
-}
-
 // W^T fragments of the backward: (block, k-step, lane, e) = row 32 block +
 // lane % 32 of W^T (a unit of the layer below), column legs_khid(k-step,
 // lane / 32, e) (a unit of the layer above).
@@ -82,26 +63,33 @@ struct MlpBwdLds {
     bf16x8 t1[4 * 64];              // W1^T: 8 rows (block padded to 32) x 64
 };
 
-template <int KB>
+template <int KB, int NT>
 __device__ __forceinline__ void mlp_stage_bwd(const float *__restrict__ params, MlpBwdLds<KB> &T)
 {
     const float *W1 = params + LEGS_MLP_OFF_W1, *W2 = params + LEGS_MLP_OFF_W2, *W3 = params + LEGS_MLP_OFF_W3;
-    const int tid = threadIdx.x, nt = blockDim.x;
     constexpr int S3 = 2 * KB;
-    for (int i = tid; i < 2 * S3 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, ks = (i >> 9) % S3, mb = (i >> 9) / S3;
-        reinterpret_cast<__bf16 *>(T.t3)[i] = (__bf16)W3[legs_khid(ks, l >> 5, e) * MH + 32 * mb + (l & 31)];
-    }
-    for (int i = tid; i < 2 * 4 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, ks = (i >> 9) & 3, mb = i >> 11;
-        reinterpret_cast<__bf16 *>(T.t2)[i] = (__bf16)W2[legs_khid(ks, l >> 5, e) * MH + 32 * mb + (l & 31)];
-    }
-    for (int i = tid; i < 4 * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, ks = i >> 9;
-        const int row = l & 31;
-        reinterpret_cast<__bf16 *>(T.t1)[i] =
-            row < LEGS_MLP_IN ? (__bf16)W1[legs_khid(ks, l >> 5, e) * LEGS_MLP_IN + row] : (__bf16)0.0f;
-    }
+    legs_stage_frags<2 * S3 * 64, NT, 4>(T.t3, [&](int i) {
+        const int l = i & 63, ks = (i >> 6) % S3, mb = (i >> 6) / S3;
+        bf16x8 f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = (__bf16)W3[legs_khid(ks, l >> 5, e) * MH + 32 * mb + (l & 31)];
+        return f;
+    });
+    legs_stage_frags<2 * 4 * 64, NT, 2>(T.t2, [&](int i) {
+        const int l = i & 63, ks = (i >> 6) & 3, mb = i >> 8;
+        bf16x8 f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = (__bf16)W2[legs_khid(ks, l >> 5, e) * MH + 32 * mb + (l & 31)];
+        return f;
+    });
+    legs_stage_frags<4 * 64, NT, 1>(T.t1, [&](int i) {
+        const int l = i & 63, ks = i >> 6, row = l & 31;
+        bf16x8 f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            f[e] = row < LEGS_MLP_IN ? (__bf16)W1[legs_khid(ks, l >> 5, e) * LEGS_MLP_IN + row] : (__bf16)0.0f;
+        return f;
+    });
 }
 
 __device__ __forceinline__ void split8(const f32x16 &z, int first, bf16x8 &hi, bf16x8 &lo)
@@ -114,33 +102,169 @@ __device__ __forceinline__ void split8(const f32x16 &z, int first, bf16x8 &hi, b
     }
 }
 
-template <int KB, bool NORM>
-__global__ void __launch_bounds__(256)
-k_mlp_fb(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, const int32_t *__restrict__ labels,
-         const float *__restrict__ params, MlpPlanes W, float *__restrict__ loss, CeWeights cw, InputGrad ig)
+__device__ __forceinline__ bf16x8 cvt8(const f32x16 &z, int first)
 {
-    constexpr int K = 32 * KB;
-    __shared__ MlpLds L;
-    __shared__ MlpBwdLds<KB> T;
+    bf16x8 f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = (__bf16)z[first + e];
+    return f;
+}
+
+// A 32-unit x 32-pixel block held as two B fragments (lane = pixel, k-slots =
+// units in accumulator order) turned into two fragments with lane = unit and
+// k-slots = pixels: as the A operand against the identity, the matrix unit
+// returns the block transposed and exact (every product is by 1 or 0). id: this
+// lane's identity fragments in LDS.
+__device__ __forceinline__ f32x16 transpose_block(const bf16x8 &f0, const bf16x8 &f1, const bf16x8 *id)
+{
+    return legs_mfma(f1, id[LEGS_WAVE], legs_mfma(f0, id[0], (f32x16){}));
+}
+
+// Accumulators of the weight gradients, 32 x 32 blocks (row = unit of the
+// layer, column = its input). Layer 1 has 8 inputs and the bias: its two unit
+// blocks share one accumulator, in columns 0 .. 8 and 16 .. 24.
+template <int KB>
+struct MlpGrad {
+    f32x16 w3[KB][2], w2[2][2], w1;
+};
+
+// dW block += dz (hi + lo parts) times the transposed layer input, over the
+// tile's 32 pixels.
+template <int NB>
+__device__ __forceinline__ void wgrad_block(const bf16x8 (&hi)[2], const bf16x8 (&lo)[2], const bf16x8 (&in)[NB][2],
+                                            const bf16x8 *id, f32x16 *acc)
+{
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+        const f32x16 t = part ? transpose_block(lo[0], lo[1], id) : transpose_block(hi[0], hi[1], id);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const bf16x8 a = cvt8(t, 8 * g);
+#pragma unroll
+            for (int n = 0; n < NB; ++n) acc[n] = legs_mfma(a, in[n][g], acc[n]);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);   // one block's operands live at a time
+}
+
+// Bias sums of a dz block: each lane adds its 16 values to its own words of LDS
+// (read, add and write back: LDS float atomics took 600 cycles a wave here).
+__device__ __forceinline__ void bias_add(float4 *bias, const f32x16 &z)
+{
+    float4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = bias[q * LEGS_WAVE];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        bias[q * LEGS_WAVE] = make_float4(v[q].x + z[4 * q], v[q].y + z[4 * q + 1], v[q].z + z[4 * q + 2],
+                                          v[q].w + z[4 * q + 3]);
+}
+
+// A workgroup's partial result: the weight-gradient accumulators in register
+// order, [16-value block][4 float4][lane], then the biases of layers 3 and 2,
+// then the loss.
+constexpr int mlp_acc_blocks(int KB) { return 2 * KB + 4 + 1; }
+constexpr int mlp_part_floats(int KB) { return mlp_acc_blocks(KB) * 1024 + (KB + 2) * 32 + 1; }
+
+template <int KB>
+__device__ __forceinline__ f32x16 &mlp_acc(MlpGrad<KB> &G, int i)
+{
+    return i < 2 * KB ? G.w3[i / 2][i % 2] : i < 2 * KB + 4 ? G.w2[(i - 2 * KB) / 2][(i - 2 * KB) % 2] : G.w1;
+}
+
+// Parameter that word i of a partial result adds to (np: the loss, -1: none).
+template <int KB>
+__device__ __forceinline__ int mlp_part_param(int i)
+{
+    constexpr int NA = mlp_acc_blocks(KB) * 1024;
+    if (i >= NA) {
+        const int u = i - NA;
+        return u < 32 * KB ? LEGS_MLP_OFF_B3(KB) + u
+                           : u < 32 * (KB + 2) ? LEGS_MLP_OFF_B2 + u - 32 * KB : (int)LEGS_MLP_NPARAMS(KB);
+    }
+    const int blk = i >> 10, q = (i >> 8) & 3, lane = (i >> 2) & 63, col = lane & 31;
+    const int row = legs_drow(4 * q + (i & 3), lane >> 5);
+    if (blk < 2 * KB) return LEGS_MLP_OFF_W3 + (32 * (blk >> 1) + row) * MH + 32 * (blk & 1) + col;
+    if (blk < 2 * KB + 4) {
+        const int k = blk - 2 * KB;
+        return LEGS_MLP_OFF_W2 + (32 * (k >> 1) + row) * MH + 32 * (k & 1) + col;
+    }
+    const int unit = 32 * (col >> 4) + row, in = col & 15;
+    return in < LEGS_MLP_IN ? LEGS_MLP_OFF_W1 + unit * LEGS_MLP_IN + in
+                            : in == LEGS_MLP_IN ? LEGS_MLP_OFF_B1 + unit : -1;
+}
+
+// Forward, loss, backward and parameter gradient of 32-pixel tiles, one wave
+// each (see the top of the file). Bound by the matrix unit and the VALU work
+// between the layers, so nothing but the features, labels and input gradients
+// touches memory: the weight gradients accumulate in registers over all of a
+// wave's tiles (14 blocks of 32 x 32 at K = 128), which takes one wave per
+// SIMD; the bias sums accumulate in LDS. part: the workgroups' partial results.
+template <int KB, bool NORM>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, const int32_t *__restrict__ labels,
+            const float *__restrict__ params, float *__restrict__ part, CeWeights cw, InputGrad ig)
+{
+    constexpr int NACC = mlp_acc_blocks(KB);
+    // id: the identity in accumulator order, then the same for the input layer
+    // (8 inputs, then the bias one), as columns 0 .. 8 and as columns 16 .. 24
+    __shared__ struct { MlpLds L; MlpBwdLds<KB> T; bf16x8 id[4 * 64]; float4 bias[4][(KB + 2) * 4 * 64]; } S;
+    static_assert(sizeof(S) <= 163840 && sizeof(S) >= 3 * NACC * 4096, "the gradient sums reuse the LDS");
+    MlpLds &L = S.L;
+    MlpBwdLds<KB> &T = S.T;
     mlp_stage_weights<KB, 256>(params, L);
-    mlp_stage_bwd<KB>(params, T);
-    __syncthreads();
+    mlp_stage_bwd<KB, 256>(params, T);
     const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
-    const int64_t tiles = W.Bp / 32;
+    {
+        bf16x8 f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int c = wave < 2 ? legs_drow(8 * wave + e, h) : (h == 0 ? e : (e == 0 ? LEGS_MLP_IN : -1));
+            f[e] = (__bf16)(c >= 0 && (lane & 31) == c + (wave == 3 ? 16 : 0) ? 1.0f : 0.0f);
+        }
+        S.id[wave * 64 + lane] = f;
+    }
+    float4 *bias = &S.bias[wave][lane];
+#pragma unroll
+    for (int i = 0; i < (KB + 2) * 4; ++i) bias[i * 64] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    __syncthreads();
+    const int64_t tiles = (B + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * 4;
     const float invB = 1.0f / (float)B;
+    MlpGrad<KB> G = {};
     float lsum = 0.0f;
-    MlpTile<KB> F;
-    for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < tiles; tile += stride) {
+    // a pixel's inputs, read one tile ahead: the features (lower lane half), the
+    // four that this half's input gradients belong to, the label and R_u
+    struct Inputs {
+        float v[LEGS_MLP_IN], f[4], ru;
+        int y;
+    };
+    const auto load = [&](int64_t tile) {
+        Inputs in;
+        const int64_t p = tile * 32 + (lane & 31);
+        const bool valid = p < B;
+#pragma unroll
+        for (int e = 0; e < LEGS_MLP_IN; ++e) in.v[e] = (h == 0 && valid) ? legs_ldfeat(feat, p, e, cs, ps) : 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            in.f[r] = (NORM && ig.d_feat && valid) ? legs_ldfeat(feat, p, 4 * h + r, cs, ps) : 0.0f;
+        in.y = valid ? labels[p] : -1;
+        in.ru = cw.ru && valid ? cw.ru[p] : 0.0f;
+        return in;
+    };
+    int64_t tile = (int64_t)blockIdx.x * 4 + wave;
+    Inputs next = load(tile);   // (past the last tile: nothing is read)
+    for (; tile < tiles; tile += stride) {
         int off = 0;
         asm volatile("" : "+s"(off));   // fragments are re-read from LDS every tile
         const int ln = lane + off;
+        const bf16x8 *id = S.id + ln;
         const int64_t p = tile * 32 + (lane & 31);
         const bool valid = p < B;
-        float v[LEGS_MLP_IN];
-#pragma unroll
-        for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = (h == 0 && valid) ? legs_ldfeat(feat, p, e, cs, ps) : 0.0f;
-        mlp_tile_forward<KB, NORM>(L, v, F, off);
+        const Inputs in = next;
+        next = load(tile + stride);
+        MlpTile<KB> F;
+        mlp_tile_forward<KB, NORM>(L, in.v, F, off);
         // softmax over the pixel's K logits (this lane and its partner)
         float mx = -INFINITY;
 #pragma unroll
@@ -148,125 +272,122 @@ k_mlp_fb(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, cons
 #pragma unroll
             for (int r = 0; r < 16; ++r) mx = fmaxf(mx, F.z3[b][r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, LEGS_WAVE));
-        float sum = 0.0f;
+        // register (b, r) of this lane holds class 32 b + drow(r, 0) + 4 h
+        const int y = in.y, yh = y - 4 * h;
+        float sum = 0.0f, zy = 0.0f;   // zy: the label's logit, in the lane that holds it
 #pragma unroll
-        for (int b = 0; b < KB; ++b)
+        for (int b = 0; b < KB; ++b) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sum += __expf(F.z3[b][r] - mx);
+            for (int r = 0; r < 16; ++r) {
+                zy = yh == 32 * b + legs_drow(r, 0) ? F.z3[b][r] : zy;
+                F.z3[b][r] = __expf(F.z3[b][r] - mx);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum += F.z3[b][r];
+        }
         sum += __shfl_xor(sum, 32, LEGS_WAVE);
         const float inv = 1.0f / sum;
-        const int y = valid ? labels[p] : -1;
         float wpx = valid ? invB : 0.0f;
         if (cw.ru && valid) {
-            const float ru = cw.ru[p];
+            const float ru = in.ru;
             wpx = cw.lce * (1.0f - ru) * cw.inv_hw;
             if (h == 0) lsum += cw.lu * ru * cw.inv_hw;
         }
-        // dz3 in place of the logits: (p - onehot) w_p; the loss and dL/dR_u
-#pragma unroll
-        for (int b = 0; b < KB; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int k = 32 * b + legs_drow(r, h);
-                const float pr = __expf(F.z3[b][r] - mx) * inv;
-                if (k == y) {
-                    const float ce = mx + __logf(sum) - F.z3[b][r];
-                    lsum += ce * wpx;
-                    if (cw.ru) cw.d_ru[p] = (cw.lu - cw.lce * ce) * cw.inv_hw;
-                }
-                F.z3[b][r] = (pr - (k == y ? 1.0f : 0.0f)) * wpx;
-            }
-        // layer inputs to the workspace (unit-major): X rows 0..7 the bf16
-        // input, row 8 ones (the bias column of layer 1), rows 9..15 zero
-        if (h == 0) {
-            const __bf16 z0 = (__bf16)0.0f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) W.X[(int64_t)e * W.Bp + p] = valid ? F.x[e] : z0;
-            W.X[8 * W.Bp + p] = valid ? (__bf16)1.0f : z0;
-#pragma unroll
-            for (int e = 9; e < 16; ++e) W.X[(int64_t)e * W.Bp + p] = z0;
+        if (y >= 0 && y < 32 * KB && h == ((y >> 2) & 1)) {
+            const float ce = mx + __logf(sum) - zy;
+            lsum += ce * wpx;
+            if (cw.ru) cw.d_ru[p] = (cw.lu - cw.lce * ce) * cw.inv_hw;
         }
+        __builtin_amdgcn_sched_barrier(0);
+        // the layer inputs transposed: columns of the weight gradients
+        bf16x8 h2t[2][2];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int64_t o = (int64_t)legs_khid(ks, h, e) * W.Bp + p;
-                W.H1[o] = valid ? F.h1[ks][e] : (__bf16)0.0f;
-                W.H2[o] = valid ? F.h2[ks][e] : (__bf16)0.0f;
-            }
-#pragma unroll
-        for (int b = 0; b < KB; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) W.D3[(int64_t)(32 * b + legs_drow(r, h)) * W.Bp + p] = F.z3[b][r];
-        // dh2 = W3^T dz3 (two blocks of 32 hidden units), gated by h2 > 0
-        bf16x8 bh[2 * KB], bl[2 * KB];
+        for (int n = 0; n < 2; ++n) {
+            const f32x16 t = transpose_block(F.h2[2 * n], F.h2[2 * n + 1], id);
+            h2t[n][0] = cvt8(t, 0);
+            h2t[n][1] = cvt8(t, 8);
+        }
+        // dz3 = (p - onehot) w_p; dh2 = W3^T dz3, dW3 = dz3 h2^T
+        const float pw = inv * wpx;
+        int yh2 = yh;
+        asm volatile("" : "+v"(yh2));   // the compares are made again: 64 masks kept from above would be spilled
+        f32x16 dh[2] = {};
 #pragma unroll
         for (int b = 0; b < KB; ++b) {
-            split8(F.z3[b], 0, bh[2 * b], bl[2 * b]);
-            split8(F.z3[b], 8, bh[2 * b + 1], bl[2 * b + 1]);
-        }
-        f32x16 dz[2];
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            f32x16 acc = {};
-#pragma unroll
-            for (int ks = 0; ks < 2 * KB; ++ks) {
-                const bf16x8 a = T.t3[(mb * 2 * KB + ks) * 64 + ln];
-                acc = legs_mfma(a, bl[ks], legs_mfma(a, bh[ks], acc));
-            }
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                if (!((float)F.h2[2 * mb + (r >> 3)][r & 7] > 0.0f)) acc[r] = 0.0f;
-            dz[mb] = acc;
+                F.z3[b][r] = fmaf(F.z3[b][r], pw, yh2 == 32 * b + legs_drow(r, 0) ? -wpx : 0.0f);
+            bias_add(bias + b * 4 * LEGS_WAVE, F.z3[b]);
+            bf16x8 hi[2], lo[2];
+            split8(F.z3[b], 0, hi[0], lo[0]);
+            split8(F.z3[b], 8, hi[1], lo[1]);
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const bf16x8 a = T.t3[(mb * 2 * KB + 2 * b + q) * 64 + ln];
+                    dh[mb] = legs_mfma(a, lo[q], legs_mfma(a, hi[q], dh[mb]));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            wgrad_block<2>(hi, lo, h2t, id, G.w3[b]);
         }
-        // dz2 stored; dh1 = W2^T dz2 gated by h1 > 0
-        bf16x8 ch[4], cl[4];
+        // dz2 = dh2 gated by h2 > 0; dh1 = W2^T dz2, dW2 = dz2 h1^T
+        bf16x8 h1t[2][2];
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) W.D2[(int64_t)(32 * mb + legs_drow(r, h)) * W.Bp + p] = dz[mb][r];
-            split8(dz[mb], 0, ch[2 * mb], cl[2 * mb]);
-            split8(dz[mb], 8, ch[2 * mb + 1], cl[2 * mb + 1]);
+        for (int n = 0; n < 2; ++n) {
+            const f32x16 t = transpose_block(F.h1[2 * n], F.h1[2 * n + 1], id);
+            h1t[n][0] = cvt8(t, 0);
+            h1t[n][1] = cvt8(t, 8);
         }
+        f32x16 dg[2] = {};
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            f32x16 acc = {};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const bf16x8 a = T.t2[(mb * 4 + ks) * 64 + ln];
-                acc = legs_mfma(a, cl[ks], legs_mfma(a, ch[ks], acc));
-            }
+        for (int b = 0; b < 2; ++b) {
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                if (!((float)F.h1[2 * mb + (r >> 3)][r & 7] > 0.0f)) acc[r] = 0.0f;
-            dz[mb] = acc;
+                if (!((float)F.h2[2 * b + (r >> 3)][r & 7] > 0.0f)) dh[b][r] = 0.0f;
+            bias_add(bias + (KB + b) * 4 * LEGS_WAVE, dh[b]);
+            bf16x8 hi[2], lo[2];
+            split8(dh[b], 0, hi[0], lo[0]);
+            split8(dh[b], 8, hi[1], lo[1]);
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const bf16x8 a = T.t2[(mb * 4 + 2 * b + q) * 64 + ln];
+                    dg[mb] = legs_mfma(a, lo[q], legs_mfma(a, hi[q], dg[mb]));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            wgrad_block<2>(hi, lo, h1t, id, G.w2[b]);
         }
+        // dz1 = dh1 gated by h1 > 0; dW1 and db1 against the input and its bias one
+        f32x16 dxa = {};
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
+        for (int b = 0; b < 2; ++b) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) W.D1[(int64_t)(32 * mb + legs_drow(r, h)) * W.Bp + p] = dz[mb][r];
+            for (int r = 0; r < 16; ++r)
+                if (!((float)F.h1[2 * b + (r >> 3)][r & 7] > 0.0f)) dg[b][r] = 0.0f;
+            bf16x8 hi[2], lo[2];
+            split8(dg[b], 0, hi[0], lo[0]);
+            split8(dg[b], 8, hi[1], lo[1]);
+            if (ig.d_feat) {
+                // dx = W1^T dz1: inputs 4 h + r in registers r = 0..3
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const bf16x8 a = T.t1[(2 * b + q) * 64 + ln];
+                    dxa = legs_mfma(a, lo[q], legs_mfma(a, hi[q], dxa));
+                }
+            }
+            const f32x16 t = legs_mfma(F.x, id[(2 + b) * LEGS_WAVE], (f32x16){});
+            const bf16x8 xt[1][2] = {{cvt8(t, 0), cvt8(t, 8)}};
+            wgrad_block<1>(hi, lo, xt, id, &G.w1);
         }
         if (ig.d_feat) {
-            // dx = W1^T dz1: inputs 4 h + r in registers r = 0..3
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb) {
-                split8(dz[mb], 0, ch[2 * mb], cl[2 * mb]);
-                split8(dz[mb], 8, ch[2 * mb + 1], cl[2 * mb + 1]);
-            }
-            f32x16 acc = {};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const bf16x8 a = T.t1[ks * 64 + ln];
-                acc = legs_mfma(a, cl[ks], legs_mfma(a, ch[ks], acc));
-            }
-            float dx[4] = {acc[0], acc[1], acc[2], acc[3]};
+            float dx[4] = {dxa[0], dxa[1], dxa[2], dxa[3]};
             if constexpr (NORM) {
-                float f[4], ss = 0.0f;
+                const float (&f)[4] = in.f;
+                float ss = 0.0f;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    f[r] = valid ? legs_ldfeat(feat, p, 4 * h + r, cs, ps) : 0.0f;
-                    ss = fmaf(f[r], f[r], ss);
-                }
+                for (int r = 0; r < 4; ++r) ss = fmaf(f[r], f[r], ss);
                 ss += __shfl_xor(ss, 32, LEGS_WAVE);
                 const float nrm = sqrtf(ss);
                 const float iv = nrm > 0.0f ? 1.0f / nrm : 0.0f;
@@ -283,85 +404,94 @@ k_mlp_fb(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, cons
             }
         }
     }
+    // the workgroup's sums over its lanes and waves
+    float *dst = part + (int64_t)blockIdx.x * mlp_part_floats(KB);
+    float *s_loss = reinterpret_cast<float *>(S.id);   // the last tile's fragments are read
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, LEGS_WAVE);
-    if (lane == 0 && lsum != 0.0f) atomicAdd(loss, lsum);
-}
-
-// dW[m][k] += sum_p (dz_hi + dz_lo)[m][p] B[k][p] over the pixels of this
-// workgroup's chunk, db[m] += sum_p dz[m][p]. Layer (blockIdx.y): 0: DZ1 x X
-// (rows 0..7 the input, row 8 ones -> b1), 1: DZ2 x H1, 2: DZ3 x H2. Wave w
-// owns the 32 rows of block w of dz against every block of B.
-__global__ void __launch_bounds__(256)
-k_mlp_wg(MlpPlanes W, int K, int64_t chunk, float *__restrict__ grad)
-{
-    const int layer = blockIdx.y;
-    const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
-    const float *Dp = layer == 0 ? W.D1 : layer == 1 ? W.D2 : W.D3;
-    const __bf16 *Bp = layer == 0 ? W.X : layer == 1 ? W.H1 : W.H2;
-    const int M = layer == 2 ? K : MH;
-    const int Kb = layer == 0 ? 16 : MH;
-    const int MB = M / 32, NB = (Kb + 31) / 32;
-    if (wave >= MB) return;
-    const int mb = wave, m = 32 * mb + (lane & 31);
-    const int64_t g0 = (int64_t)blockIdx.x * chunk;
-    const int64_t g1 = min(g0 + chunk, W.Bp);
-    const float *Drow = Dp + (int64_t)m * W.Bp + 8 * h;
-    const __bf16 *Bq0 = Bp + (int64_t)(lane & 31) * W.Bp + 8 * h;
-    const __bf16 *Bq1 = Bp + (int64_t)(32 + (lane & 31)) * W.Bp + 8 * h;
-    const bool k0 = (lane & 31) < Kb, k1 = NB > 1;
-    f32x16 acc[2] = {};
-    float dbs = 0.0f;
-#pragma unroll 2
-    for (int64_t g = g0; g < g1; g += 16) {
-        const float4 v0 = *reinterpret_cast<const float4 *>(Drow + g);
-        const float4 v1 = *reinterpret_cast<const float4 *>(Drow + g + 4);
-        const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-        bf16x8 ah, al;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            ah[e] = (__bf16)v[e];
-            al[e] = (__bf16)(v[e] - (float)ah[e]);
-            dbs += v[e];
+    __syncthreads();
+    if (lane == 0) s_loss[wave] = lsum;
+    __syncthreads();
+    for (int u = threadIdx.x; u < (KB + 2) * 32; u += 256) {
+        const int b = u >> 5, q = u & 31;   // unit q of block b: register 4 (q / 8) + q % 4, lane half (q / 4) % 2
+        float s = 0.0f;
+        for (int w = 0; w < 4; ++w) {
+            const float *src = reinterpret_cast<const float *>(&S.bias[w][(b * 4 + (q >> 3)) * 64 + 32 * ((q >> 2) & 1)]);
+#pragma unroll 8
+            for (int i = 0; i < 32; ++i) s += src[4 * ((i + u) & 31) + (q & 3)];
         }
-        const bf16x8 b0 = k0 ? *reinterpret_cast<const bf16x8 *>(Bq0 + g) : (bf16x8){};
-        acc[0] = legs_mfma(al, b0, legs_mfma(ah, b0, acc[0]));
-        if (k1) {
-            const bf16x8 b1 = *reinterpret_cast<const bf16x8 *>(Bq1 + g);
-            acc[1] = legs_mfma(al, b1, legs_mfma(ah, b1, acc[1]));
+        dst[NACC * 1024 + u] = s;
+    }
+    if (threadIdx.x == 0)
+        dst[NACC * 1024 + (KB + 2) * 32] = (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]);
+    __syncthreads();
+    float4 *sum = reinterpret_cast<float4 *>(&S) + lane;
+    if (wave > 0) {
+#pragma unroll
+        for (int i = 0; i < NACC; ++i) {
+            const f32x16 &z = mlp_acc<KB>(G, i);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                sum[((wave - 1) * NACC + i) * 256 + q * 64] = make_float4(z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]);
         }
     }
-    const int KB = K / 32;
-    if (layer != 0) {                                   // row sums: the bias gradient
-        dbs += __shfl_xor(dbs, 32, LEGS_WAVE);
-        float *db = grad + (layer == 1 ? LEGS_MLP_OFF_B2 : LEGS_MLP_OFF_B3(KB));
-        if (h == 0 && dbs != 0.0f) atomicAdd(db + m, dbs);
-    }
+    __syncthreads();
+    if (wave == 0) {
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        if (nb >= NB) continue;
+        for (int i = 0; i < NACC; ++i) {
+            const f32x16 &z = mlp_acc<KB>(G, i);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 32 * mb + legs_drow(r, h);
-            const int col = 32 * nb + (lane & 31);
-            const float x = acc[nb][r];
-            if (col >= Kb || x == 0.0f) continue;
-            if (layer == 0) {
-                if (col < LEGS_MLP_IN) atomicAdd(grad + LEGS_MLP_OFF_W1 + row * LEGS_MLP_IN + col, x);
-                else if (col == LEGS_MLP_IN) atomicAdd(grad + LEGS_MLP_OFF_B1 + row, x);
-            } else {
-                const int o = layer == 1 ? LEGS_MLP_OFF_W2 : LEGS_MLP_OFF_W3;
-                atomicAdd(grad + o + row * MH + col, x);
+            for (int q = 0; q < 4; ++q) {
+                float4 v = make_float4(z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]);
+#pragma unroll
+                for (int w = 0; w < 3; ++w) {
+                    const float4 o = sum[(w * NACC + i) * 256 + q * 64];
+                    v.x += o.x;
+                    v.y += o.y;
+                    v.z += o.z;
+                    v.w += o.w;
+                }
+                float *d = dst + i * 1024 + q * 256 + 4 * lane;   // 4-byte aligned rows
+                d[0] = v.x;
+                d[1] = v.y;
+                d[2] = v.z;
+                d[3] = v.w;
             }
         }
     }
 }
 
+// Sums the nwg partial results: a wave per 16 words, its four lane groups
+// taking every fourth workgroup. ADD: added to grad and loss with atomics
+// (calls on several streams may share them), otherwise stored.
+template <int KB, bool ADD>
 __global__ void __launch_bounds__(256)
-k_zero_f32(float *__restrict__ p, int64_t n)
+k_mlp_reduce(const float *__restrict__ part, int nwg, float *__restrict__ grad, float *__restrict__ loss)
+{
+    constexpr int n = mlp_part_floats(KB);
+    const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE;
+    const int i = (blockIdx.x * 4 + wave) * 16 + (lane & 15);
+    const int param = i < n ? mlp_part_param<KB>(i) : -1;
+    float s = 0.0f;
+    if (param >= 0) {
+#pragma unroll 8
+        for (int g = lane >> 4; g < nwg; g += 4) s += part[(int64_t)g * n + i];
+    }
+    s += __shfl_xor(s, 16, LEGS_WAVE);
+    s += __shfl_xor(s, 32, LEGS_WAVE);
+    if (param >= 0 && lane < 16) {
+        float *dst = param < (int)LEGS_MLP_NPARAMS(KB) ? grad + param : loss;
+        if constexpr (ADD) atomicAdd(dst, s);
+        else *dst = s;
+    }
+}
+
+__global__ void __launch_bounds__(256)
+k_zero_f32(float *__restrict__ p, int64_t n, float *__restrict__ q)
 {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         p[i] = 0.0f;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *q = 0.0f;
 }
 
 } // namespace
@@ -373,38 +503,35 @@ int64_t legs_mlp_workspace_floats(int64_t B, int32_t K)
 
 namespace {
 
-// Forward and backward through the layers, then the weight gradients
-// (accumulated into grad with float atomics).
+// The training kernel, then the sum of its partial results: added to grad and
+// loss, or stored there.
 int32_t mlp_train_kernels(legs_ctx *ctx, const float *feat, int64_t B, int64_t cs, int64_t ps,
                           const int32_t *labels, int32_t K, int32_t mlp_flags, const float *params,
                           float *workspace, float *grad, float *loss, const CeWeights &cw,
-                          const InputGrad &ig, hipStream_t s)
+                          const InputGrad &ig, bool add, hipStream_t s)
 {
-    const int KB = K / 32;
-    if (B == 0) return LEGS_OK;
-    const MlpPlanes W = mlp_planes(workspace, B, K);
-    int64_t g = (W.Bp / 32 + 3) / 4;
-    const int64_t cap = (int64_t)ctx->num_cus * 2;
-    if (g > cap) g = cap;
+    if (B == 0) {
+        if (!add)
+            hipLaunchKernelGGL(k_zero_f32, dim3(64), dim3(256), 0, s, grad, (int64_t)LEGS_MLP_NPARAMS(K / 32), loss);
+        LEGS_CHECK_LAUNCH(ctx);
+        return LEGS_OK;
+    }
+    // one workgroup per CU (one wave per SIMD), each with at least one tile: its
+    // partial result fits in the workspace rows of 64 pixels
+    static_assert(mlp_part_floats(4) <= 64 * LEGS_MLP_WS_PER_PIXEL(128) &&
+                  mlp_part_floats(2) <= 64 * LEGS_MLP_WS_PER_PIXEL(64) &&
+                  mlp_part_floats(1) <= 64 * LEGS_MLP_WS_PER_PIXEL(32), "workspace layout");
+    int64_t g = (B + 127) / 128;
+    if (g > ctx->num_cus) g = ctx->num_cus;
     const bool norm = (mlp_flags & LEGS_MLP_NORMALIZE_INPUT) != 0;
-#define LEGS_MLP_TRAIN(KBV)                                                                                         \
-    if (norm) hipLaunchKernelGGL((k_mlp_fb<KBV, true>), dim3((unsigned)g), dim3(256), 0, s, feat, B, cs, ps, labels, \
-                                 params, W, loss, cw, ig);                                                           \
-    else hipLaunchKernelGGL((k_mlp_fb<KBV, false>), dim3((unsigned)g), dim3(256), 0, s, feat, B, cs, ps, labels,    \
-                            params, W, loss, cw, ig);
-    switch (KB) {
-    case 1: LEGS_MLP_TRAIN(1) break;
-    case 2: LEGS_MLP_TRAIN(2) break;
-    case 4: LEGS_MLP_TRAIN(4) break;
+#define LEGS_MLP_TRAIN(KBV)                                                                                                {                                                                                                                          if (norm) hipLaunchKernelGGL((k_mlp_train<KBV, true>), dim3((unsigned)g), dim3(256), 0, s, feat, B, cs, ps,                                         labels, params, workspace, cw, ig);                                                      else hipLaunchKernelGGL((k_mlp_train<KBV, false>), dim3((unsigned)g), dim3(256), 0, s, feat, B, cs, ps,                                        labels, params, workspace, cw, ig);                                                            const dim3 gr((mlp_part_floats(KBV) + 63) / 64);                                                                       if (add) hipLaunchKernelGGL((k_mlp_reduce<KBV, true>), gr, dim3(256), 0, s, workspace, (int)g, grad, loss);            else hipLaunchKernelGGL((k_mlp_reduce<KBV, false>), gr, dim3(256), 0, s, workspace, (int)g, grad, loss);           }
+    switch (K) {
+    case 32: LEGS_MLP_TRAIN(1) break;
+    case 64: LEGS_MLP_TRAIN(2) break;
+    case 128: LEGS_MLP_TRAIN(4) break;
     default: return legs_set_error(ctx, LEGS_ERR_ARG, "K must be 32, 64 or 128");
     }
 #undef LEGS_MLP_TRAIN
-    LEGS_CHECK_LAUNCH(ctx);
-    // pixel chunks of 256 to 4096 (a multiple of 64), about 256 per layer
-    int64_t chunk = (W.Bp / 256 + 63) / 64 * 64;
-    chunk = chunk < 256 ? 256 : (chunk > 4096 ? 4096 : chunk);
-    const dim3 gw((unsigned)((W.Bp + chunk - 1) / chunk), 3);
-    hipLaunchKernelGGL(k_mlp_wg, gw, dim3(256), 0, s, W, K, chunk, grad);
     LEGS_CHECK_LAUNCH(ctx);
     return LEGS_OK;
 }
@@ -415,13 +542,10 @@ int32_t legs_launch_mlp_grad(legs_ctx *ctx, const float *feat, int64_t B, int64_
                              const int32_t *labels, int32_t K, int32_t mlp_flags, const float *params,
                              float *workspace, float *grad, float *loss, hipStream_t s)
 {
-    const int64_t np = LEGS_MLP_NPARAMS(K / 32);
-    hipLaunchKernelGGL(k_zero_f32, dim3(64), dim3(256), 0, s, grad, np);
-    hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(256), 0, s, loss, (int64_t)1);
-    LEGS_CHECK_LAUNCH(ctx);
     const CeWeights cw = {nullptr, nullptr, 1.0f, 0.0f, 0.0f};
     const InputGrad ig = {nullptr, 0, 0};
-    return mlp_train_kernels(ctx, feat, B, cs, ps, labels, K, mlp_flags, params, workspace, grad, loss, cw, ig, s);
+    return mlp_train_kernels(ctx, feat, B, cs, ps, labels, K, mlp_flags, params, workspace, grad, loss, cw, ig, false,
+                             s);
 }
 
 int32_t legs_launch_semantic_loss_grad(legs_ctx *ctx, const float *feat, const float *ru, int64_t P,
@@ -433,7 +557,8 @@ int32_t legs_launch_semantic_loss_grad(legs_ctx *ctx, const float *feat, const f
 {
     const CeWeights cw = {ru, d_ru, lambda_ce, lambda_u, inv_hw};
     const InputGrad ig = {d_feat, dcs, dps};
-    return mlp_train_kernels(ctx, feat, P, cs, ps, labels, K, mlp_flags, params, workspace, grad, loss, cw, ig, s);
+    return mlp_train_kernels(ctx, feat, P, cs, ps, labels, K, mlp_flags, params, workspace, grad, loss, cw, ig, true,
+                             s);
 }
 
 // ---- fused Adam over parameter groups -------------------------------------------

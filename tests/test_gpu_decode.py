@@ -282,3 +282,31 @@ def test_top1_inputs_at_tile_edges(ctx, DEC, K, normalize):
             for src in ((rows, P, 1, 8), (planes, P, P, 1), (wide.view(-1)[2:], P, 1, 11)):
                 assert torch.equal(dec(ctx, src, p, K, normalize=normalize)[0], want)
             assert torch.equal(dec(ctx, (rows, P, 1, 8), shifted, K, normalize=normalize)[0], want)
+
+
+@pytest.mark.parametrize("K,B", [(32, 1), (64, 33), (128, 128), (128, 129), (32, 4097), (64, 32768 + 1), (128, 40000)])
+def test_mlp_gradient_sizes(ctx, DEC, K, B):
+    """Batches around the training kernel's tiles (32 pixels), workgroups (128)
+    and launch (a workgroup per CU), every K, raw and normalised input. The
+    tolerance is the one of float32 sums of split-bf16 (16 significant bits)
+    upstream gradients times exact bf16 operands: 3e-5 of a segment's norm."""
+    normalize = K != 64
+    f = features(B + 20, 70 + K)[20:].copy()
+    y = np.random.default_rng(71 + B).integers(0, K, B).astype(np.int32)
+    ws, bs = synth.mlp_init((8, 64, 64, K), 72 + K)
+    note(f"mlp gradient K={K} B={B}")
+    tr = DEC.MlpTrainer(ctx, DEC.mlp_pack(ws, bs), K, B, normalize=normalize)
+    fd_, yd = torch.from_numpy(f).cuda(), torch.from_numpy(y).cuda()
+    tr.grad.fill_(7.0)                                     # overwritten, not added to
+    grad, loss = tr.grad_only(DEC.rowmajor_features(fd_), yd)
+    _, pr = DEC.decode_mlp(ctx, DEC.rowmajor_features(fd_), tr.params, K, probs=True, normalize=normalize)
+    torch.cuda.synchronize()
+    hid = []
+    PT.check_mlp_probs(pr.cpu().numpy().astype(np.float64), f, ws, bs, normalize, hidden_out=hid)
+    loss_ref, gW, gb = D.mlp_grads(f, y, ws, bs, normalize=normalize, hidden=hid)
+    assert loss.item() == pytest.approx(loss_ref, rel=1e-6)
+    g, off = grad.cpu().numpy().astype(np.float64), 0
+    for part in [q for w, b in zip(gW, gb) for q in (w.reshape(-1), b)]:
+        assert np.linalg.norm(g[off:off + part.size] - part) <= 3e-5 * np.linalg.norm(part), (off, part.size)
+        off += part.size
+    assert off == g.size
