@@ -8,36 +8,48 @@
 // v_mfma_f32_32x32x16_f16.
 //
 //  k_quant_prep      S once per call into the LDS image of each 128-dimension
-//                    chunk (A-operand fragments, code rows x dimensions), and
-//                    1 / |S_j| of both parts.
-//  k_quant_pass      one workgroup of 4 waves per CU, 32-feature tiles (two
-//                    per wave at N = 32, sharing every codebook fragment read
-//                    from LDS): the codebook image of each chunk and every
-//                    wave's feature fragments stream straight into one of two
-//                    LDS buffers (global_load_lds, no registers) while the
-//                    other feeds the MFMAs;
-//                    the 32 x N dot products of each part stay in registers
-//                    (transposed: codes x features), the feature norms are
-//                    summed from the same B fragments. Then per feature the
-//                    distance D_j = cos^C_j + lambda cos^D_j, its argmax (first
-//                    maximum) and its softmax. ASSIGN: index, histogram of the
-//                    indices, sum of the softmax (the mean selection
-//                    probability), cosine loss. GRAD: dL_q/dD_j with the final
-//                    histogram, written (scaled by 2^10 K) as half weights
-//                    W^C, W^D (N x Kp, in the weight gradient's MFMA operand
-//                    order: one 16-byte fragment per lane after an 8 x 8 lane
-//                    transpose) with 1 / |F_i| of both parts, and the column
-//                    sums sum_i dL/dD_ij cos_ij per part. Column sums over the 32
-//                    features of a wave go through a transpose reduction
-//                    (five lane-bit stages) before the LDS and global atomics.
+//                    chunk (A-operand fragments, code rows x dimensions),
+//                    1 / |S_j| of both parts, and the sums and the gradient
+//                    cleared.
+//  k_quant_pass      one workgroup of 8 waves per CU, 32 features per wave: the
+//                    codebook image of each 128-dimension chunk streams into
+//                    one of two LDS buffers (global_load_lds, no registers) and
+//                    each wave's feature fragments into registers one chunk
+//                    ahead, across the rounds as well, so that loads are in
+//                    flight during the softmax. The 32 x N dot products of a
+//                    wave stay in registers (transposed: codes x features); at
+//                    the end of the CLIP part they become its cosines. The
+//                    feature norms are summed from the same fragments. Then per
+//                    feature the distance D_j = cos^C_j + lambda cos^D_j, its
+//                    argmax (first maximum) and its softmax: index, histogram
+//                    of the indices, sum of the softmax (the mean selection
+//                    probability), cosine loss and, for the gradient, 1 / |F_i|
+//                    and the cosines of both parts in register order (1 KB
+//                    contiguous per store).
+//                    Bound by memory latency (one 8 KB chunk in flight per
+//                    wave; two need 30 registers more than there are and
+//                    spill, 1.36 ms a call instead of 1.21). 1M features x 896
+//                    dimensions at N = 128: 640 us with the cosines' 1 GB,
+//                    where four waves of 32 features with the features through
+//                    LDS too and a drain per round took 695 without them.
+//  k_quant_weights   dL_q/dD_ij with the final histogram from the stored
+//                    cosines, in place, as half weights (scaled by 2^10 K) in
+//                    the weight gradient's MFMA operand order (one 16-byte
+//                    fragment per lane after an 8 x 8 lane transpose), and the
+//                    sums over i of dL/dD_ij cos_ij. Reading 1 GB back takes
+//                    295 us where a second pass over the features took 876.
 //  k_quant_wgrad     sum_i W_ij F_ic / |F_i| for every code j and dimension c:
 //                    FP16 MFMA with the features as the contraction (the
 //                    weight fragments 1 KB contiguous per wave), the unit
 //                    feature rows staged through LDS transposed
 //                    (dimension-major) in steps of 64, split over feature
-//                    ranges (x) and 128-dimension chunks (y), float atomics
-//                    into the gradient.
-//  k_quant_finish    the gradient's second term, the losses, r and p.
+//                    ranges (x) and groups of two 128-dimension chunks (y: the
+//                    weights are read once per group), float atomics into the
+//                    gradient. Two workgroups per CU, one round of them: 632 us
+//                    at the size above, with its weights of both parts and a
+//                    chunk per group 660; one workgroup per CU makes the call
+//                    35 % slower, four 9 %, one chunk per group 19 %.
+//  k_quant_finish    the column-sum term, the losses, r and p.
 #include "legs_internal.h"
 #include "legs_decode_internal.h"
 #include "wave_reduce.h"
@@ -53,12 +65,9 @@ constexpr int QCH = 128;           // dimensions per chunk
 // lambda_lb) in magnitude): the scale keeps the small terms of the
 // load-balancing loss out of the half-precision subnormal range.
 constexpr float WSCALE = 1024.0f;
-constexpr int QTHREADS = 256;      // 4 waves, one per SIMD
-constexpr int QGROUP = 256;        // feature padding of the half weights W^C, W^D
-// 32-feature tiles per wave (every codebook fragment read from LDS feeds QNT
-// MFMAs): two at N = 32, one from N = 64 (the LDS holds two chunks of the
-// codebook image and of every wave's feature fragments)
-template <int KB> constexpr int qnt() { return KB == 1 ? 2 : 1; }
+constexpr int QTHREADS = 512;      // 8 waves, two per SIMD
+constexpr int QGROUP = 256;        // features per workgroup round (the cosines and weights are padded to it)
+static_assert(QTHREADS / LEGS_WAVE * 32 == QGROUP, "a workgroup's round is one padding group");
 
 // s_waitcnt vmcnt(N) (expcnt and lgkmcnt not waited for).
 template <int N>
@@ -108,10 +117,16 @@ __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
 // dimensions 128 ch + 16 ks + 8 (lane / 32) + [0, 8).
 template <int KB>
 __global__ void __launch_bounds__(256)
-k_quant_prep(const float *__restrict__ S, int d, int dC, f16x8 *__restrict__ img, float *__restrict__ invS)
+k_quant_prep(const float *__restrict__ S, int d, int dC, f16x8 *__restrict__ img, float *__restrict__ invS,
+             uint32_t *__restrict__ counts, uint32_t *__restrict__ sums, int nsums, float *__restrict__ grad)
 {
     constexpr int NF = KB * 8 * 64;
     const int nch = d / QCH;
+    const int t0 = blockIdx.x * 256 + threadIdx.x;
+    for (int q = t0; q < 32 * KB; q += gridDim.x * 256) counts[q] = 0u;
+    for (int q = t0; q < nsums; q += gridDim.x * 256) sums[q] = 0u;
+    if (grad)
+        for (int q = t0; q < 32 * KB * d; q += gridDim.x * 256) grad[q] = 0.0f;
     for (int q = blockIdx.x * 256 + threadIdx.x; q < nch * NF; q += gridDim.x * 256) {
         const int ch = q / NF, f = q % NF;
         const int l = f & 63, ks = (f >> 6) & 7, mb = f >> 9;
@@ -153,211 +168,213 @@ struct QuantArgs {
     int32_t *index;             // [K]
     uint32_t *counts;           // [N]
     float *psum;                // [N] sum of softmax over features
-    float *lsum;                // [1] cosine-loss sum
-    _Float16 *Wc, *Wd;          // N x Kp half weights 2^10 K dL/dD (lambda_dino K dL/dD for DINO) in
-                                // MFMA operand order (legs_lt::frag_at, codes as rows, features as columns)
+    double *lsum;               // [1] cosine-loss sum
+    float4 *cos;                // [Kp / 32][2 parts][N / 8][64 lanes] cosines (codes 8 q + 4 h .. + 3 of feature l % 32)
     float *invF;                // [2][Kp] 1 / |F_i| of both parts (0 past K)
-    float *col;                 // [2][N]
+    float *col;                 // [2][N] sum_i dL/dD_ij cos_ij (lambda dL/dD for DINO)
 };
 
-// Sums over the 32 features of each lane half of V values per lane, then LDS
-// atomics: value v of a lane is code code_of(v) (lane half fixed).
-template <int V, typename CodeOf>
-__device__ __forceinline__ void half_wave_sums(float (&v)[V], float *dst, CodeOf code_of)
+// Half weights 2^10 K dL/dD of the 32 features from i (a multiple of 32) in
+// the place of their cosines: the first quarter of it, in MFMA operand order
+// (legs_lt::frag_at, codes as rows, features as columns).
+__device__ __forceinline__ _Float16 *quant_weights(void *cos, int N, int64_t i)
 {
-    const int lane = __lane_id();
-    legs_tr::run<4, V, V>(v, lane);
-    constexpr int R = legs_tr::final_k(V, 5);
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const int ix = legs_tr::src_index<4, V>(k, lane);
-        if (ix >= 0 && v[k] != 0.0f) atomicAdd(dst + code_of(ix), v[k]);
-    }
+    return reinterpret_cast<_Float16 *>(static_cast<char *>(cos) + (i >> 5) * (256 * (int64_t)N));
 }
 
-template <int KB, bool GRAD>
+// Adds the sums of v over the 32 features of each lane half to this lane's
+// shares: legs_tr::final_k slots, one code each (src_index names it).
+template <int V>
+__device__ __forceinline__ void half_wave_sums(float (&v)[V], float (&sum)[legs_tr::final_k(V, 5)], int lane)
+{
+    legs_tr::run<4, V, V>(v, lane);
+#pragma unroll
+    for (int k = 0; k < legs_tr::final_k(V, 5); ++k) sum[k] += v[k];
+}
+
+// A workgroup's shares of half_wave_sums, wave after wave, into dst (LDS; code
+// order). Plain reads and writes: LDS float atomics take hundreds of cycles.
+template <int V, int WAVES>
+__device__ __forceinline__ void block_sums(const float (&sum)[legs_tr::final_k(V, 5)], float *dst, int lane, int wave)
+{
+    for (int w = 0; w < WAVES; ++w) {
+        __syncthreads();
+        if (wave == w) {
+#pragma unroll
+            for (int k = 0; k < legs_tr::final_k(V, 5); ++k) {
+                const int ix = legs_tr::src_index<4, V>(k, lane);
+                if (ix < 0) continue;
+                const int j = 32 * (ix >> 4) + legs_drow(ix & 15, lane >> 5);
+                dst[j] = w == 0 ? sum[k] : dst[j] + sum[k];
+            }
+        }
+    }
+    __syncthreads();
+}
+
+template <int KB, bool KEEP>
 __global__ void __launch_bounds__(QTHREADS)
 k_quant_pass(QuantArgs A)
 {
-    constexpr int N = 32 * KB, NF = KB * 8 * 64, PER = NF / QTHREADS;
-    constexpr int QNT = qnt<KB>(), ROUND = QTHREADS / LEGS_WAVE * 32 * QNT;   // features per round
-    static_assert(NF % QTHREADS == 0, "fragments per thread");
-    // two LDS buffers, each the codebook image of a chunk and every wave's
-    // feature fragments; distinct arrays, so that the compiler can tell the
-    // reads of one buffer from the loads still landing in the other
-    constexpr int FEF = QTHREADS / LEGS_WAVE * QNT * 8 * LEGS_WAVE;
+    constexpr int N = 32 * KB, NF = KB * 8 * 64;
+    // two LDS buffers for the codebook image of a chunk; distinct arrays, so that
+    // the compiler can tell the reads of one from the loads landing in the other
     __shared__ f16x8 frag0[NF], frag1[NF];
-    __shared__ f16x8 feat0[FEF], feat1[FEF];
     __shared__ float s_inv[2][N];
-    __shared__ float s_ab[2 * N];         // psum | col^C then col^D
     __shared__ uint32_t s_cnt[N];
-    __shared__ float s_r[N];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
-    // position in the lane's group of 8 for the transposed weight stores
-    const int i8 = lane & 7;
-    const bool b1 = (lane & 2) != 0;
-    const uint32_t psel = (lane & 1) ? 0x03020706u : 0x05040100u;
-    const float invK = 1.0f / (float)A.K;
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int j = tid; j < N; j += QTHREADS) {
         s_inv[0][j] = A.invS[j];
         s_inv[1][j] = A.invS[N + j];
-        s_ab[j] = 0.0f;
-        s_ab[N + j] = 0.0f;
         s_cnt[j] = 0u;
-        if (GRAD) s_r[j] = (float)A.counts[j] * invK;
     }
     float lcos = 0.0f;
+    float psum[legs_tr::final_k(KB * 16, 5)] = {};
     const int nch = A.d / QCH, nchC = A.dC / QCH;
-    // the gradient pass writes every column of W^C, W^D below Kp (zeros past
-    // K: the weight-gradient kernel reads whole 16-byte fragments)
-    const int64_t groups = ((GRAD ? A.Kp : A.K) + ROUND - 1) / ROUND;
+    const int64_t groups = A.Kp / QGROUP;   // (every column of invF below Kp is written)
+    auto issue = [&](int ch, f16x8 *fg) {    // codebook image of chunk ch, 1 KB pieces over the waves
+        for (int p = wave; p < NF / LEGS_WAVE; p += QTHREADS / LEGS_WAVE)
+            global_to_lds(A.img + (int64_t)ch * NF + p * LEGS_WAVE + lane, fg + p * LEGS_WAVE);
+    };
+    // nothing requested later moves above the codebook pieces (the waits count)
+    auto issue_end = [] {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // this lane's feature of round g; rows past K read row K - 1
+    auto row_of = [&](int64_t g) {
+        const int64_t i = g * QGROUP + wave * 32 + (lane & 31);
+        return A.F + (i < A.K ? i : A.K - 1) * (int64_t)A.d + 8 * h;
+    };
+    f16x8 fb[8];                             // feature fragments of the next chunk, a k-step each
+    const _Float16 *row = nullptr;
+    if ((int64_t)blockIdx.x < groups) {
+        row = row_of(blockIdx.x);
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) fb[ks] = *reinterpret_cast<const f16x8 *>(row + 16 * ks);
+        issue(0, frag0);
+    }
+    vm_wait<0>();
+    __syncthreads();
     for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
-        int64_t ii[QNT];
-        bool valid[QNT];
-        const _Float16 *frow[QNT];
+        const int64_t gn = g + gridDim.x < groups ? g + gridDim.x : g;   // the round after (or this one again)
+        const _Float16 *nrow = row_of(gn);
+        f32x16 acc[KB], D[KB];
+        float ss = 0.0f, inv0 = 0.0f;
 #pragma unroll
-        for (int t = 0; t < QNT; ++t) {
-            ii[t] = g * ROUND + (wave * QNT + t) * 32 + (lane & 31);
-            valid[t] = ii[t] < A.K;
-            frow[t] = A.F + (valid[t] ? ii[t] : 0) * (int64_t)A.d + 8 * h;
+        for (int mb = 0; mb < KB; ++mb) {
+            acc[mb] = (f32x16){};
+            D[mb] = (f32x16){};
         }
-        f32x16 ac[QNT][KB], ad[QNT][KB];
-#pragma unroll
-        for (int t = 0; t < QNT; ++t)
-#pragma unroll
-            for (int mb = 0; mb < KB; ++mb) { ac[t][mb] = (f32x16){}; ad[t][mb] = (f32x16){}; }
-        float ssc[QNT] = {}, ssd[QNT] = {};
-        // the fragments of chunk ch into LDS buffer ch & 1: the codebook image
-        // in 1 KB pieces (wave w copies pieces w, w + 4, ...) and this wave's
-        // feature fragments (lane l of k-step ks: feature l % 32, dimensions
-        // 128 ch + 16 ks + 8 (l / 32) .. + 7; padding features read row 0 and
-        // are zeroed when read back)
-        auto issue = [&](int ch, f16x8 *fg, f16x8 *fe) {
-            for (int p = wave; p < NF / LEGS_WAVE; p += QTHREADS / LEGS_WAVE)
-                global_to_lds(A.img + (int64_t)ch * NF + p * LEGS_WAVE + lane, fg + p * LEGS_WAVE);
-#pragma unroll
-            for (int t = 0; t < QNT; ++t)
-#pragma unroll
-                for (int ks = 0; ks < 8; ++ks)
-                    global_to_lds(frow[t] + ch * QCH + 16 * ks, fe + ((wave * QNT + t) * 8 + ks) * LEGS_WAVE);
+        auto norm = [&]() {                  // 1 / |F_i| of the part just summed
+            const float s2 = ss + __shfl_xor(ss, 32, LEGS_WAVE);
+            return s2 > 0.0f ? 1.0f / sqrtf(s2) : 0.0f;
         };
-        auto chunk = [&](const f16x8 *fr, const f16x8 *fe, f32x16 (&acc)[QNT][KB], float (&ss)[QNT]) {
-            const f16x8(*fb)[8 * LEGS_WAVE] = reinterpret_cast<const f16x8(*)[8 * LEGS_WAVE]>(fe + wave * QNT * 8 * LEGS_WAVE);
-            // software pipeline: the fragments of k-step ks + 1 are read while
-            // the MFMAs of ks run; a scheduling barrier per k-step keeps the
-            // compiler from hoisting every read of the chunk (registers)
-            f16x8 a[KB], b[QNT];
+        // the CLIP dot products become cosines at the end of the part
+        auto part_end = [&]() {
+            inv0 = norm();
+            ss = 0.0f;
+#pragma unroll
+            for (int mb = 0; mb < KB; ++mb) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    D[mb][r] = acc[mb][r] * inv0 * s_inv[0][32 * mb + legs_drow(r, h)];
+                acc[mb] = (f32x16){};
+            }
+        };
+        auto chunk = [&](const f16x8 *fr, int ch) {
+            // the fragments of k-step ks + 1 are read while the MFMAs of ks run, and
+            // the next chunk's feature fragments are requested in their place
+            f16x8 a[KB];
 #pragma unroll
             for (int mb = 0; mb < KB; ++mb) a[mb] = fr[mb * 8 * 64 + lane];
-#pragma unroll
-            for (int t = 0; t < QNT; ++t) b[t] = valid[t] ? fb[t][lane] : (f16x8){};
+            const _Float16 *src = ch + 1 == nch ? nrow : row + (ch + 1) * QCH;
 #pragma unroll
             for (int ks = 0; ks < 8; ++ks) {
-                f16x8 an[KB], bn[QNT];
+                f16x8 an[KB];
                 if (ks + 1 < 8) {
 #pragma unroll
                     for (int mb = 0; mb < KB; ++mb) an[mb] = fr[(mb * 8 + ks + 1) * 64 + lane];
-#pragma unroll
-                    for (int t = 0; t < QNT; ++t) bn[t] = valid[t] ? fb[t][(ks + 1) * 64 + lane] : (f16x8){};
                 }
+                const f16x8 b = fb[ks];
 #pragma unroll
-                for (int mb = 0; mb < KB; ++mb)
+                for (int mb = 0; mb < KB; ++mb) acc[mb] = mfma16(a[mb], b, acc[mb]);
 #pragma unroll
-                    for (int t = 0; t < QNT; ++t) acc[t][mb] = mfma16(a[mb], b[t], acc[t][mb]);
+                for (int e = 0; e < 8; ++e) ss = fmaf((float)b[e], (float)b[e], ss);
+                // a row's 128-byte line at a time: spread over the steps, the line
+                // left the L1 between them (1.28 ms a call instead of 1.21)
+                if ((ks & 3) == 3) {
 #pragma unroll
-                for (int t = 0; t < QNT; ++t)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) ss[t] = fmaf((float)b[t][e], (float)b[t][e], ss[t]);
+                    for (int k = ks - 3; k <= ks; ++k) fb[k] = *reinterpret_cast<const f16x8 *>(src + 16 * k);
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 if (ks + 1 < 8) {
 #pragma unroll
                     for (int mb = 0; mb < KB; ++mb) a[mb] = an[mb];
-#pragma unroll
-                    for (int t = 0; t < QNT; ++t) b[t] = bn[t];
                 }
             }
         };
-        // chunk ch + 1 loads while chunk ch computes: the wait for this wave's
-        // loads and the barrier before each chunk make its fragments visible
-        // and free the other buffer (read by chunk ch - 1) for the next loads.
-        // The loop takes two chunks per iteration, even ones in buffer 0 and
-        // odd ones in buffer 1, so that every read and every load has its
-        // buffer fixed at compile time. In the gradient pass the last chunk
-        // reloads itself into the other buffer: there a conditional load made
-        // the compiler wait before the reads (and spill); the assign pass
-        // loads only what it reads. One set of accumulators serves the part
-        // being summed: at chunk nchC the CLIP sums move to ac.
-        f32x16 acc[QNT][KB];
-        float ss[QNT];
-#pragma unroll
-        for (int t = 0; t < QNT; ++t) {
-            ss[t] = 0.0f;
-#pragma unroll
-            for (int mb = 0; mb < KB; ++mb) acc[t][mb] = (f32x16){};
-        }
-        auto part_switch = [&](int ch) {
-            if (ch != nchC) return;
-#pragma unroll
-            for (int t = 0; t < QNT; ++t) {
-                ssc[t] = ss[t];
-                ss[t] = 0.0f;
-#pragma unroll
-                for (int mb = 0; mb < KB; ++mb) {
-                    ac[t][mb] = acc[t][mb];
-                    acc[t][mb] = (f32x16){};
-                }
-            }
-        };
-        vm_wait<0>();                                 // the previous round's stores
-        __syncthreads();                              // the previous round's readers are done
-        issue(0, frag0, feat0);
+        // Chunk ch + 1's codebook loads while chunk ch computes. The waits count
+        // what was requested after the codebook pieces that they wait for: the 8
+        // feature fragments of the chunk before, or, at a round's start, the
+        // cosines' stores (without them, whatever there is; the first round's
+        // loads were waited for above).
+        constexpr int FL = 8, ST = KEEP ? 8 * KB : 0;
 #pragma unroll 1
         for (int ch = 0; ch < nch; ch += 2) {
-            part_switch(ch);
-            vm_wait<0>();
+            if (ch == nchC) part_end();
+            if (ch) vm_wait<FL>();
+            else vm_wait<ST>();
             ring_barrier();
-            if (GRAD || ch + 1 < nch) issue(ch + 1 < nch ? ch + 1 : ch, frag1, feat1);
-            chunk(frag0, feat0, acc, ss);
+            if (ch + 1 < nch) issue(ch + 1, frag1);
+            issue_end();
+            chunk(frag0, ch);
             if (ch + 1 < nch) {
-                part_switch(ch + 1);
-                vm_wait<0>();
+                if (ch + 1 == nchC) part_end();
+                vm_wait<FL>();
                 ring_barrier();
-                if (GRAD || ch + 2 < nch) issue(ch + 2 < nch ? ch + 2 : ch + 1, frag0, feat0);
-                chunk(frag1, feat1, acc, ss);
+                if (ch + 2 < nch) issue(ch + 2, frag0);
+                issue_end();
+                chunk(frag1, ch + 1);
             }
         }
-        if (nchC == nch) part_switch(nch);             // no DINO chunks: ad stays zero
-#pragma unroll
-        for (int t = 0; t < QNT; ++t) {
-            ssd[t] = ss[t];
-#pragma unroll
-            for (int mb = 0; mb < KB; ++mb) ad[t][mb] = acc[t][mb];
-        }
-#pragma unroll
-        for (int t = 0; t < QNT; ++t) {
-            const int64_t i = ii[t];
-            const bool vt = valid[t];
-            const float sc2 = ssc[t] + __shfl_xor(ssc[t], 32, LEGS_WAVE);
-            const float sd2 = ssd[t] + __shfl_xor(ssd[t], 32, LEGS_WAVE);
-            const float ifc = sc2 > 0.0f ? 1.0f / sqrtf(sc2) : 0.0f;
-            const float ifd = sd2 > 0.0f ? 1.0f / sqrtf(sd2) : 0.0f;
-            if (GRAD && h == 0) {
-                A.invF[i] = vt ? ifc : 0.0f;
-                A.invF[A.Kp + i] = vt ? ifd : 0.0f;
+        if (nchC == nch) part_end();         // no DINO chunks: their dot products are zero
+        ring_barrier();                      // every wave is done with the codebook buffers
+        issue(0, frag0);                     // the next round's first chunk, during the softmax
+        issue_end();
+        float sv[KB * 16];
+        {
+            const int64_t i = g * QGROUP + wave * 32 + (lane & 31);
+            const bool vt = i < A.K;
+            const float inv1 = nchC == nch ? 0.0f : norm();
+            if (KEEP && h == 0) {
+                A.invF[i] = vt ? inv0 : 0.0f;
+                A.invF[A.Kp + i] = vt ? inv1 : 0.0f;
             }
-            // cosines of both parts in place, distance, argmax (first maximum)
+            // distance, argmax (first maximum)
             float best = -INFINITY;
             int bidx = 0x7fffffff;
+            float4 *pc = KEEP ? A.cos + (i >> 5) * (N / 4 * LEGS_WAVE) + lane : nullptr;
 #pragma unroll
             for (int mb = 0; mb < KB; ++mb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int j = 32 * mb + legs_drow(r, h);
-                    ac[t][mb][r] = ac[t][mb][r] * ifc * s_inv[0][j];
-                    ad[t][mb][r] = ad[t][mb][r] * ifd * s_inv[1][j];
-                    const float Dv = ac[t][mb][r] + A.lam_d * ad[t][mb][r];
-                    if (Dv > best) { best = Dv; bidx = j; }
+                for (int q = 0; q < 4; ++q) {
+                    float e[4];
+                    if (KEEP)
+                        pc[(4 * mb + q) * LEGS_WAVE] = make_float4(D[mb][4 * q], D[mb][4 * q + 1], D[mb][4 * q + 2], D[mb][4 * q + 3]);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int r = 4 * q + u;
+                        e[u] = acc[mb][r] * inv1 * s_inv[1][32 * mb + legs_drow(r, h)];
+                        const float Dv = D[mb][r] + A.lam_d * e[u];
+                        D[mb][r] = Dv;
+                        // (the half's offset 4 h, the same for every code, is added below)
+                        if (Dv > best) { best = Dv; bidx = 32 * mb + legs_drow(r, 0); }
+                    }
+                    if (KEEP) pc[(N / 8 + 4 * mb + q) * LEGS_WAVE] = make_float4(e[0], e[1], e[2], e[3]);
                 }
+            if (best > -INFINITY) bidx += 4 * h;
             {
                 const float ob = __shfl_xor(best, 32, LEGS_WAVE);
                 const int oi = __shfl_xor(bidx, 32, LEGS_WAVE);
@@ -366,177 +383,215 @@ k_quant_pass(QuantArgs A)
             }
             float sum = 0.0f;
 #pragma unroll
-            for (int mb = 0; mb < KB; ++mb)
+            for (int mb = 0; mb < KB; ++mb) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) sum += __expf(ac[t][mb][r] + A.lam_d * ad[t][mb][r] - best);
+                for (int r = 0; r < 16; ++r) D[mb][r] = __expf(D[mb][r] - best);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum += D[mb][r];
+            }
             sum += __shfl_xor(sum, 32, LEGS_WAVE);
             const float isum = 1.0f / sum;
-            if constexpr (!GRAD) {
-                float sv[KB * 16];
 #pragma unroll
-                for (int mb = 0; mb < KB; ++mb)
+            for (int mb = 0; mb < KB; ++mb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float c = ac[t][mb][r], e = ad[t][mb][r];
-                        sv[mb * 16 + r] = vt ? __expf(c + A.lam_d * e - best) * isum : 0.0f;
-                    }
-                // the cosine loss of the assigned code: (1 - cos^C) + lambda (1 - cos^D)
-                // = (1 + lambda) - D at the maximum, which is best
-                if (vt && h == 0) lcos += (1.0f + A.lam_d) - best;
-                half_wave_sums<KB * 16>(sv, s_ab, [h](int v) { return 32 * (v >> 4) + legs_drow(v & 15, h); });
-                if (vt && h == 0) {
-                    A.index[i] = bidx;
-                    atomicAdd(&s_cnt[bidx], 1u);
-                }
-            } else {
-                const int m = vt ? A.index[i] : -1;
-                float rs = 0.0f;
-#pragma unroll
-                for (int mb = 0; mb < KB; ++mb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        rs += s_r[32 * mb + legs_drow(r, h)] * __expf(ac[t][mb][r] + A.lam_d * ad[t][mb][r] - best);
-                rs += __shfl_xor(rs, 32, LEGS_WAVE);
-                rs *= isum;
-                const float scale = (float)A.K * WSCALE;
-                // W^C, W^D in the weight gradient's operand order: the 8 codes
-                // r = 8 k .. 8 k + 7 of block mb of this lane's feature,
-                // transposed across its group of 8 lanes (8 consecutive
-                // features), are one 16-byte fragment per lane
-                const int64_t i0 = i - i8;
-#pragma unroll
-                for (int mb = 0; mb < KB; ++mb)
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        uint32_t wc[4], wd[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            float gv[2];
-#pragma unroll
-                            for (int u = 0; u < 2; ++u) {
-                                const int r = 8 * k + 2 * q + u;
-                                const int j = 32 * mb + legs_drow(r, h);
-                                const float c = ac[t][mb][r], e = ad[t][mb][r];
-                                const float s = __expf(c + A.lam_d * e - best) * isum;
-                                float gj = A.lam_lb * invK * s * (s_r[j] - rs);
-                                if (j == m) gj -= A.lam_cos * invK;
-                                if (!vt) gj = 0.0f;
-                                ac[t][mb][r] = gj * c;         // column-sum terms, in place
-                                ad[t][mb][r] = A.lam_d * gj * e;
-                                gv[u] = gj;
-                            }
-                            wc[q] = pack_half2(scale * gv[0], scale * gv[1]);
-                            wd[q] = pack_half2(scale * A.lam_d * gv[0], scale * A.lam_d * gv[1]);
-                        }
-                        legs_lt::oct_transpose(wc, b1, psel);
-                        legs_lt::oct_transpose(wd, b1, psel);
-                        // lane i8 now holds code 32 mb + drow(8 k + i8, h) of features i0 .. i0 + 7
-                        const int row = 32 * mb + 16 * k + 8 * (i8 >> 2) + 4 * h + (i8 & 3);
-                        const int64_t off = legs_lt::frag_at(i0, N, row);
-                        *reinterpret_cast<uint4 *>(A.Wc + off) = make_uint4(wc[0], wc[1], wc[2], wc[3]);
-                        *reinterpret_cast<uint4 *>(A.Wd + off) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
-                    }
-                auto code = [h](int v) { return 32 * (v >> 4) + legs_drow(v & 15, h); };
-                {
-                    float v[KB * 16];
-#pragma unroll
-                    for (int k = 0; k < KB * 16; ++k) v[k] = ac[t][k >> 4][k & 15];
-                    half_wave_sums<KB * 16>(v, s_ab, code);
-                }
-                {
-                    float v[KB * 16];
-#pragma unroll
-                    for (int k = 0; k < KB * 16; ++k) v[k] = ad[t][k >> 4][k & 15];
-                    half_wave_sums<KB * 16>(v, s_ab + N, code);
-                }
+                for (int r = 0; r < 16; ++r) sv[16 * mb + r] = vt ? D[mb][r] * isum : 0.0f;
+            // the cosine loss of the assigned code: (1 - cos^C) + lambda (1 - cos^D)
+            // = (1 + lambda) - D at the maximum, which is best
+            if (vt && h == 0) {
+                lcos += (1.0f + A.lam_d) - best;
+                A.index[i] = bidx;
+                atomicAdd(&s_cnt[bidx], 1u);
             }
         }
+        half_wave_sums(sv, psum, lane);
+        row = nrow;
     }
-    // cosine-loss partial: one wave sum, one atomic
+    // the workgroup's sums (the softmax's in the codebook's place)
+    vm_wait<0>();                            // the loads of the round that does not come
+    float *s_p = reinterpret_cast<float *>(frag1);
+    block_sums<KB * 16, QTHREADS / LEGS_WAVE>(psum, s_p, lane, wave);
+    // (in float64: thousands of waves add to the one loss)
+    double lsum = lcos;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lcos += __shfl_xor(lcos, o, LEGS_WAVE);
-    __syncthreads();
-    if (!GRAD && lane == 0 && lcos != 0.0f) atomicAdd(A.lsum, lcos);
+    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, LEGS_WAVE);
+    if (lane == 0 && lsum != 0.0) atomicAdd(A.lsum, lsum);
     for (int j = tid; j < N; j += QTHREADS) {
-        if (!GRAD) {
-            if (s_ab[j] != 0.0f) atomicAdd(A.psum + j, s_ab[j]);
-            if (s_cnt[j]) atomicAdd(A.counts + j, s_cnt[j]);
-        } else {
-            if (s_ab[j] != 0.0f) atomicAdd(A.col + j, s_ab[j]);
-            if (s_ab[N + j] != 0.0f) atomicAdd(A.col + N + j, s_ab[N + j]);
-        }
+        if (s_p[j] != 0.0f) atomicAdd(A.psum + j, s_p[j]);
+        if (s_cnt[j]) atomicAdd(A.counts + j, s_cnt[j]);
     }
 }
 
-// sum_i W_ij F_ic over the features [x0, x1) of this workgroup, for the 128
-// dimensions of chunk blockIdx.y; wave w computes code block w % KB and
-// 4 / (4 / KB) dimension blocks.
+// dL_q/dD of 32 features per wave from their cosines, as half weights in their
+// place (a wave reads its 256 N bytes before it writes the first quarter of
+// them), and the sums over the features of its products with the cosines.
+// Bound by memory: 10 N bytes a feature.
+template <int KB>
+__global__ void __launch_bounds__(256, 2)
+k_quant_weights(QuantArgs A)
+{
+    constexpr int N = 32 * KB;
+    __shared__ float s_r[N], s_col[2][N];
+    const int lane = __lane_id(), h = lane >> 5;
+    const int wave = threadIdx.x / LEGS_WAVE;
+    const int i8 = lane & 7;
+    const bool b1 = (lane & 2) != 0;
+    const uint32_t psel = (lane & 1) ? 0x03020706u : 0x05040100u;
+    const float invK = 1.0f / (float)A.K;
+    for (int j = threadIdx.x; j < N; j += 256) s_r[j] = (float)A.counts[j] * invK;
+    __syncthreads();
+    const float scale = (float)A.K * WSCALE;
+    float col[2][legs_tr::final_k(KB * 16, 5)] = {};
+    for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < A.Kp / 32; tile += (int64_t)gridDim.x * 4) {
+        const int64_t i = 32 * tile + (lane & 31);
+        const bool vt = i < A.K;
+        const float4 *pc = A.cos + tile * (N / 4 * LEGS_WAVE) + lane;
+        float c[KB * 16], e[KB * 16];
+#pragma unroll
+        for (int k = 0; k < KB * 4; ++k) {
+            const float4 x = pc[k * LEGS_WAVE], y = pc[(N / 8 + k) * LEGS_WAVE];
+            c[4 * k] = x.x, c[4 * k + 1] = x.y, c[4 * k + 2] = x.z, c[4 * k + 3] = x.w;
+            e[4 * k] = y.x, e[4 * k + 1] = y.y, e[4 * k + 2] = y.z, e[4 * k + 3] = y.w;
+        }
+        const int m = vt ? A.index[i] : -1;
+        float best = -INFINITY, sum = 0.0f, rs = 0.0f;
+#pragma unroll
+        for (int k = 0; k < KB * 16; ++k) best = fmaxf(best, c[k] + A.lam_d * e[k]);
+        best = fmaxf(best, __shfl_xor(best, 32, LEGS_WAVE));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < KB * 16; ++k) {
+            const float x = __expf(c[k] + A.lam_d * e[k] - best);
+            sum += x;
+            rs += s_r[8 * (k >> 2) + 4 * h + (k & 3)] * x;
+            if (k % 16 == 15) __builtin_amdgcn_sched_barrier(0);   // (all of the shares at once would spill)
+        }
+        sum += __shfl_xor(sum, 32, LEGS_WAVE);
+        rs += __shfl_xor(rs, 32, LEGS_WAVE);
+        const float isum = 1.0f / sum;
+        rs *= isum;
+        __builtin_amdgcn_sched_barrier(0);
+        // the 8 codes r = 8 k .. 8 k + 7 of block mb of this lane's feature,
+        // transposed across its group of 8 lanes (8 consecutive features), are one
+        // 16-byte fragment per lane
+        _Float16 *W = quant_weights(A.cos, N, 32 * tile);
+#pragma unroll
+        for (int mb = 0; mb < KB; ++mb)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                uint32_t w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float gv[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int r = 8 * k + 2 * q + u, x = 16 * mb + r;
+                        const float sm = __expf(c[x] + A.lam_d * e[x] - best) * isum;
+                        float gj = A.lam_lb * invK * sm * (s_r[32 * mb + legs_drow(r, h)] - rs);
+                        if (32 * mb + legs_drow(r, 0) == m - 4 * h) gj -= A.lam_cos * invK;
+                        if (!vt) gj = 0.0f;
+                        c[x] *= gj;                        // column-sum terms, in place
+                        e[x] *= A.lam_d * gj;
+                        gv[u] = gj;
+                    }
+                    w[q] = pack_half2(scale * gv[0], scale * gv[1]);
+                }
+                legs_lt::oct_transpose(w, b1, psel);
+                // lane i8 now holds code 32 mb + drow(8 k + i8, h) of its group's 8 features
+                const int row = 32 * mb + 16 * k + 8 * (i8 >> 2) + 4 * h + (i8 & 3);
+                *reinterpret_cast<uint4 *>(W + legs_lt::frag_at((lane & 31) - i8, N, row)) =
+                    make_uint4(w[0], w[1], w[2], w[3]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        half_wave_sums(c, col[0], lane);
+        __builtin_amdgcn_sched_barrier(0);
+        half_wave_sums(e, col[1], lane);
+    }
+    block_sums<KB * 16, 4>(col[0], s_col[0], lane, wave);
+    block_sums<KB * 16, 4>(col[1], s_col[1], lane, wave);
+    for (int j = threadIdx.x; j < 2 * N; j += 256)
+        if ((&s_col[0][0])[j] != 0.0f) atomicAdd(A.col + j, (&s_col[0][0])[j]);
+}
+
+// sum_i W_ij F_ic over the features [x0, x1) of this workgroup, for the NC
+// 128-dimension chunks from NC blockIdx.y; wave w computes code block w % KB
+// and, of each chunk, 4 / (4 / KB) dimension blocks.
 constexpr int WG_FEAT = 64;          // features per LDS step
 
-template <int KB>
-__global__ void __launch_bounds__(256)
+template <int KB, int NC>
+__global__ void __launch_bounds__(256, 2)
 k_quant_wgrad(const _Float16 *__restrict__ F, int64_t K, int64_t Kp, int d, int dC, int64_t per_block,
-              const _Float16 *__restrict__ Wc, const _Float16 *__restrict__ Wd, const float *__restrict__ invF,
-              const float *__restrict__ invS, float *__restrict__ grad)
+              const void *__restrict__ weights, const float *__restrict__ invF, const float *__restrict__ invS,
+              float lam_d, float *__restrict__ grad)
 {
     constexpr int N = 32 * KB, WPB = 4 / KB, DB = 4 / WPB;   // waves per code block, dim blocks per wave
-    __shared__ f16x8 tile[WG_FEAT / 16][QCH / 32][64];   // B fragments of a step: [k-step][dim block][lane]
+    __shared__ f16x8 tile[NC][WG_FEAT / 16][QCH / 32][64];   // B fragments of a step: [chunk][k-step][dim block][lane]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
     const int i8 = lane & 7;
     const bool b1 = (lane & 2) != 0;
     const uint32_t psel = (lane & 1) ? 0x03020706u : 0x05040100u;
     const int mb = wave % KB, db0 = (wave / KB) * DB;
-    const int c0 = blockIdx.y * QCH;
-    const bool clip = c0 < dC;
-    const _Float16 *W = clip ? Wc : Wd;
-    const float *iF = invF + (clip ? 0 : Kp);
+    const int c0 = blockIdx.y * QCH * NC;
+    const int nc = min(NC, d / QCH - (int)blockIdx.y * NC);
     const int64_t x0 = (int64_t)blockIdx.x * per_block;
     const int64_t x1 = min(x0 + per_block, Kp);
-    f32x16 acc[DB];
+    f32x16 acc[NC][DB];
 #pragma unroll
-    for (int q = 0; q < DB; ++q) acc[q] = (f32x16){};
+    for (int n = 0; n < NC; ++n)
+#pragma unroll
+        for (int q = 0; q < DB; ++q) acc[n][q] = (f32x16){};
     // the next step's feature rows, their norms and this wave's weight
     // fragments are loaded into registers while the current step computes
-    f16x8 fv[4], wa[WG_FEAT / 16];
-    float fsc[4];
+    f16x8 fv[NC][4], wa[WG_FEAT / 16];
+    float fsc[NC][4];
     auto load_step = [&](int64_t s0) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int u = 4 * wave + it;
-            const int64_t ii = s0 + 8 * (u >> 1) + i8;
-            const int c8 = 64 * (u & 1) + 8 * (lane >> 3);
-            fv[it] = ii < K ? *reinterpret_cast<const f16x8 *>(F + ii * d + c0 + c8) : (f16x8){};
-            fsc[it] = ii < K ? iF[ii] : 0.0f;               // unit feature rows of this part
+        for (int n = 0; n < NC; ++n) {
+            if (n >= nc) continue;
+            const float *iF = invF + (c0 + n * QCH < dC ? 0 : Kp);
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int u = 4 * wave + it;
+                const int64_t ii = s0 + 8 * (u >> 1) + i8;
+                const int c8 = 64 * (u & 1) + 8 * (lane >> 3);
+                fv[n][it] = ii < K ? *reinterpret_cast<const f16x8 *>(F + ii * d + c0 + n * QCH + c8) : (f16x8){};
+                fsc[n][it] = ii < K ? iF[ii] : 0.0f;         // unit feature rows of this part
+            }
         }
 #pragma unroll
         for (int ks = 0; ks < WG_FEAT / 16; ++ks) {
             // operand order: the wave's fragments of (code block mb, features
             // s0 + 16 ks ..) are 1 KB contiguous
-            const int64_t ia = s0 + 16 * ks + 8 * h;
-            wa[ks] = ia < x1 ? *reinterpret_cast<const f16x8 *>(W + legs_lt::frag_at(ia, N, 32 * mb + (lane & 31)))
+            const int64_t ia = s0 + 16 * ks;
+            wa[ks] = ia < x1 ? *reinterpret_cast<const f16x8 *>(
+                                   quant_weights(const_cast<void *>(weights), N, ia) +
+                                   legs_lt::frag_at((ia & 31) + 8 * h, N, 32 * mb + (lane & 31)))
                              : (f16x8){};
         }
     };
     if (x0 < x1) load_step(x0);
     for (int64_t s0 = x0; s0 < x1; s0 += WG_FEAT) {
         ring_barrier();                                    // the previous step's readers are done
-        // stage features [s0, s0 + 64) x dimensions [c0, c0 + 128) as B
-        // fragments: 16 units of 8 features x 64 dimensions, four per wave;
-        // lane l holds dimensions 8 (l / 8) .. + 7 (of the unit's half) of
+        // stage features [s0, s0 + 64) x dimensions [c0, c0 + 128 nc) as B
+        // fragments: per chunk 16 units of 8 features x 64 dimensions, four per
+        // wave; lane l holds dimensions 8 (l / 8) .. + 7 (of the unit's half) of
         // feature l % 8 (of the unit's block of 8), scales the row to unit
         // length, and the transpose across its group of 8 lanes leaves it
         // dimension 8 (l / 8) + l % 8 of the 8 features: one fragment
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int u = 4 * wave + it, fb = u >> 1;
-            uint32_t w[4];
+        for (int n = 0; n < NC; ++n) {
+            if (n >= nc) continue;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                w[q] = pack_half2((float)fv[it][2 * q] * fsc[it], (float)fv[it][2 * q + 1] * fsc[it]);
-            legs_lt::oct_transpose(w, b1, psel);
-            const int c = 64 * (u & 1) + 8 * (lane >> 3) + i8;   // the dimension this lane now holds
-            tile[fb >> 1][c >> 5][(c & 31) + 32 * (fb & 1)] =
-                __builtin_bit_cast(f16x8, make_uint4(w[0], w[1], w[2], w[3]));
+            for (int it = 0; it < 4; ++it) {
+                const int u = 4 * wave + it, fb = u >> 1;
+                uint32_t w[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    w[q] = pack_half2((float)fv[n][it][2 * q] * fsc[n][it], (float)fv[n][it][2 * q + 1] * fsc[n][it]);
+                legs_lt::oct_transpose(w, b1, psel);
+                const int c = 64 * (u & 1) + 8 * (lane >> 3) + i8;   // the dimension this lane now holds
+                tile[n][fb >> 1][c >> 5][(c & 31) + 32 * (fb & 1)] =
+                    __builtin_bit_cast(f16x8, make_uint4(w[0], w[1], w[2], w[3]));
+            }
         }
         f16x8 a[WG_FEAT / 16];
 #pragma unroll
@@ -545,24 +600,33 @@ k_quant_wgrad(const _Float16 *__restrict__ F, int64_t K, int64_t Kp, int d, int 
         ring_barrier();                                    // the staged fragments (LDS only: the
                                                            // loads just issued stay in flight)
 #pragma unroll
-        for (int ks = 0; ks < WG_FEAT / 16; ++ks)
+        for (int n = 0; n < NC; ++n) {
+            if (n >= nc) continue;
 #pragma unroll
-            for (int q = 0; q < DB; ++q) {
-                const f16x8 b = tile[ks][db0 + q][lane];     // dimension 32 (db0 + q) + lane % 32
-                acc[q] = mfma16(a[ks], b, acc[q]);
+            for (int ks = 0; ks < WG_FEAT / 16; ++ks)
+#pragma unroll
+                for (int q = 0; q < DB; ++q) {
+                    const f16x8 b = tile[n][ks][db0 + q][lane];     // dimension 32 (db0 + q) + lane % 32
+                    acc[n][q] = mfma16(a[ks], b, acc[n][q]);
+                }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        if (n >= nc) continue;
+        const bool clip = c0 + n * QCH < dC;
+        const float sc = (clip ? 1.0f : lam_d) / ((float)K * WSCALE);
+        const float *is = invS + (clip ? 0 : N);
+#pragma unroll
+        for (int q = 0; q < DB; ++q)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int j = 32 * mb + legs_drow(r, h);
+                const int c = c0 + n * QCH + 32 * (db0 + q) + (lane & 31);
+                const float v = acc[n][q][r] * sc * is[j];
+                if (v != 0.0f) atomicAdd(grad + (int64_t)j * d + c, v);
             }
     }
-    const float invK = 1.0f / ((float)K * WSCALE);
-    const float *is = invS + (clip ? 0 : N);
-#pragma unroll
-    for (int q = 0; q < DB; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int j = 32 * mb + legs_drow(r, h);
-            const int c = c0 + 32 * (db0 + q) + (lane & 31);
-            const float v = acc[q][r] * invK * is[j];
-            if (v != 0.0f) atomicAdd(grad + (int64_t)j * d + c, v);
-        }
 }
 
 // grad[j][c] -= col^part_j S16_jc / |S16_j^part|^2; losses; r and p.
@@ -570,7 +634,7 @@ template <int KB>
 __global__ void __launch_bounds__(256)
 k_quant_finish(const float *__restrict__ S, int d, int dC, int64_t K, const float *__restrict__ invS,
                const float *__restrict__ col, float *__restrict__ grad, const uint32_t *__restrict__ counts,
-               const float *__restrict__ psum, const float *__restrict__ lsum, float lam_cos, float lam_lb,
+               const float *__restrict__ psum, const double *__restrict__ lsum, float lam_cos, float lam_lb,
                float *__restrict__ prob_mean, float *__restrict__ losses)
 {
     constexpr int N = 32 * KB;
@@ -593,7 +657,7 @@ k_quant_finish(const float *__restrict__ S, int d, int dC, int64_t K, const floa
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) lb += __shfl_xor(lb, o, LEGS_WAVE);
         if (threadIdx.x == 0 && losses) {
-            const float lc = lsum[0] * invK;
+            const float lc = (float)lsum[0] * invK;
             losses[0] = lc;
             losses[1] = lb;
             losses[2] = lam_cos * lc + lam_lb * lb;
@@ -601,17 +665,8 @@ k_quant_finish(const float *__restrict__ S, int d, int dC, int64_t K, const floa
     }
 }
 
-__global__ void __launch_bounds__(256)
-k_quant_zero(uint32_t *__restrict__ a, int64_t na, uint32_t *__restrict__ b, int64_t nb)
-{
-    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < na + nb; q += (int64_t)gridDim.x * 256) {
-        if (q < na) a[q] = 0u;
-        else b[q - na] = 0u;
-    }
-}
-
 struct QuantLayout {
-    int64_t img, invS, psum, col, lsum, wc, wd, invF, total, Kp;
+    int64_t img, invS, psum, col, lsum, cos, invF, total, Kp;
 };
 
 QuantLayout quant_layout(int64_t K, int32_t N, int32_t d)
@@ -624,9 +679,8 @@ QuantLayout quant_layout(int64_t K, int32_t N, int32_t d)
     L.invS = o; o = up(o + 2 * (int64_t)N * 4);
     L.psum = o; o = up(o + (int64_t)N * 4);
     L.col = o;  o = up(o + 2 * (int64_t)N * 4);
-    L.lsum = o; o = up(o + 4);
-    L.wc = o;   o = up(o + (int64_t)N * L.Kp * 2);
-    L.wd = o;   o = up(o + (int64_t)N * L.Kp * 2);
+    L.lsum = o; o = up(o + 8);
+    L.cos = o;  o = up(o + 2 * (int64_t)N * L.Kp * 4);
     L.invF = o; o = up(o + 2 * L.Kp * 4);
     L.total = o;
     return L;
@@ -657,32 +711,36 @@ int32_t legs_launch_quantize(legs_ctx *ctx, const uint16_t *feat, int64_t K, int
     A.index = index;
     A.counts = counts;
     A.psum = reinterpret_cast<float *>(ws + Lw.psum);
-    A.lsum = reinterpret_cast<float *>(ws + Lw.lsum);
-    A.Wc = reinterpret_cast<_Float16 *>(ws + Lw.wc);
-    A.Wd = reinterpret_cast<_Float16 *>(ws + Lw.wd);
+    A.lsum = reinterpret_cast<double *>(ws + Lw.lsum);
+    A.cos = reinterpret_cast<float4 *>(ws + Lw.cos);
     A.col = reinterpret_cast<float *>(ws + Lw.col);
     A.invF = reinterpret_cast<float *>(ws + Lw.invF);
     // psum, col and lsum are contiguous (up to padding) in the workspace
-    hipLaunchKernelGGL(k_quant_zero, dim3(1), dim3(256), 0, s, counts, (int64_t)N,
-                       reinterpret_cast<uint32_t *>(ws + Lw.psum), (Lw.wc - Lw.psum) / 4);
+    const int nsums = (int)((Lw.cos - Lw.psum) / 4);
     const int KB = N / 32;
     const int64_t rounds = (K + QGROUP - 1) / QGROUP;
     const int gq = (int)(rounds < ctx->num_cus ? (rounds < 1 ? 1 : rounds) : ctx->num_cus);
-    const int64_t per_block = 4096;
-    const dim3 gw((unsigned)((Lw.Kp + per_block - 1) / per_block), (unsigned)(d / QCH));
+    constexpr int NC = 2;
+    // feature ranges of the weight gradient: two workgroups per CU over all of
+    // the dimension groups, in steps of WG_FEAT
+    const int gy = (d / QCH + NC - 1) / NC;
+    int64_t per_block = (Lw.Kp * gy / (2 * ctx->num_cus) + WG_FEAT - 1) / WG_FEAT * WG_FEAT;
+    per_block = per_block < 512 ? 512 : per_block;
+    const dim3 gw((unsigned)((Lw.Kp + per_block - 1) / per_block), (unsigned)gy);
     const int gz = (int)((((int64_t)N * d + 255) / 256) < 1024 ? ((int64_t)N * d + 255) / 256 : 1024);
+    const int64_t wt = (Lw.Kp / 32 + 3) / 4, wtc = (int64_t)ctx->num_cus * 8;
+    const int gt = (int)(wt < wtc ? wt : wtc);
 #define LEGS_QUANT(KBV)                                                                                              \
     hipLaunchKernelGGL(k_quant_prep<KBV>, dim3(64), dim3(256), 0, s, S, d, dC,                                     \
-                       reinterpret_cast<f16x8 *>(ws + Lw.img), reinterpret_cast<float *>(ws + Lw.invS));           \
-    if (K > 0) hipLaunchKernelGGL((k_quant_pass<KBV, false>), dim3(gq), dim3(QTHREADS), 0, s, A);                  \
-    if (grad) {                                                                                                      \
-        hipLaunchKernelGGL(k_quant_zero, dim3(gz), dim3(256), 0, s, reinterpret_cast<uint32_t *>(grad),            \
-                           (int64_t)N * d, (uint32_t *)nullptr, (int64_t)0);                                        \
-        if (K > 0) {                                                                                                 \
-            hipLaunchKernelGGL((k_quant_pass<KBV, true>), dim3(gq), dim3(QTHREADS), 0, s, A);                      \
-            hipLaunchKernelGGL(k_quant_wgrad<KBV>, gw, dim3(256), 0, s, A.F, K, Lw.Kp, d, dC, per_block, A.Wc,      \
-                               A.Wd, A.invF, A.invS, grad);                                                                 \
-        }                                                                                                            \
+                       reinterpret_cast<f16x8 *>(ws + Lw.img), reinterpret_cast<float *>(ws + Lw.invS), counts,    \
+                       reinterpret_cast<uint32_t *>(ws + Lw.psum), nsums, grad);                                    \
+    if (!grad) {                                                                                                     \
+        hipLaunchKernelGGL((k_quant_pass<KBV, false>), dim3(gq), dim3(QTHREADS), 0, s, A);                         \
+    } else {                                                                                                         \
+        hipLaunchKernelGGL((k_quant_pass<KBV, true>), dim3(gq), dim3(QTHREADS), 0, s, A);                          \
+        hipLaunchKernelGGL(k_quant_weights<KBV>, dim3(gt), dim3(256), 0, s, A);                                    \
+        hipLaunchKernelGGL((k_quant_wgrad<KBV, NC>), gw, dim3(256), 0, s, A.F, K, Lw.Kp, d, dC, per_block, A.cos,   \
+                           A.invF, A.invS, lam_d, grad);                                                            \
     }                                                                                                                \
     hipLaunchKernelGGL(k_quant_finish<KBV>, dim3(grad ? gz : 1), dim3(256), 0, s, S, d, dC, K, A.invS, A.col,      \
                        grad, counts, A.psum, A.lsum, lam_cos, lam_lb, prob_mean, losses);

@@ -85,6 +85,15 @@ def test_quantize_matches_oracle(ctx, N, d, d_clip, K):
          f"losses {L.tolist()} vs {[q2['L_cos'], q2['L_lb'], q2['L_q']]}")
 
 
+# one chunk, an odd number of chunks with the part boundary in either buffer, a
+# last dimension group of one chunk, a single row, whole and ragged rounds of 256
+# rows and more rounds than workgroups
+@pytest.mark.parametrize("N,d,d_clip,K", [(32, 128, 128, 2), (64, 128, 128, 256), (128, 640, 384, 511),
+                                          (64, 384, 256, 513), (32, 256, 128, 66000), (128, 384, 256, 65793)])
+def test_quantize_chunk_and_round_edges(ctx, N, d, d_clip, K):
+    test_quantize_matches_oracle(ctx, N, d, d_clip, K)
+
+
 def test_quantize_rejects_bad_shapes(ctx):
     from paper_2311_18482_amd import decode as DEC
     F = torch.zeros((10, 200), dtype=torch.float16, device="cuda")
