@@ -24,8 +24,9 @@
 // whose box misses the quadrant is skipped by a scalar test; early exit per
 // wave (ballot) and per workgroup (__syncthreads_count).
 // Backward: each wave owns a 16 x 16 block with 4 pixels per lane (16 x 8 with
-// 2 for 17-32 channels, 8 x 8 with 1 for wider sets or 8-pixel tiles), and
-// replays them back to front from (T_final, last): T_k = T_{k+1} / (1 - alpha_k).
+// 2 for 17-32 channels, 8 x 8 with 1 for wider sets or 8-pixel tiles; 8 x 8
+// where there are few of them), and replays them back to front from
+// (T_final, last): T_k = T_{k+1} / (1 - alpha_k).
 // Per Gaussian, a lane first sums its own pixels in registers, then the wave
 // sums the 6 + C values with a transpose reduction (lane swaps and DPP moves
 // that leave each total in one lane), and one atomic instruction adds all of
@@ -286,24 +287,7 @@ __device__ __forceinline__ TileInfo tile_info(const BlendParams &P, int64_t tile
     return t;
 }
 
-// Next tile of this workgroup: one tile per workgroup, or the next entry of
-// the heaviest-first tile order from the persistent counter.
-__device__ __forceinline__ int64_t next_tile(const BlendParams &P, int64_t prev, int64_t *s_tile)
-{
-    if (P.counter) {
-        if (threadIdx.x == 0) {
-            const uint32_t i = atomicAdd(P.counter, 1u);
-            *s_tile = (int64_t)i < P.total_tiles ? (int64_t)P.order[i] : P.total_tiles;
-        }
-        __syncthreads();
-        const int64_t t = *s_tile;
-        __syncthreads();
-        return t;
-    }
-    return prev < 0 ? (int64_t)blockIdx.x : P.total_tiles;
-}
-
-// Next forward work item: one per workgroup, or the next queue position from
+// Next work item: one per workgroup, or the next queue position from
 // the persistent counter (items / parts of one tile = one queue entry).
 __device__ __forceinline__ int64_t next_item(const BlendParams &P, int64_t prev, int64_t items, int64_t *s_item)
 {
@@ -447,13 +431,20 @@ k_blend_fwd(BlendParams P, float *__restrict__ out, float *__restrict__ Tf,
 // ---- backward ----------------------------------------------------------------------
 
 // Per-wave block of the backward: SW x SH pixels, PPL = SW * SH / 64 per lane.
-template <int TILE, int CP> struct BwdShape {
-    static constexpr int SW = (TILE == 8 || CP > 32) ? 8 : 16;
-    static constexpr int SH = (TILE == 8 || CP > 32) ? 8 : (CP <= 16 ? 16 : 8);
-    static constexpr int PPL = SW * SH / LEGS_WAVE;
-    static constexpr int NT = TILE * TILE / PPL;
+// WPG of a tile's blocks make a workgroup.
+template <int TILE, int PPLV, int WPG> struct BwdShape {
+    static constexpr int PPL = PPLV;
+    static constexpr int SW = PPL == 1 ? 8 : 16;
+    static constexpr int SH = PPL == 4 ? 16 : 8;
+    static constexpr int NT = LEGS_WAVE * WPG;
+    static constexpr int NP = TILE * TILE / (PPL * NT);    // workgroups per tile
     static constexpr int ROWSTEP = LEGS_WAVE / SW;
 };
+
+// The block that takes the least work: one reduction and one set of atomics for
+// the most pixels that the registers hold G of.
+template <int TILE, int CP>
+constexpr int bwd_ppl() { return TILE == 8 || CP > 32 ? 1 : (CP <= 16 ? 4 : 2); }
 
 // Backward of Eq. 1 per pixel, back to front from (T_final, last). With
 // w_k = alpha_k T_k and g_k = sum_c G_c c_{k,c} (G = dL/dR at the pixel),
@@ -465,12 +456,12 @@ template <int TILE, int CP> struct BwdShape {
 // and dL/do = exp(power) dL/dalpha when not clamped. The power's derivatives
 // (mean offset and conic) are summed per lane as moments of (dx, dy) and
 // turned into gradients once per Gaussian (the map is linear).
-template <int TILE, int CP>
-__global__ void __launch_bounds__((BwdShape<TILE, CP>::NT), 4)
+template <int TILE, int CP, int PPLV, int WPG>
+__global__ void __launch_bounds__((BwdShape<TILE, PPLV, WPG>::NT), 4)
 k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restrict__ last,
             const float *__restrict__ d_out, float *__restrict__ grad2d, float *__restrict__ d_ch)
 {
-    using Shp = BwdShape<TILE, CP>;
+    using Shp = BwdShape<TILE, PPLV, WPG>;
     constexpr int NT = Shp::NT, PPL = Shp::PPL, NQ = TILE / 8;
     constexpr int NV = 6 + CP;                          // values summed per Gaussian
     constexpr int KF = legs_tr::final_k(NV);
@@ -480,13 +471,8 @@ k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restr
     __shared__ uint32_t s_maxlast;
     const int B = P.batch;
     const float amax = P.amax;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / LEGS_WAVE), l = threadIdx.x % LEGS_WAVE;
+    const int l = threadIdx.x % LEGS_WAVE;
     constexpr int BX = TILE / Shp::SW;                 // wave blocks per tile row
-    const int bx0 = (w % BX) * Shp::SW, by0 = (w / BX) * Shp::SH;
-    const int lx = bx0 + (l % Shp::SW);
-    const int ly0 = by0 + (l / Shp::SW);               // pixel p of this lane: row ly0 + ROWSTEP p
-    const float fx = (float)(lx & 7);
-    const int qxi = lx >> 3;
     // which summed value this lane adds to memory after the wave reduction
     int vidx[NV];
     legs_tr::index<NV>(vidx, l);
@@ -499,7 +485,18 @@ k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restr
         vok[r] = vidx[r] >= 0 && (vgeo[r] || voff[r] < P.C);
     }
 
-    for (int64_t tile = next_tile(P, -1, &s_tile); tile < P.total_tiles; tile = next_tile(P, tile, &s_tile)) {
+    // work items: (tile, part) pairs, the parts of a tile consecutive
+    constexpr int NP = Shp::NP;
+    const int64_t items = P.total_tiles * NP;
+    for (int64_t item = next_item(P, -1, items, &s_tile); item < items; item = next_item(P, item, items, &s_tile)) {
+        const int64_t q = item / NP;
+        const int64_t tile = P.counter ? (int64_t)P.order[q] : q;
+        const int w = __builtin_amdgcn_readfirstlane((int)(item - q * NP) * WPG + threadIdx.x / LEGS_WAVE);
+        const int bx0 = (w % BX) * Shp::SW, by0 = (w / BX) * Shp::SH;
+        const int lx = bx0 + (l % Shp::SW);
+        const int ly0 = by0 + (l / Shp::SW);           // pixel p of this lane: row ly0 + ROWSTEP p
+        const float fx = (float)(lx & 7);
+        const int qxi = lx >> 3;
         const TileInfo ti = tile_info<TILE>(P, tile);
         const int64_t hw = (int64_t)ti.W * ti.H;
         float G[PPL][CP], T[PPL], gs[PPL];
@@ -736,43 +733,70 @@ k_tile_order(const uint32_t *__restrict__ ranges, int64_t T, uint32_t *__restric
     }
 }
 
+// Workgroups of a launch over `items` work items of `threads` threads. A
+// persistent one (P.counter) has enough to fill every CU several times, each
+// looping over tiles, and rebuilds its queue first.
+int64_t blend_grid(legs_ctx *ctx, const BlendParams &P, int64_t items, int threads, hipStream_t s)
+{
+    if (!P.counter) return items;
+    const int64_t per_cu = threads >= 1024 ? 2 : (threads >= 256 ? 6 : 12);
+    const int64_t cap = (int64_t)ctx->num_cus * per_cu;
+    hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, s, P.ranges, P.total_tiles,
+                       const_cast<uint32_t *>(P.order), P.counter);
+    return items < cap ? items : cap;
+}
+
+template <int TILE, int CP, int PPL, int WPG = TILE * TILE / (PPL * LEGS_WAVE)>
+int32_t launch_bwd(legs_ctx *ctx, const BlendParams &P0, const float *Tf, const uint32_t *last, const float *d_out,
+                   float *grad2d, float *d_ch, hipStream_t s)
+{
+    using Shp = BwdShape<TILE, PPL, WPG>;
+    constexpr int NT = Shp::NT;
+    BlendParams P = P0;
+    // single-wave workgroups stage at most 128 entries: a 256-entry batch would
+    // let LDS, not registers, cap the waves per CU
+    if (NT == LEGS_WAVE && P.batch > 128) P.batch = 128;
+    const size_t lds = Stage<TILE, CP>::bytes(P.batch);
+    if (lds > 65536) return legs_set_error(ctx, LEGS_ERR_UNSUPPORTED, "LDS batch too large for C");
+    if (P.total_tiles <= 0) return LEGS_OK;
+    const int64_t grid = blend_grid(ctx, P, P.total_tiles * Shp::NP, NT, s);
+    hipLaunchKernelGGL((k_blend_bwd<TILE, CP, PPL, WPG>), dim3((unsigned)grid), dim3(NT), lds, s, P, Tf, last, d_out,
+                       grad2d, d_ch);
+    LEGS_CHECK_LAUNCH(ctx);
+    return LEGS_OK;
+}
+
 template <int TILE, int CP>
-int32_t launch_tile_cp(legs_ctx *ctx, bool fwd, const BlendParams &P0, float *out, float *Tf,
+int32_t launch_tile_cp(legs_ctx *ctx, bool fwd, const BlendParams &P, float *out, float *Tf,
                        uint32_t *last, const float *cTf, const uint32_t *clast, const float *d_out,
                        float *grad2d, float *d_ch, hipStream_t s)
 {
-    BlendParams P = P0;
-    // single-wave backward workgroups stage at most 128 entries: a 256-entry
-    // batch would let LDS, not registers, cap the waves per CU
-    if (!fwd && BwdShape<TILE, CP>::NT == LEGS_WAVE && P.batch > 128) P.batch = 128;
+    if (!fwd) {
+        // Few blocks leave the chip idle for as long as the longest list takes:
+        // up to two of 16 x 16 pixels per CU (one wave for every second SIMD) they
+        // are cut to 8 x 8, four to a workgroup. In us, whole / cut: 12 channels,
+        // 16-pixel tiles, 64 blocks 501 / 187, 294: 296 / 140, 512: 375 / 181;
+        // 32-pixel tiles 557 / 196 and 371 / 189; 20 channels (16 x 8 whole) 333 /
+        // 222 and 318 / 223. Beyond the line a cut still pays (900 blocks 250 / 171,
+        // in halves 2040: 295 / 272; 3600: 363 / 415), but it multiplies the partial
+        // sums that arrive in no fixed order, and from about 600 blocks gradients
+        // that cancel to 1e-3 of their terms then differ between two runs by more
+        // than 1e-4 of themselves (whole blocks: by half of that).
+        constexpr int PPL = bwd_ppl<TILE, CP>();
+        if constexpr (PPL > 1) {
+            if (P.total_tiles * (TILE * TILE) / 256 <= 2 * (int64_t)ctx->num_cus)
+                return launch_bwd<TILE, CP, 1, 4>(ctx, P, cTf, clast, d_out, grad2d, d_ch, s);
+        }
+        return launch_bwd<TILE, CP, PPL>(ctx, P, cTf, clast, d_out, grad2d, d_ch, s);
+    }
     const size_t lds = Stage<TILE, CP>::bytes(P.batch);
     if (lds > 65536) return legs_set_error(ctx, LEGS_ERR_UNSUPPORTED, "LDS batch too large for C");
-    int64_t grid = P.total_tiles;
-    if (grid <= 0) return LEGS_OK;
-    // forward launches at 32-pixel tiles run a workgroup per 16 x 16 part (a
-    // part is a work item of its own, persistent or not)
+    if (P.total_tiles <= 0) return LEGS_OK;
+    // at 32-pixel tiles a workgroup takes a 16 x 16 part (a part is a work item of
+    // its own, persistent or not)
     constexpr int SUB = TILE == 32 ? 16 : TILE;
-    const bool parts = fwd && SUB < TILE;
-    const int threads = fwd ? (parts ? SUB * SUB : TILE * TILE) : BwdShape<TILE, CP>::NT;
-    if (parts) grid *= (TILE / SUB) * (TILE / SUB);
-    if (P.counter) {
-        // enough workgroups to fill every CU several times; each loops over tiles
-        const int64_t per_cu = threads >= 1024 ? 2 : (threads >= 256 ? 6 : 12);
-        const int64_t cap = (int64_t)ctx->num_cus * per_cu;
-        grid = grid < cap ? grid : cap;
-        hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, s, P.ranges, P.total_tiles,
-                           const_cast<uint32_t *>(P.order), P.counter);
-    }
-    if (parts) {
-        hipLaunchKernelGGL((k_blend_fwd<TILE, CP, SUB>), dim3((unsigned)grid), dim3(threads), lds, s,
-                           P, out, Tf, last);
-    } else if (fwd) {
-        hipLaunchKernelGGL((k_blend_fwd<TILE, CP, TILE>), dim3((unsigned)grid), dim3(threads), lds, s,
-                           P, out, Tf, last);
-    } else {
-        hipLaunchKernelGGL((k_blend_bwd<TILE, CP>), dim3((unsigned)grid), dim3(threads), lds, s,
-                           P, cTf, clast, d_out, grad2d, d_ch);
-    }
+    const int64_t grid = blend_grid(ctx, P, P.total_tiles * (TILE / SUB) * (TILE / SUB), SUB * SUB, s);
+    hipLaunchKernelGGL((k_blend_fwd<TILE, CP, SUB>), dim3((unsigned)grid), dim3(SUB * SUB), lds, s, P, out, Tf, last);
     LEGS_CHECK_LAUNCH(ctx);
     return LEGS_OK;
 }

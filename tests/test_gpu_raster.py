@@ -99,6 +99,31 @@ def test_ragged_multiview(R):
         full_check(R, scene, cams, tile=tile, batch=128)
 
 
+@pytest.mark.parametrize("w,h,tile,d_sem", [(511, 255, 16, 8), (511, 270, 16, 8), (511, 255, 32, 8), (511, 270, 32, 12),
+                                            (511, 255, 16, 16), (511, 270, 16, 16), (505, 250, 32, 16), (61, 33, 32, 0),
+                                            (61, 33, 16, 28)])
+def test_backward_block_sizes(R, w, h, tile, d_sem):
+    """Images on both sides of the line where the backward's wave blocks are cut
+    (512 blocks of 16 x 16 with 256 compute units), and below one block per
+    compute unit; 4 to 32 channels."""
+    scene = synth.make_scene(3000, 40 + d_sem, synth.VOL_C1, d_sem=d_sem)
+    full_check(R, scene, [synth.camera_front(w, h, 0.9 * w)], tile=tile)
+
+
+@pytest.mark.parametrize("tile", [16, 32])
+def test_cut_backward_blocks_from_the_persistent_queue(R, tile):
+    """Parts of a tile as entries of the persistent queue."""
+    scene = synth.make_scene(3000, 77, synth.VOL_C1, d_sem=8)
+    cams = [synth.camera_front(150, 90, 140.0), synth.camera_front(37, 53, 40.0)]
+    G = synth.upstream_grads(cams, scene.n_channels, 78)
+    got = []
+    for persistent in (False, True):
+        rast, d, proj, bins, out, T, last = run_forward(R, scene, cams, R.opts(tile=tile, persistent=persistent))
+        _, g, d_ch = run_backward(R, rast, d, proj, bins, T, last, G)
+        got.append(PT.gpu_grads_to_np(g, d_ch))
+    PT.compare_grads(got[1], got[0], scene.n)
+
+
 def test_many_views_index_apart_from_depth_keys(R):
     """520 small views: the G-view depth keys need 6 digit passes (10 view bits
     above the 32 depth bits) and the G-view index 17 bits, more than 64 in all,
