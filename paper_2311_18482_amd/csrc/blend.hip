@@ -20,9 +20,10 @@
 // forward's decisions exactly. The offsets are also accurate to float32
 // relative precision anywhere on a 4K image.
 //
-// Forward: each wave64 owns an 8 x 8 quadrant, one pixel per lane; a Gaussian
-// whose box misses the quadrant is skipped by a scalar test; early exit per
-// wave (ballot) and per workgroup (__syncthreads_count).
+// Forward: each wave64 owns an 8 x 8 quadrant, one pixel per lane (8 x 4 or 4 x 4
+// pixels with two or four lanes each in small renders); a Gaussian whose box
+// misses the quadrant is skipped by a scalar test; early exit per wave (ballot)
+// and per workgroup (__syncthreads_count).
 // Backward: each wave owns a 16 x 16 block with 4 pixels per lane (16 x 8 with
 // 2 for 17-32 channels, 8 x 8 with 1 for wider sets or 8-pixel tiles; 8 x 8
 // where there are few of them), and replays them back to front from
@@ -310,19 +311,30 @@ __device__ __forceinline__ int64_t next_item(const BlendParams &P, int64_t prev,
 // channels and 256-thread workgroups: the LDS limit of a 256-entry batch (7 at
 // 16 x 16 tiles, 6 for the 16 x 16 parts of 32 x 32 tiles), which costs at
 // most a few spills of loop invariants outside the visit loop; none elsewhere.
-template <int TILE, int CP, int SUB>
-constexpr int fwd_waves() { return SUB != 16 || CP > 12 ? 1 : (TILE == 16 ? 7 : 6); }
+template <int TILE, int CP, int LPP>
+constexpr int fwd_waves() { return TILE == 8 || LPP > 1 || CP > 12 ? 1 : (TILE == 16 ? 7 : 6); }
 
-// SUB < TILE: each workgroup composites one SUB x SUB part of a tile over the
-// whole tile's list (one workgroup per part, one-per-tile launches only), so
+// Pixels of a forward workgroup of four waves (one at 8-pixel tiles) and of a
+// wave, with LPP lanes per pixel, each accumulating CP / LPP channels.
+template <int TILE, int LPP> struct FwdShape {
+    static constexpr int SW = TILE == 8 || LPP == 4 ? 8 : 16;
+    static constexpr int SH = TILE == 8 || LPP > 1 ? 8 : 16;
+    static constexpr int NT = SW * SH * LPP;
+    static constexpr int NSX = TILE / SW, NP = NSX * (TILE / SH);   // parts of a tile
+    static constexpr int BW = LPP == 4 ? 4 : 8, BH = LPP == 1 ? 8 : 4;
+};
+
+// Each workgroup composites one part of a tile over the whole tile's list, so
 // a part stops as soon as its own pixels are done.
-template <int TILE, int CP, int SUB>
-__global__ void __launch_bounds__(SUB *SUB) __attribute__((amdgpu_waves_per_eu(fwd_waves<TILE, CP, SUB>())))
+template <int TILE, int CP, int LPP>
+__global__ void __launch_bounds__((FwdShape<TILE, LPP>::NT)) __attribute__((amdgpu_waves_per_eu(fwd_waves<TILE, CP, LPP>())))
 k_blend_fwd(BlendParams P, float *__restrict__ out, float *__restrict__ Tf,
             uint32_t *__restrict__ last)
 {
-    constexpr int NT = SUB * SUB, NQ = TILE / 8, NS = TILE / SUB, QS = SUB / 8;
-    static_assert(NS * SUB == TILE, "parts tile the tile");
+    using Shp = FwdShape<TILE, LPP>;
+    constexpr int NT = Shp::NT, NQ = TILE / 8, NP = Shp::NP, BW = Shp::BW, BH = Shp::BH;
+    constexpr int NPIX = LEGS_WAVE / LPP, CL = CP / LPP;   // pixels per wave, channels per lane
+    static_assert(CL * LPP == CP && BW * BH == NPIX, "channels and pixels over the lanes");
     extern __shared__ float4 s_dyn[];
     Stage<TILE, CP> S(s_dyn, P.batch);
     __shared__ int64_t s_tile;
@@ -338,24 +350,26 @@ k_blend_fwd(BlendParams P, float *__restrict__ out, float *__restrict__ Tf,
         if (blockIdx.x == 0 && (int)threadIdx.x < P.zero_tail)
             reinterpret_cast<float *>(P.zero4 + P.zero_n4)[threadIdx.x] = 0.0f;
     }
-    const float fx = (float)(l & 7), fy = (float)(l >> 3);
+    const int pi = l % NPIX, c_first = l / NPIX * CL;      // this lane's pixel and channels
     // work items: (tile, part) pairs, the parts of a tile consecutive; one
     // item per workgroup, or the persistent queue (heaviest tiles first)
-    constexpr int NP = NS * NS;
     const int64_t items = P.total_tiles * NP;
     for (int64_t item = next_item(P, -1, items, &s_tile); item < items; item = next_item(P, item, items, &s_tile)) {
         const int64_t q = item / NP;
         const int part = (int)(item - q * NP);
         const int64_t tile = P.counter ? (int64_t)P.order[q] : q;
-        const int qxi = (part % NS) * QS + w % QS, qyi = (part / NS) * QS + w / QS;   // this wave's 8 x 8 quadrant
-        const int qx0 = 8 * qxi, qy0 = 8 * qyi;
-        const int lx = qx0 + (l & 7), ly = qy0 + (l >> 3);
+        // this wave's block of BW x BH pixels
+        const int qx0 = (part % Shp::NSX) * Shp::SW + w % (Shp::SW / BW) * BW;
+        const int qy0 = (part / Shp::NSX) * Shp::SH + w / (Shp::SW / BW) * BH;
+        const int qxi = qx0 >> 3, qyi = qy0 >> 3;
+        const int lx = qx0 + pi % BW, ly = qy0 + pi / BW;
+        const float fx = (float)(lx & 7), fy = (float)(ly & 7);
         const TileInfo ti = tile_info<TILE>(P, tile);
         const int px = ti.tile_x0 + lx, py = ti.tile_y0 + ly;
         const bool inside = px < ti.W && py < ti.H;
-        float acc[CP];
+        float acc[CL];
 #pragma unroll
-        for (int c = 0; c < CP; ++c) acc[c] = 0.0f;
+        for (int c = 0; c < CL; ++c) acc[c] = 0.0f;
         float T = 1.0f;
         uint32_t lastpos = 0;
         uint64_t donemask = legs_ballot(!inside);   // pixels that stopped (or lie off the image)
@@ -363,21 +377,29 @@ k_blend_fwd(BlendParams P, float *__restrict__ out, float *__restrict__ Tf,
             if (__syncthreads_count(l == 0 && ~donemask != 0) == 0) break;
             const int nb = (int)min((uint32_t)B, ti.re - lo);
             stage_batch<TILE, CP, NT>(P, ti.v, ti.tile_x0, ti.tile_y0, lo, nb, S);
-            // 64 entries at a time: lane l computes the mask of this wave's 8 x 8
-            // block pixels inside entry c0 + l's box; an entry is visited only
-            // while it covers a pixel that is not done, and only those lanes work
+            // 64 entries at a time: lane l computes the mask of this wave's pixels
+            // inside entry c0 + l's box; an entry is visited only while it covers a
+            // pixel that is not done, and only those lanes work
             for (int c0 = 0; c0 < nb && ~donemask; c0 += LEGS_WAVE) {
                 uint32_t mlo = 0, mhi = 0;
                 if (c0 + l < nb) {
                     const uint32_t pk = S.box[c0 + l];
-                    const int cx0 = max(sext8(pk, 0) - qx0, 0), cx1 = min(sext8(pk, 8) - qx0, 7);
-                    const int ry0 = max(sext8(pk, 16) - qy0, 0), ry1 = min(sext8(pk, 24) - qy0, 7);
+                    const int cx0 = max(sext8(pk, 0) - qx0, 0), cx1 = min(sext8(pk, 8) - qx0, BW - 1);
+                    const int ry0 = max(sext8(pk, 16) - qy0, 0), ry1 = min(sext8(pk, 24) - qy0, BH - 1);
                     if (cx0 <= cx1 && ry0 <= ry1) {
-                        const uint32_t xm = (0xffu << cx0) & (0xffu >> (7 - cx1));
-                        const uint32_t xr = xm * 0x01010101u;
-                        const uint64_t rows = (~0ull << (8 * ry0)) & (~0ull >> (8 * (7 - ry1)));
-                        mlo = (uint32_t)rows & xr;
-                        mhi = (uint32_t)(rows >> 32) & xr;
+                        constexpr uint32_t row = (1u << BW) - 1u;
+                        const uint32_t xm = (row << cx0) & (row >> (BW - 1 - cx1));
+                        const uint32_t xr = xm * (BW == 8 ? 0x01010101u : 0x11111111u);
+                        if constexpr (LPP == 1) {
+                            const uint64_t rows = (~0ull << (8 * ry0)) & (~0ull >> (8 * (7 - ry1)));
+                            mlo = (uint32_t)rows & xr;
+                            mhi = (uint32_t)(rows >> 32) & xr;
+                        } else {
+                            constexpr uint32_t all = 0xffffffffu >> (32 - NPIX);
+                            mlo = (all << (BW * ry0)) & (all >> (BW * (BH - 1 - ry1))) & xr;
+                            if constexpr (LPP == 4) mlo |= mlo << 16;
+                            mhi = mlo;                 // the same pixels in every group of lanes
+                        }
                     }
                 }
                 uint64_t rel = legs_ballot(((((uint64_t)mhi << 32) | mlo) & ~donemask) != 0);
@@ -405,9 +427,9 @@ k_blend_fwd(BlendParams P, float *__restrict__ out, float *__restrict__ Tf,
                     donemask |= reach & stop;
                     if (__builtin_amdgcn_inverse_ballot_w64(reach & ~stop)) {
                         const float wgt = alpha * T;
-                        const float *cj = S.ch + j * CP;
+                        const float *cj = S.ch + j * CP + c_first;
 #pragma unroll
-                        for (int c = 0; c < CP; ++c) acc[c] = fmaf(wgt, cj[c], acc[c]);
+                        for (int c = 0; c < CL; ++c) acc[c] = fmaf(wgt, cj[c], acc[c]);
                         T = Tn;
                         lastpos = (lo - ti.rs) + (uint32_t)j + 1u;
                     }
@@ -420,8 +442,9 @@ k_blend_fwd(BlendParams P, float *__restrict__ out, float *__restrict__ Tf,
             const int64_t hw = (int64_t)ti.W * ti.H;
             float *o = out + (int64_t)P.C * ti.pixel_offset + (int64_t)py * ti.W + px;
 #pragma unroll
-            for (int c = 0; c < CP; ++c)
-                if (c < P.C) o[c * hw] = acc[c];
+            for (int c = 0; c < CL; ++c)
+                if (c_first + c < P.C) o[(c_first + c) * hw] = acc[c];
+            if (LPP > 1 && l >= NPIX) continue;
             Tf[pix] = T;
             last[pix] = lastpos;
         }
@@ -766,6 +789,19 @@ int32_t launch_bwd(legs_ctx *ctx, const BlendParams &P0, const float *Tf, const 
     return LEGS_OK;
 }
 
+template <int TILE, int CP, int LPP>
+int32_t launch_fwd(legs_ctx *ctx, const BlendParams &P, float *out, float *Tf, uint32_t *last, hipStream_t s)
+{
+    using Shp = FwdShape<TILE, LPP>;
+    const size_t lds = Stage<TILE, CP>::bytes(P.batch);
+    if (lds > 65536) return legs_set_error(ctx, LEGS_ERR_UNSUPPORTED, "LDS batch too large for C");
+    if (P.total_tiles <= 0) return LEGS_OK;
+    const int64_t grid = blend_grid(ctx, P, P.total_tiles * Shp::NP, Shp::NT, s);
+    hipLaunchKernelGGL((k_blend_fwd<TILE, CP, LPP>), dim3((unsigned)grid), dim3(Shp::NT), lds, s, P, out, Tf, last);
+    LEGS_CHECK_LAUNCH(ctx);
+    return LEGS_OK;
+}
+
 template <int TILE, int CP>
 int32_t launch_tile_cp(legs_ctx *ctx, bool fwd, const BlendParams &P, float *out, float *Tf,
                        uint32_t *last, const float *cTf, const uint32_t *clast, const float *d_out,
@@ -789,16 +825,19 @@ int32_t launch_tile_cp(legs_ctx *ctx, bool fwd, const BlendParams &P, float *out
         }
         return launch_bwd<TILE, CP, PPL>(ctx, P, cTf, clast, d_out, grad2d, d_ch, s);
     }
-    const size_t lds = Stage<TILE, CP>::bytes(P.batch);
-    if (lds > 65536) return legs_set_error(ctx, LEGS_ERR_UNSUPPORTED, "LDS batch too large for C");
-    if (P.total_tiles <= 0) return LEGS_OK;
-    // at 32-pixel tiles a workgroup takes a 16 x 16 part (a part is a work item of
-    // its own, persistent or not)
-    constexpr int SUB = TILE == 32 ? 16 : TILE;
-    const int64_t grid = blend_grid(ctx, P, P.total_tiles * (TILE / SUB) * (TILE / SUB), SUB * SUB, s);
-    hipLaunchKernelGGL((k_blend_fwd<TILE, CP, SUB>), dim3((unsigned)grid), dim3(SUB * SUB), lds, s, P, out, Tf, last);
-    LEGS_CHECK_LAUNCH(ctx);
-    return LEGS_OK;
+    // With few pixels, two or four lanes share one (each with its part of the
+    // channels), so that more waves walk shorter lists. The lines lie at 3/2 and
+    // 3/4 blocks of 16 x 16 per CU. In us with 1 / 2 / 4 lanes per pixel at 12
+    // channels: 64 blocks 99 / 84 / 77, 121: 86 / 73 / 68, 196: 106 / 90 / 86, 256:
+    // 114 / 104 / 104, 294: 81 / 75 / 85, 384: 74 / 73 / 89, 500: 104 / 102 / 142,
+    // 900: 78 / 102 / 143; 32-pixel tiles 64: 111 / 91 / 85, 256: 137 / 125 / 132;
+    // 20 channels 64: 117 / 97 / 88, 256: 87 / 76 / 78.
+    if constexpr (TILE > 8 && CP <= 32) {
+        const int64_t blocks = P.total_tiles * (TILE * TILE) / 256, cus = ctx->num_cus;
+        if (4 * blocks <= 3 * cus) return launch_fwd<TILE, CP, 4>(ctx, P, out, Tf, last, s);
+        if (2 * blocks <= 3 * cus) return launch_fwd<TILE, CP, 2>(ctx, P, out, Tf, last, s);
+    }
+    return launch_fwd<TILE, CP, 1>(ctx, P, out, Tf, last, s);
 }
 
 template <int TILE>

@@ -99,6 +99,22 @@ def test_ragged_multiview(R):
         full_check(R, scene, cams, tile=tile, batch=128)
 
 
+@pytest.mark.parametrize("w,h,d_sem", [(20, 20, 8), (253, 185, 8), (271, 185, 0), (380, 250, 16), (400, 250, 28)])
+def test_forward_lanes_per_pixel(R, w, h, d_sem):
+    """Images on both sides of the lines where two and four lanes share a pixel
+    (384 and 192 blocks of 16 x 16 with 256 compute units): the same bits as with
+    8-pixel tiles, where a lane always has a pixel of its own."""
+    scene = synth.make_scene(3000, 90 + d_sem, synth.VOL_C1, d_sem=d_sem)
+    cams = [synth.camera_front(w, h, 0.9 * w)]
+    want = None
+    for tile, persistent in ((8, False), (16, False), (32, False), (16, True), (32, True)):
+        _, _, _, _, out, T, last = run_forward(R, scene, cams, R.opts(tile=tile, persistent=persistent))
+        got = (out.cpu().numpy(), T.cpu().numpy())
+        if want is None:
+            want = got
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), (tile, persistent)
+
+
 @pytest.mark.parametrize("w,h,tile,d_sem", [(511, 255, 16, 8), (511, 270, 16, 8), (511, 255, 32, 8), (511, 270, 32, 12),
                                             (511, 255, 16, 16), (511, 270, 16, 16), (505, 250, 32, 16), (61, 33, 32, 0),
                                             (61, 33, 16, 28)])
