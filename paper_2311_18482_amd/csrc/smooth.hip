@@ -20,14 +20,18 @@
 //                    dL/ds_G (accumulated into the channel gradient), and
 //                    dz of every layer; writes the bf16 hidden activations and
 //                    dz (as its two bf16 parts) into the workspace planes in
-//                    the weight gradient's operand order, each lane's 8 rows
-//                    transposed across its group of 8 lanes first so that one
-//                    16-byte store is one operand fragment.
+//                    the weight gradient's operand order, each block turned by
+//                    the matrix unit so that a wave stores 1 KB contiguous.
+//                    Bound by its stores, 2.4 KB a Gaussian (without them it
+//                    takes 0.13 ms for 1M): plane after plane and past the
+//                    caches, 0.64 ms.
 //  k_smooth_wgrad    dW_l = sum_g dz_l h_(l-1)^T and db_l = sum_g dz_l: the
 //                    Gaussians are the MFMA contraction, each operand one
 //                    16-byte load (a wave's load of a 128-row plane is 1 KB
-//                    contiguous); split over Gaussian chunks (x) and layers
-//                    (y), float atomics into the gradient.
+//                    contiguous); whole products per wave, so that the planes
+//                    are read once, past the caches, and a third of the atomics
+//                    are left. Bound by the reads: 0.41 ms
+//                    for 1M, a row block per wave and 245 chunks 0.56.
 #include "legs_internal.h"
 #include "legs_decode_internal.h"
 #include "lane_transpose.h"
@@ -51,70 +55,62 @@ struct SmoothLds {
     bf16x8 t3[SB * SK * 64], t2[SB * SK * 64];
 };
 
-__device__ void smooth_stage(const float *__restrict__ P, SmoothLds &L)
+__device__ __forceinline__ void smooth_stage(const float *__restrict__ P, SmoothLds &L)
 {
+    constexpr int NT = 256;
     const float *W1 = P + LEGS_SMOOTH_OFF_W1, *b1 = P + LEGS_SMOOTH_OFF_B1;
     const float *W2 = P + LEGS_SMOOTH_OFF_W2, *b2 = P + LEGS_SMOOTH_OFF_B2;
     const float *W3 = P + LEGS_SMOOTH_OFF_W3, *b3 = P + LEGS_SMOOTH_OFF_B3;
     const float *W4 = P + LEGS_SMOOTH_OFF_W4, *b4 = P + LEGS_SMOOTH_OFF_B4;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    // layer 1: lower half [wx wy wz wx wy wz wx wy], upper half [wz b_hi b_mid b_lo 0 0 0 0]
-    for (int i = tid; i < SB * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, mb = i >> 9;
-        const int row = 32 * mb + (l & 31), h = l >> 5;
-        __bf16 v;
-        if (h == 0) {
-            v = (__bf16)W1[row * 3 + e % 3];
-        } else if (e == 0) {
-            v = (__bf16)W1[row * 3 + 2];
-        } else if (e <= 3) {
-            __bf16 p[3];
-            legs_split3(b1[row], p[0], p[1], p[2]);
-            v = p[e - 1];
-        } else {
-            v = (__bf16)0.0f;
-        }
-        reinterpret_cast<__bf16 *>(L.w1)[i] = v;
-    }
     // hidden layers and their transposes: fragment (block, k-step, lane, e)
     // = row 32 block + lane % 32, column legs_khid(k-step, lane / 32, e)
-    for (int i = tid; i < SB * SK * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, ks = (i >> 9) % SK, mb = (i >> 9) / SK;
-        const int row = 32 * mb + (l & 31), col = legs_khid(ks, l >> 5, e);
-        reinterpret_cast<__bf16 *>(L.w2)[i] = (__bf16)W2[row * SH + col];
-        reinterpret_cast<__bf16 *>(L.w3)[i] = (__bf16)W3[row * SH + col];
-        reinterpret_cast<__bf16 *>(L.t3)[i] = (__bf16)W3[col * SH + row];
-        reinterpret_cast<__bf16 *>(L.t2)[i] = (__bf16)W2[col * SH + row];
-    }
-    for (int i = tid; i < SK * 64 * 8; i += nt) {       // W4: rows 8..31 zero
-        const int e = i & 7, l = (i >> 3) & 63, ks = i >> 9;
-        const int row = l & 31;
-        reinterpret_cast<__bf16 *>(L.w4)[i] =
-            row < LEGS_SMOOTH_OUT ? (__bf16)W4[row * SH + legs_khid(ks, l >> 5, e)] : (__bf16)0.0f;
-    }
+    auto rows = [](const float *W) {
+        return [W](int i) {
+            const int l = i & 63, ks = (i >> 6) % SK, mb = (i >> 6) / SK;
+            return legs_frag_row(W + (32 * mb + (l & 31)) * SH, ks, l >> 5);
+        };
+    };
+    auto columns = [](const float *W) {
+        return [W](int i) {
+            const int l = i & 63, ks = (i >> 6) % SK, mb = (i >> 6) / SK;
+            bf16x8 f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f[e] = (__bf16)W[legs_khid(ks, l >> 5, e) * SH + 32 * mb + (l & 31)];
+            return f;
+        };
+    };
+    legs_stage_frags<SB * SK * 64, NT, 4>(L.w2, rows(W2));
+    legs_stage_frags<SB * SK * 64, NT, 4>(L.w3, rows(W3));
+    legs_stage_frags<SB * SK * 64, NT, 4>(L.t3, columns(W3));
+    legs_stage_frags<SB * SK * 64, NT, 4>(L.t2, columns(W2));
+    legs_stage_frags<SK * 64, NT, 2>(L.w4, [&](int i) {      // W4: rows 8..31 zero
+        const int l = i & 63, row = l & 31;
+        return row < LEGS_SMOOTH_OUT ? legs_frag_row(W4 + row * SH, i >> 6, l >> 5) : (bf16x8){};
+    });
+    // layer 1: lower half [wx wy wz wx wy wz wx wy], upper half [wz b_hi b_mid b_lo 0 0 0 0]
+    legs_stage_frags<SB * 64, NT, 1>(L.w1, [&](int i) {
+        const int row = 32 * (i >> 6) + (i & 31);
+        const __bf16 x = (__bf16)W1[row * 3], y = (__bf16)W1[row * 3 + 1], z = (__bf16)W1[row * 3 + 2];
+        __bf16 p[3];
+        legs_split3(b1[row], p[0], p[1], p[2]);
+        const __bf16 o = (__bf16)0.0f;
+        const bf16x8 lower = {x, y, z, x, y, z, x, y}, upper = {z, p[0], p[1], p[2], o, o, o, o};
+        return (i >> 5) & 1 ? upper : lower;
+    });
     // W4^T: k-slot e of half h is output legs_khid(0, h, e) (outputs 0..7
     // sit in slots 0..3 of both halves)
-    for (int i = tid; i < SB * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, mb = i >> 9;
-        const int o = legs_khid(0, l >> 5, e);
-        reinterpret_cast<__bf16 *>(L.t4)[i] =
-            o < LEGS_SMOOTH_OUT ? (__bf16)W4[o * SH + 32 * mb + (l & 31)] : (__bf16)0.0f;
-    }
-    for (int i = tid; i < (2 * SB + 1) * 64 * 8; i += nt) {
-        const int e = i & 7, l = (i >> 3) & 63, mb = i >> 9;
-        const int row = 32 * (mb % SB) + (l & 31);
-        float b = 0.0f;
-        if (mb < SB) b = b2[row];
-        else if (mb < 2 * SB) b = b3[row];
-        else b = row < LEGS_SMOOTH_OUT ? b4[row] : 0.0f;
-        __bf16 p[3];
-        legs_split3(b, p[0], p[1], p[2]);
-        const __bf16 v = ((l >> 5) == 1 && e < 3) ? p[e] : (__bf16)0.0f;
-        __bf16 *dst = mb < SB ? reinterpret_cast<__bf16 *>(L.bb2) + (mb * 64 + l) * 8
-                    : mb < 2 * SB ? reinterpret_cast<__bf16 *>(L.bb3) + ((mb - SB) * 64 + l) * 8
-                                  : reinterpret_cast<__bf16 *>(L.bb4) + l * 8;
-        dst[e] = v;
-    }
+    legs_stage_frags<SB * 64, NT, 1>(L.t4, [&](int i) {
+        const int l = i & 63, mb = i >> 6;
+        bf16x8 f = {};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = (__bf16)W4[legs_khid(0, l >> 5, e) * SH + 32 * mb + (l & 31)];
+        return f;
+    });
+    legs_stage_frags<SB * 64, NT, 1>(L.bb2, [&](int i) { return legs_frag_bias(b2[32 * (i >> 6) + (i & 31)], (i >> 5) & 1); });
+    legs_stage_frags<SB * 64, NT, 1>(L.bb3, [&](int i) { return legs_frag_bias(b3[32 * (i >> 6) + (i & 31)], (i >> 5) & 1); });
+    legs_stage_frags<64, NT, 1>(L.bb4, [&](int i) {
+        return legs_frag_bias((i & 31) < LEGS_SMOOTH_OUT ? b4[i & 31] : 0.0f, (i >> 5) & 1);
+    });
 }
 
 // bf16 split of 8 accumulator values (first .. first + 7): hi = bf16(z),
@@ -161,33 +157,86 @@ __device__ __forceinline__ void layer_block(const bf16x8 *__restrict__ wA, const
     }
 }
 
-// Eight rows (row(e), e = 0..7) of this lane's Gaussian into a plane of R
-// rows in fragment order: transposed across the lane's group of 8 (Gaussians
-// g0 .. g0 + 7), lane i stores row(i) of those Gaussians, one 16-byte
-// fragment; rows at or past R are not stored.
-template <typename RowOf>
-__device__ __forceinline__ void store_rows8(__bf16 *__restrict__ plane, int R, int64_t g0, bf16x8 v, RowOf row_of,
-                                            int i8, bool b1, uint32_t psel)
+// Lanes and Gaussians of a tile: lane l holds Gaussian l % 32 with bits 2 and 3
+// swapped, so that the 16 rows of a lane half in an MFMA result are two runs of
+// 8 Gaussians in order (rows legs_drow(r, h): Gaussians 8 h + r and, from r = 8,
+// 16 more), the two 16-byte fragments of the planes.
+__device__ __forceinline__ int swap23(int x) { return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1); }
+
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(16))) int i32x16;
+
+__device__ __forceinline__ i32x16 mfma_i8(const bf16x8 &a, i32x4 b, i32x16 c)
 {
-    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-    const u32x4 x = __builtin_bit_cast(u32x4, v);
-    uint32_t w[4] = {x[0], x[1], x[2], x[3]};
-    legs_lt::oct_transpose(w, b1, psel);
-    const int row = row_of(i8);
-    if (row < R) *reinterpret_cast<uint4 *>(plane + frag_at(g0, R, row)) = make_uint4(w[0], w[1], w[2], w[3]);
+    return __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, a), b, c, 0, 0, 0);
+}
+
+// A block of 32 rows x the tile's 32 Gaussians, held as two B fragments (lane =
+// Gaussian, k-slots = rows in accumulator order), turned into the two fragments
+// with lane = row, 8 Gaussians each: as the A operand against the identity the
+// matrix unit returns the block transposed. In bytes, the low and the high ones
+// of the values apart, so that every bit pattern comes through (against a bf16
+// identity an infinity would turn its row's other Gaussians into NaN). 28
+// instructions for a block where lane swaps took 52.
+// id: this lane's identity fragments, [low, high byte][k-step].
+__device__ __forceinline__ void turn(const bf16x8 &f0, const bf16x8 &f1, const i32x4 *id, bf16x8 (&out)[2])
+{
+    const i32x16 lo = mfma_i8(f1, id[LEGS_WAVE], mfma_i8(f0, id[0], (i32x16){}));
+    const i32x16 hi = mfma_i8(f1, id[3 * LEGS_WAVE], mfma_i8(f0, id[2 * LEGS_WAVE], (i32x16){}));
+    i32x4 w[2];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const uint32_t a = __builtin_amdgcn_perm(lo[2 * q + 1], lo[2 * q], 0x0c040c00u);
+        const uint32_t b = __builtin_amdgcn_perm(hi[2 * q + 1], hi[2 * q], 0x0c040c00u);
+        w[q >> 2][q & 3] = (int)(b << 8 | a);
+    }
+    out[0] = __builtin_bit_cast(bf16x8, w[0]);
+    out[1] = __builtin_bit_cast(bf16x8, w[1]);
+}
+
+// Row block mb of a 128-row plane: 1 KB contiguous per fragment.
+__device__ __forceinline__ void store_block(__bf16 *__restrict__ plane, int64_t g0, int mb, const bf16x8 &f0,
+                                            const bf16x8 &f1, const i32x4 *id, int lane)
+{
+    bf16x8 f[2];
+    turn(f0, f1, id, f);
+    __bf16 *p = plane + frag_at(g0, SH, 32 * mb) + 8 * lane;
+    __builtin_nontemporal_store(f[0], reinterpret_cast<bf16x8 *>(p));
+    __builtin_nontemporal_store(f[1], reinterpret_cast<bf16x8 *>(p + SB * 64 * 8));
+    __builtin_amdgcn_sched_barrier(0);          // one block's registers at a time
+}
+
+// A plane of R <= 16 rows from one fragment; lane column n holds row row(n).
+template <int R, typename RowOf>
+__device__ __forceinline__ void store_narrow(__bf16 *__restrict__ plane, int64_t g0, const bf16x8 &v, const i32x4 *id,
+                                             int lane, RowOf row_of)
+{
+    bf16x8 f[2];
+    turn(v, (bf16x8){}, id, f);
+    if ((lane & 31) >= R) return;
+    __bf16 *p = plane + frag_at(g0, R, row_of(lane & 31)) + R * 8 * (lane >> 5);
+    *reinterpret_cast<bf16x8 *>(p) = f[0];
+    *reinterpret_cast<bf16x8 *>(p + 2 * R * 8) = f[1];
 }
 
 __global__ void __launch_bounds__(256)
 k_smooth_fwd_bwd(SmoothArgs A)
 {
     __shared__ SmoothLds L;
+    __shared__ i32x4 ident[4 * 64];        // the identity in accumulator order (turn)
+    __shared__ float s_loss[4];
     smooth_stage(A.params, L);
-    __syncthreads();
     const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
-    // position in the lane's group of 8 for the transposed plane stores
-    const int i8 = lane & 7;
-    const bool b1 = (lane & 2) != 0;
-    const uint32_t psel = (lane & 1) ? 0x03020706u : 0x05040100u;
+    {
+        union {
+            int8_t b[16];
+            i32x4 v;
+        } f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) f.b[k] = (k & 1) == (wave >> 1) && (lane & 31) == legs_khid(wave & 1, h, k >> 1);
+        ident[wave * 64 + lane] = f.v;
+    }
+    __syncthreads();
     const int64_t groups = (A.n + 32 * SNT - 1) / (32 * SNT);
     const int64_t stride = (int64_t)gridDim.x * 4;
     float lsum = 0.0f;
@@ -195,12 +244,13 @@ k_smooth_fwd_bwd(SmoothArgs A)
         int off = 0;
         asm volatile("" : "+s"(off));     // fragments are re-read from LDS every group
         const int ln = lane + off;
+        const i32x4 *id = ident + ln;
         int64_t gi[SNT];
         bool valid[SNT];
         bf16x8 x[SNT][1];
 #pragma unroll
         for (int t = 0; t < SNT; ++t) {
-            gi[t] = (grp * SNT + t) * 32 + (lane & 31);
+            gi[t] = (grp * SNT + t) * 32 + swap23(lane & 31);
             valid[t] = gi[t] < A.n;
             float p[3] = {0.0f, 0.0f, 0.0f};
             if (valid[t]) {
@@ -222,14 +272,6 @@ k_smooth_fwd_bwd(SmoothArgs A)
                 v[4] = v[5] = v[6] = v[7] = (__bf16)0.0f;
             }
             x[t][0] = v;
-            // layer-1 input plane for the weight gradient: rows 0..8 the split
-            // coordinates (part-major), row 9 ones (zero for padding
-            // Gaussians), rows 10..15 zero; lane half h holds rows 8 h .. 8 h + 7
-            if (h == 1) {
-                v[1] = valid[t] ? (__bf16)1.0f : (__bf16)0.0f;
-                v[2] = v[3] = (__bf16)0.0f;
-            }
-            store_rows8(A.X, 16, gi[t] - i8, v, [h](int i) { return 8 * h + i; }, i8, b1, psel);
         }
         // forward
         bf16x8 h1[SNT][SK], h2[SNT][SK], h3[SNT][SK];
@@ -265,17 +307,32 @@ k_smooth_fwd_bwd(SmoothArgs A)
         }
         f32x16 s4[SNT];
         layer_block<SK>(L.w4, L.bb4, 0, ln, h3, s4);
-        // hidden activations to the workspace (zero for padding Gaussians)
+        // inputs and hidden activations to the workspace (zero for padding
+        // Gaussians). Input rows 0..8: the split coordinates (part-major), row 9
+        // ones, rows 10..15 zero; lane half h holds rows 8 h .. 8 h + 7
+        if (h == 1) {
+#pragma unroll
+            for (int t = 0; t < SNT; ++t) x[t][0][2] = x[t][0][3] = (__bf16)0.0f;
+        }
+        if (legs_ballot(valid[0] && valid[1]) != ~0ull) {
+#pragma unroll
+            for (int t = 0; t < SNT; ++t) {
+                if (valid[t]) continue;
+                x[t][0] = (bf16x8){};
+#pragma unroll
+                for (int ks = 0; ks < SK; ++ks) h1[t][ks] = h2[t][ks] = h3[t][ks] = (bf16x8){};
+            }
+        }
 #pragma unroll
         for (int t = 0; t < SNT; ++t) {
+            const int64_t g0 = (grp * SNT + t) * 32;
+            store_narrow<16>(A.X, g0, x[t][0], id, lane, [](int n) { return swap23(n); });
 #pragma unroll
-            for (int ks = 0; ks < SK; ++ks) {
-                const auto unit = [ks, h](int i) { return legs_khid(ks, h, i); };
-                const bf16x8 z8 = {};
-                store_rows8(A.H1, SH, gi[t] - i8, valid[t] ? h1[t][ks] : z8, unit, i8, b1, psel);
-                store_rows8(A.H2, SH, gi[t] - i8, valid[t] ? h2[t][ks] : z8, unit, i8, b1, psel);
-                store_rows8(A.H3, SH, gi[t] - i8, valid[t] ? h3[t][ks] : z8, unit, i8, b1, psel);
-            }
+            for (int mb = 0; mb < SB; ++mb) store_block(A.H1, g0, mb, h1[t][2 * mb], h1[t][2 * mb + 1], id, lane);
+#pragma unroll
+            for (int mb = 0; mb < SB; ++mb) store_block(A.H2, g0, mb, h2[t][2 * mb], h2[t][2 * mb + 1], id, lane);
+#pragma unroll
+            for (int mb = 0; mb < SB; ++mb) store_block(A.H3, g0, mb, h3[t][2 * mb], h3[t][2 * mb + 1], id, lane);
         }
         // loss and dz4: outputs 4 h + r in registers r = 0..3
         f32x16 dz4[SNT];
@@ -314,14 +371,9 @@ k_smooth_fwd_bwd(SmoothArgs A)
         // product with it), so the planes hold zeros there.
         // dh3 = W4^T dz4 (one k-step: outputs 0..7 in slots 0..3 of both halves)
         bf16x8 bh[SNT][SK], bl[SNT][SK];
-#pragma unroll
-        for (int t = 0; t < SNT; ++t) {
-            split_bf16x8(dz4[t], 0, bh[t][0], bl[t][0]);
-            const auto out = [h](int i) { return legs_khid(0, h, i); };   // outputs 4 h + i for i < 4
-            store_rows8(A.D4, LEGS_SMOOTH_OUT, gi[t] - i8, bh[t][0], out, i8, b1, psel);
-            store_rows8(A.D4 + LEGS_SMOOTH_OUT * A.Gp, LEGS_SMOOTH_OUT, gi[t] - i8, bl[t][0], out, i8, b1, psel);
-        }
         f32x16 dz[SNT][SB];
+#pragma unroll
+        for (int t = 0; t < SNT; ++t) split_bf16x8(dz4[t], 0, bh[t][0], bl[t][0]);
 #pragma unroll
         for (int mb = 0; mb < SB; ++mb) {
             const bf16x8 a = L.t4[mb * 64 + ln];
@@ -329,6 +381,15 @@ k_smooth_fwd_bwd(SmoothArgs A)
             for (int t = 0; t < SNT; ++t)
                 dz[t][mb] = legs_mfma(a, bl[t][0], legs_mfma(a, bh[t][0], (f32x16){}));
         }
+#pragma unroll
+        for (int t = 0; t < SNT; ++t)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const bf16x8 &f = p ? bl[t][0] : bh[t][0];
+                __bf16 *plane = A.D4 + p * LEGS_SMOOTH_OUT * A.Gp;
+                // outputs 4 h + i for i < 4: column n of the turned block is output n
+                store_narrow<LEGS_SMOOTH_OUT>(plane, (grp * SNT + t) * 32, f, id, lane, [](int n) { return n; });
+            }
         // ReLU gates from the stored activations (positive exactly where z > 0)
         auto gate = [&](const bf16x8 (&hf)[SNT][SK]) {
 #pragma unroll
@@ -346,14 +407,19 @@ k_smooth_fwd_bwd(SmoothArgs A)
                 for (int mb = 0; mb < SB; ++mb) {
                     split_bf16x8(dz[t][mb], 0, bh[t][2 * mb], bl[t][2 * mb]);
                     split_bf16x8(dz[t][mb], 8, bh[t][2 * mb + 1], bl[t][2 * mb + 1]);
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {   // rows legs_khid(2 mb + k, h, .)
-                        const int ks = 2 * mb + k;
-                        const auto row = [ks, h](int i) { return legs_khid(ks, h, i); };
-                        store_rows8(plane, SH, gi[t] - i8, bh[t][ks], row, i8, b1, psel);
-                        store_rows8(plane + SH * A.Gp, SH, gi[t] - i8, bl[t][ks], row, i8, b1, psel);
-                    }
                 }
+#pragma unroll
+            for (int t = 0; t < SNT; ++t)
+#pragma unroll
+                for (int mb = 0; mb < SB; ++mb) {
+                    const int64_t g0 = (grp * SNT + t) * 32;
+                    store_block(plane, g0, mb, bh[t][2 * mb], bh[t][2 * mb + 1], id, lane);
+                }
+#pragma unroll
+            for (int t = 0; t < SNT; ++t)
+#pragma unroll
+                for (int mb = 0; mb < SB; ++mb)
+                    store_block(plane + SH * A.Gp, (grp * SNT + t) * 32, mb, bl[t][2 * mb], bl[t][2 * mb + 1], id, lane);
             if (!T) return;
 #pragma unroll
             for (int mb = 0; mb < SB; ++mb) {
@@ -379,79 +445,154 @@ k_smooth_fwd_bwd(SmoothArgs A)
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, LEGS_WAVE);
-    if (lane == 0 && lsum != 0.0f) atomicAdd(A.loss, lsum);
+    if (lane == 0) s_loss[wave] = lsum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const float v = (s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3]);
+        if (v != 0.0f) atomicAdd(A.loss, v);
+    }
 }
 
-// dW[m][k] += sum_g (Dhi + Dlo)[m][g] B[k][g] over the Gaussians of this
-// workgroup's chunk, db[m] += sum_g (Dhi + Dlo)[m][g]. Layer (blockIdx.y):
-// 0: D1 x X (rows 0..8 = split coordinates, row 9 = ones) -> W1 [128][3], b1
-// 1: D2 x H1 -> W2, b2;  2: D3 x H2 -> W3, b3;  3: D4 (8 rows) x H3 -> W4, b4.
-constexpr int WG_CHUNK_G = 4096;
+// dW[m][k] += sum_g (Dhi + Dlo)[m][g] B[k][g], db[m] += sum_g (Dhi + Dlo)[m][g].
+// Three kinds of workgroups (blockIdx.y), of about 12.5 KB per 16 Gaussians each:
+// 0: D2 x H1 -> W2, b2;  1: D3 x H2 -> W3, b3;  2: D1 x X (rows 0..8 = split
+// coordinates, row 9 = ones) -> W1 [128][3], b1, and D4 (8 rows) x H3 -> W4, b4.
+// A wave owns whole products, all 16 blocks of a 128 x 128 one, for its steps of
+// 16 Gaussians, so that every fragment is read once (with a row block per wave,
+// B was read four times and the L2 was the limit), and has WG_AHEAD steps in
+// flight; the waves of a workgroup sum in LDS before the atomics.
+constexpr int WG_AHEAD = 3;
+
+// The 1 KB fragments of one step: DN of D hi and of D lo, BN of B; rows past a
+// plane's (DR, BR < 32) read its row 0 and count as zero.
+template <int DR, int BR>
+struct SmoothStep {
+    static constexpr int DN = (DR + 31) / 32, BN = (BR + 31) / 32;
+    bf16x8 hi[DN], lo[DN], b[BN];
+    __device__ __forceinline__ void load(const __bf16 *D, const __bf16 *B, int64_t Gp, int64_t g, int lane)
+    {
+        const int r = lane & 31, h = lane >> 5;
+        const int64_t gl = g + 8 * h;
+#pragma unroll
+        for (int k = 0; k < DN; ++k) {
+            const int64_t o = frag_at(gl, DR, DR >= 32 || r < DR ? 32 * k + r : 0);
+            hi[k] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(D + o));
+            lo[k] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(D + DR * Gp + o));
+        }
+#pragma unroll
+        for (int k = 0; k < BN; ++k)
+            b[k] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(B + frag_at(gl, BR, BR >= 32 || r < BR ? 32 * k + r : 0)));
+    }
+    __device__ __forceinline__ void add(f32x16 (&acc)[DN][BN], float (&db)[DN], bool bias, int lane)
+    {
+        const int r = lane & 31;
+        const bf16x8 zero = {};
+        if constexpr (DR < 32) {
+            hi[0] = r < DR ? hi[0] : zero;
+            lo[0] = r < DR ? lo[0] : zero;
+        }
+        if constexpr (BR < 32) b[0] = r < BR ? b[0] : zero;
+#pragma unroll
+        for (int m = 0; m < DN; ++m)
+#pragma unroll
+            for (int k = 0; k < BN; ++k) acc[m][k] = legs_mfma(lo[m], b[k], legs_mfma(hi[m], b[k], acc[m][k]));
+        if (bias) {
+#pragma unroll
+            for (int m = 0; m < DN; ++m)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) db[m] += (float)hi[m][e] + (float)lo[m][e];
+        }
+    }
+};
+
+// Sum of z over the workgroup's waves, in wave 0's order (plain reads and
+// writes of LDS, one wave after the other).
+template <int N>
+__device__ __forceinline__ void block_sum(f32x16 (&z)[N], float4 *lds, int lane, int wave)
+{
+    for (int w = 3; w >= 0; --w) {
+        if (wave == w) {
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float4 &x = lds[(n * 4 + q) * LEGS_WAVE + lane];
+                    float4 v = make_float4(z[n][4 * q], z[n][4 * q + 1], z[n][4 * q + 2], z[n][4 * q + 3]);
+                    if (w < 3) {
+                        const float4 y = x;
+                        v = make_float4(v.x + y.x, v.y + y.y, v.z + y.z, v.w + y.w);
+                    }
+                    x = v;
+                }
+        }
+        __syncthreads();
+    }
+}
+
+// One product over the workgroup's steps; W(row, col, v) takes its elements.
+template <int DR, int BR, bool BIAS, typename W>
+__device__ __forceinline__ void smooth_product(const SmoothArgs &A, const __bf16 *D, const __bf16 *B, float4 *lds,
+                                               float *__restrict__ db_out, W add)
+{
+    using Step = SmoothStep<DR, BR>;
+    const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
+    const int64_t steps = A.Gp / 16, stride = (int64_t)gridDim.x * 4;
+    const int64_t s0 = (int64_t)blockIdx.x * 4 + wave;
+    f32x16 acc[Step::DN][Step::BN] = {};
+    float db[Step::DN] = {};
+    Step ring[WG_AHEAD];
+        auto at = [&](int64_t s) { return 16 * min(s, steps - 1); };
+#pragma unroll
+    for (int k = 0; k < WG_AHEAD; ++k) ring[k].load(D, B, A.Gp, at(s0 + k * stride), lane);
+#pragma unroll 1
+    for (int64_t s = s0; s < steps; s += WG_AHEAD * stride) {
+#pragma unroll
+        for (int k = 0; k < WG_AHEAD; ++k) {
+            if (s + k * stride < steps) ring[k].add(acc, db, BIAS, lane);
+            ring[k].load(D, B, A.Gp, at(s + (k + WG_AHEAD) * stride), lane);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (BIAS) {
+#pragma unroll
+        for (int m = 0; m < Step::DN; ++m) {
+            const float v = db[m] + __shfl_xor(db[m], 32, LEGS_WAVE);
+            if (h == 0 && 32 * m + lane < DR && v != 0.0f) atomicAdd(db_out + 32 * m + lane, v);
+        }
+    }
+    block_sum(reinterpret_cast<f32x16(&)[Step::DN * Step::BN]>(acc), lds, lane, wave);
+    for (int n = wave; n < Step::DN * Step::BN; n += 4)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 x = lds[(n * 4 + q) * LEGS_WAVE + lane];
+            const float v[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int row = 32 * (n / Step::BN) + legs_drow(4 * q + u, h), col = 32 * (n % Step::BN) + (lane & 31);
+                if (row < DR && col < BR && v[u] != 0.0f) add(row, col, v[u]);
+            }
+        }
+    __syncthreads();
+}
 
 __global__ void __launch_bounds__(256)
 k_smooth_wgrad(SmoothArgs A, float *__restrict__ grad)
 {
-    const int layer = blockIdx.y;
-    const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
-    const __bf16 *Dh = layer == 0 ? A.D1 : layer == 1 ? A.D2 : layer == 2 ? A.D3 : A.D4;
-    const __bf16 *Bp = layer == 0 ? A.X : layer == 1 ? A.H1 : layer == 2 ? A.H2 : A.H3;
-    const int M = layer == 3 ? LEGS_SMOOTH_OUT : SH;          // rows of D
-    const int Kb = layer == 0 ? 16 : SH;                      // rows of B
-    const int MB = (M + 31) / 32, NB = (Kb + 31) / 32;
-    const __bf16 *Dl = Dh + (int64_t)M * A.Gp;                 // lo parts after the hi plane
-    // wave w owns the 32 rows of block w of D against every block of B, so
-    // each fragment of D is loaded once and each of B once per wave
-    if (wave >= MB) return;
-    const int mb = wave, m = 32 * mb + (lane & 31);
-    const int64_t g0 = (int64_t)blockIdx.x * WG_CHUNK_G;
-    const int64_t g1 = min(g0 + (int64_t)WG_CHUNK_G, A.Gp);
-    const bool mrow = m < M;
-    bool krow[4];
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) krow[nb] = nb < NB && 32 * nb + (lane & 31) < Kb;
-    f32x16 acc[4] = {};
-    float dbs = 0.0f;
-#pragma unroll 2
-    for (int64_t g = g0; g < g1; g += 16) {
-        // this lane's operands: Gaussians g + 8 h .. + 7 (16-byte fragments)
-        const int64_t gl = g + 8 * h;
-        bf16x8 ah = {}, al = {}, b[4];
-        if (mrow) {                 // dz as hi + lo bf16 parts (16 significant bits)
-            ah = *reinterpret_cast<const bf16x8 *>(Dh + frag_at(gl, M, m));
-            al = *reinterpret_cast<const bf16x8 *>(Dl + frag_at(gl, M, m));
-        }
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-            b[nb] = krow[nb] ? *reinterpret_cast<const bf16x8 *>(Bp + frag_at(gl, Kb, 32 * nb + (lane & 31)))
-                             : (bf16x8){};
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-            if (nb < NB) acc[nb] = legs_mfma(al, b[nb], legs_mfma(ah, b[nb], acc[nb]));
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dbs += (float)ah[e] + (float)al[e];
-    }
-    if (layer != 0) {                                           // bias gradient of rows m
-        dbs += __shfl_xor(dbs, 32, LEGS_WAVE);
-        float *db = grad + (layer == 1 ? LEGS_SMOOTH_OFF_B2 : layer == 2 ? LEGS_SMOOTH_OFF_B3 : LEGS_SMOOTH_OFF_B4);
-        if (h == 0 && mrow && dbs != 0.0f) atomicAdd(db + m, dbs);
-    }
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-        if (nb >= NB) continue;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 32 * mb + legs_drow(r, h);
-            const int col = 32 * nb + (lane & 31);
-            const float v = acc[nb][r];
-            if (row >= M || col >= Kb || v == 0.0f) continue;
-            if (layer == 0) {
-                if (col < 9) atomicAdd(grad + LEGS_SMOOTH_OFF_W1 + row * 3 + col % 3, v);
-                else if (col == 9) atomicAdd(grad + LEGS_SMOOTH_OFF_B1 + row, v);
-            } else {
-                const int off = layer == 1 ? LEGS_SMOOTH_OFF_W2 : layer == 2 ? LEGS_SMOOTH_OFF_W3 : LEGS_SMOOTH_OFF_W4;
-                atomicAdd(grad + off + row * SH + col, v);
-            }
-        }
+    __shared__ float4 lds[SB * SB * 4 * LEGS_WAVE];
+    if (blockIdx.y < 2) {
+        const int off = blockIdx.y ? LEGS_SMOOTH_OFF_W3 : LEGS_SMOOTH_OFF_W2;
+        smooth_product<SH, SH, true>(A, blockIdx.y ? A.D3 : A.D2, blockIdx.y ? A.H2 : A.H1, lds,
+                                     grad + (blockIdx.y ? LEGS_SMOOTH_OFF_B3 : LEGS_SMOOTH_OFF_B2),
+                                     [=](int row, int col, float v) { atomicAdd(grad + off + row * SH + col, v); });
+    } else {
+        smooth_product<SH, 16, false>(A, A.D1, A.X, lds, nullptr, [=](int row, int col, float v) {
+            if (col < 9) atomicAdd(grad + LEGS_SMOOTH_OFF_W1 + row * 3 + col % 3, v);
+            else if (col == 9) atomicAdd(grad + LEGS_SMOOTH_OFF_B1 + row, v);
+        });
+        smooth_product<LEGS_SMOOTH_OUT, SH, true>(A, A.D4, A.H3, lds, grad + LEGS_SMOOTH_OFF_B4,
+                                                  [=](int row, int col, float v) {
+                                                      atomicAdd(grad + LEGS_SMOOTH_OFF_W4 + row * SH + col, v);
+                                                  });
     }
 }
 
@@ -512,7 +653,10 @@ int32_t legs_launch_smooth(legs_ctx *ctx, const float *mean, const float *channe
     int64_t blocks = (Lw.Gp + 32 * SNT * 4 - 1) / (32 * SNT * 4);
     if (blocks > ctx->num_cus) blocks = ctx->num_cus;
     hipLaunchKernelGGL(k_smooth_fwd_bwd, dim3((unsigned)blocks), dim3(256), 0, s, A);
-    const dim3 gw((unsigned)((Lw.Gp + WG_CHUNK_G - 1) / WG_CHUNK_G), 4);
+    // one workgroup per CU over the three kinds
+    int64_t gx = (Lw.Gp / 16 + 3) / 4;
+    if (gx > ctx->num_cus / 3) gx = ctx->num_cus / 3 > 0 ? ctx->num_cus / 3 : 1;
+    const dim3 gw((unsigned)gx, 3);
     hipLaunchKernelGGL(k_smooth_wgrad, gw, dim3(256), 0, s, A, grad);
     LEGS_CHECK_LAUNCH(ctx);
     return LEGS_OK;

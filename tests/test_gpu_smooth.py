@@ -137,3 +137,37 @@ def test_smoothing_matches_oracle(ctx, n):
             e = (e @ np.abs(Wb[l])) * gate + 3e-5 * (dz @ np.abs(Wb[l])) * gate
             dz = (dz @ np.abs(Wb[l])) * gate
     note(f"n={n}: loss {loss.item():.6g} vs {lam * r['loss']:.6g}, activations off the oracle's by rounding: {n_amb}")
+
+
+@pytest.mark.parametrize("n", [1, 31, 64, 65, 4 * 64 * 3 + 1, 65_537])
+def test_smoothing_sizes(ctx, n):
+    """Tiles, wave groups and steps that are not whole; fewer steps than waves."""
+    test_smoothing_matches_oracle(ctx, n)
+
+
+@pytest.mark.parametrize("far", [np.inf, 3e38, np.nan])
+def test_smoothing_keeps_infinities_in_their_rows(ctx, far):
+    """A Gaussian at infinity (or whose activations overflow): the planes of its
+    neighbours in the tile keep their values, and its own are the same in every
+    place of a tile."""
+    from paper_2311_18482_amd import decode as DEC
+    n, C = 128, 12
+    rng = np.random.default_rng(7)
+    pos = rng.uniform(-4, 4, (n, 3)).astype(np.float32)
+    ws, bs = synth.mlp_init((3, 128, 128, 128, 8), 181)
+    params = torch.cat([torch.from_numpy(np.concatenate([W.reshape(-1), b])) for W, b in zip(ws, bs)]).cuda()
+    chans = torch.from_numpy(rng.normal(0, 0.3, (n, C)).astype(np.float32)).cuda()
+
+    def run(p):
+        w = DEC.smooth_loss_grad(ctx, torch.from_numpy(p).cuda(), chans, 3, 11, params, torch.zeros_like(params),
+                                 torch.zeros_like(chans), torch.zeros(1, device="cuda"))
+        torch.cuda.synchronize()
+        return planes(w, n, 128)
+
+    want = run(pos)
+    pos[37] = (far, 1.0, 2.0)
+    got, same = run(pos), run(np.tile(pos[37], (n, 1)))
+    others = np.arange(n) != 37
+    for a, b, c in zip(got, want, same):
+        assert np.array_equal(a[others], b[others])
+        assert np.array_equal(c, np.tile(a[37], (n, 1)), equal_nan=True)
