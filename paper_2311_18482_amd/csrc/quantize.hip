@@ -37,7 +37,7 @@
 //                    the weight gradient's MFMA operand order (one 16-byte
 //                    fragment per lane after an 8 x 8 lane transpose), and the
 //                    sums over i of dL/dD_ij cos_ij. Reading 1 GB back takes
-//                    295 us where a second pass over the features took 876.
+//                    274 us where a second pass over the features took 876.
 //  k_quant_wgrad     sum_i W_ij F_ic / |F_i| for every code j and dimension c:
 //                    FP16 MFMA with the features as the contraction (the
 //                    weight fragments 1 KB contiguous per wave), the unit
@@ -58,6 +58,7 @@
 namespace {
 
 typedef legs_f32x16 f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 
 constexpr int QCH = 128;           // dimensions per chunk
@@ -169,7 +170,7 @@ struct QuantArgs {
     uint32_t *counts;           // [N]
     float *psum;                // [N] sum of softmax over features
     double *lsum;               // [1] cosine-loss sum
-    float4 *cos;                // [Kp / 32][2 parts][N / 8][64 lanes] cosines (codes 8 q + 4 h .. + 3 of feature l % 32)
+    f32x4 *cos;                 // [Kp / 32][2 parts][N / 8][64 lanes] cosines (codes 8 q + 4 h .. + 3 of feature l % 32)
     float *invF;                // [2][Kp] 1 / |F_i| of both parts (0 past K)
     float *col;                 // [2][N] sum_i dL/dD_ij cos_ij (lambda dL/dD for DINO)
 };
@@ -355,14 +356,13 @@ k_quant_pass(QuantArgs A)
             // distance, argmax (first maximum)
             float best = -INFINITY;
             int bidx = 0x7fffffff;
-            float4 *pc = KEEP ? A.cos + (i >> 5) * (N / 4 * LEGS_WAVE) + lane : nullptr;
+            f32x4 *pc = KEEP ? A.cos + (i >> 5) * (N / 4 * LEGS_WAVE) + lane : nullptr;
 #pragma unroll
             for (int mb = 0; mb < KB; ++mb)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    float e[4];
-                    if (KEEP)
-                        pc[(4 * mb + q) * LEGS_WAVE] = make_float4(D[mb][4 * q], D[mb][4 * q + 1], D[mb][4 * q + 2], D[mb][4 * q + 3]);
+                    f32x4 e;
+                    const f32x4 c = {D[mb][4 * q], D[mb][4 * q + 1], D[mb][4 * q + 2], D[mb][4 * q + 3]};
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         const int r = 4 * q + u;
@@ -372,7 +372,10 @@ k_quant_pass(QuantArgs A)
                         // (the half's offset 4 h, the same for every code, is added below)
                         if (Dv > best) { best = Dv; bidx = 32 * mb + legs_drow(r, 0); }
                     }
-                    if (KEEP) pc[(N / 8 + 4 * mb + q) * LEGS_WAVE] = make_float4(e[0], e[1], e[2], e[3]);
+                    if (KEEP) {              // past the caches: a call's cosines outgrow them
+                        __builtin_nontemporal_store(c, pc + (4 * mb + q) * LEGS_WAVE);
+                        __builtin_nontemporal_store(e, pc + (N / 8 + 4 * mb + q) * LEGS_WAVE);
+                    }
                 }
             if (best > -INFINITY) bidx += 4 * h;
             {
@@ -444,13 +447,17 @@ k_quant_weights(QuantArgs A)
     for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < A.Kp / 32; tile += (int64_t)gridDim.x * 4) {
         const int64_t i = 32 * tile + (lane & 31);
         const bool vt = i < A.K;
-        const float4 *pc = A.cos + tile * (N / 4 * LEGS_WAVE) + lane;
+        const f32x4 *pc = A.cos + tile * (N / 4 * LEGS_WAVE) + lane;
         float c[KB * 16], e[KB * 16];
 #pragma unroll
         for (int k = 0; k < KB * 4; ++k) {
-            const float4 x = pc[k * LEGS_WAVE], y = pc[(N / 8 + k) * LEGS_WAVE];
-            c[4 * k] = x.x, c[4 * k + 1] = x.y, c[4 * k + 2] = x.z, c[4 * k + 3] = x.w;
-            e[4 * k] = y.x, e[4 * k + 1] = y.y, e[4 * k + 2] = y.z, e[4 * k + 3] = y.w;
+            const f32x4 x = __builtin_nontemporal_load(pc + k * LEGS_WAVE);
+            const f32x4 y = __builtin_nontemporal_load(pc + (N / 8 + k) * LEGS_WAVE);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                c[4 * k + u] = x[u];
+                e[4 * k + u] = y[u];
+            }
         }
         const int m = vt ? A.index[i] : -1;
         float best = -INFINITY, sum = 0.0f, rs = 0.0f;
@@ -712,7 +719,7 @@ int32_t legs_launch_quantize(legs_ctx *ctx, const uint16_t *feat, int64_t K, int
     A.counts = counts;
     A.psum = reinterpret_cast<float *>(ws + Lw.psum);
     A.lsum = reinterpret_cast<double *>(ws + Lw.lsum);
-    A.cos = reinterpret_cast<float4 *>(ws + Lw.cos);
+    A.cos = reinterpret_cast<f32x4 *>(ws + Lw.cos);
     A.col = reinterpret_cast<float *>(ws + Lw.col);
     A.invF = reinterpret_cast<float *>(ws + Lw.invF);
     // psum, col and lsum are contiguous (up to padding) in the workspace
