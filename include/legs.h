@@ -13,7 +13,8 @@
  *  - Every pointer argument named *_dev or documented as "device" is device
  *    memory of the context's GPU, allocated and owned by the caller. The
  *    library never allocates on the calls below (the context owns nothing but
- *    its error text).
+ *    its error text; the first legs_create of a process also allocates one
+ *    page of pinned host memory).
  *  - All work is enqueued on `stream` (a hipStream_t; NULL = legacy default
  *    stream) and is asynchronous unless stated otherwise.
  *  - Return codes: LEGS_OK, or a negative LEGS_ERR_* code. On error nothing is

@@ -45,7 +45,58 @@ int32_t scratch_setup(legs_ctx *ctx)
     return LEGS_OK;
 }
 
+// Words of pinned host memory that kernels report to a waiting host through,
+// one cache line each; allocated once per process.
+constexpr int kHostWords = 64, kHostWordStride = 8;
+uint64_t *g_host_words, *g_host_words_dev;
+std::atomic<uint64_t> g_host_words_free{0};
+
+// (Relaxed: a context may be created while the thread captures a stream. Without
+// the page the calls that would wait for a word copy instead.)
+void host_words_setup()
+{
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    if (g_host_words) return;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    void *p = nullptr, *d = nullptr;
+    if (hipHostMalloc(&p, kHostWords * kHostWordStride * 8,
+                      hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+    } else if (hipHostGetDevicePointer(&d, p, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipHostFree(p);
+        p = nullptr;
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!p) return;
+    g_host_words_dev = static_cast<uint64_t *>(d);
+    g_host_words = static_cast<uint64_t *>(p);
+    g_host_words_free.store(~0ull, std::memory_order_release);
+}
+
 } // namespace
+
+uint64_t *legs_host_word_acquire(uint64_t **device)
+{
+    uint64_t f = g_host_words_free.load(std::memory_order_acquire);
+    while (f) {
+        if (!g_host_words_free.compare_exchange_weak(f, f & (f - 1), std::memory_order_acquire)) continue;
+        const int i = __builtin_ctzll(f) * kHostWordStride;
+        *device = g_host_words_dev + i;
+        return g_host_words + i;
+    }
+    return nullptr;
+}
+
+void legs_host_word_release(uint64_t *word)
+{
+    g_host_words_free.fetch_or(1ull << ((word - g_host_words) / kHostWordStride), std::memory_order_release);
+}
 
 int32_t legs_set_error(legs_ctx *ctx, int32_t code, const char *fmt, ...)
 {
@@ -141,6 +192,7 @@ int32_t legs_create(int32_t device, legs_ctx **out)
     c->device = device;
     c->num_cus = prop.multiProcessorCount;
     c->err[0] = 0;
+    host_words_setup();
     const int32_t rc = scratch_setup(c);
     if (rc != LEGS_OK) {
         fprintf(stderr, "legs_create: %s\n", c->err);

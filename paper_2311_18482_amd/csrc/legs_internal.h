@@ -26,6 +26,11 @@ int32_t legs_set_error(legs_ctx *ctx, int32_t code, const char *fmt, ...);
     } while (0)
 #define LEGS_CHECK_LAUNCH(ctx) LEGS_CHECK_HIP(ctx, hipGetLastError())
 
+// A zero-able 64-bit word of pinned host memory and its device address, from a
+// page that legs_create allocates once per process (NULL: all 64 are in use).
+uint64_t *legs_host_word_acquire(uint64_t **device);
+void legs_host_word_release(uint64_t *word);
+
 // ---- device helpers ---------------------------------------------------------
 
 __device__ __forceinline__ uint64_t legs_ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }

@@ -24,6 +24,8 @@
 // partitions (partition ids handed out by an atomic counter in launch order,
 // so every partition waited on belongs to a running workgroup) or, for the
 // segment passes, from per-segment digit counts scanned beforehand.
+#include <thread>
+
 #include "legs_internal.h"
 
 namespace {
@@ -677,15 +679,20 @@ k_seg_scan(const uint32_t *__restrict__ seg_hist, int nseg, const uint32_t *__re
 // counts the digit histograms of its npass passes into hist (cleared before):
 // each workgroup takes chunks of ORDER_RUN rows of ORDER_THREADS G-views,
 // loads a chunk's inputs at once, counts in LDS (hist_add for the clustered
-// digits) and flushes its counts once.
+// digits) and flushes its counts once. With `slot` the last workgroup to finish
+// writes the instance total + 1 there (a word of host memory that the caller
+// waits for while the depth sort runs; gcount[1] and [2], cleared before, are the
+// running total and the workgroups done).
 constexpr int ORDER_THREADS = 1024, ORDER_RUN = 4;   // measured: 4 waves per SIMD beat 1 (256 x 16)
 
 __global__ void __launch_bounds__(ORDER_THREADS)
 k_order_keys(const uint32_t *__restrict__ ntiles, const float *__restrict__ depth, int64_t n,
              int64_t G, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
-             uint64_t *__restrict__ gcount, int npass, uint32_t *__restrict__ hist, int vbits)
+             uint64_t *__restrict__ gcount, int npass, uint32_t *__restrict__ hist, int vbits,
+             uint64_t *slot)
 {
     constexpr int NT = ORDER_THREADS, RUN = ORDER_RUN;
+    uint64_t tiles = 0;
     __shared__ uint32_t s_h[LEGS_SORT_MAX_PASSES][256];
     for (int i = threadIdx.x; i < LEGS_SORT_MAX_PASSES * 256; i += NT) (&s_h[0][0])[i] = 0;
     __syncthreads();
@@ -700,6 +707,7 @@ k_order_keys(const uint32_t *__restrict__ ntiles, const float *__restrict__ dept
             const int64_t gv = base + NT * i + threadIdx.x;
             nt[i] = gv < G ? ntiles[gv] : 0u;
             dp[i] = gv < G ? depth[gv] : 0.0f;
+            tiles += nt[i];
         }
 #pragma unroll
         for (int i = 0; i < RUN; ++i) {
@@ -728,6 +736,23 @@ k_order_keys(const uint32_t *__restrict__ ntiles, const float *__restrict__ dept
     for (int i = threadIdx.x; i < npass * 256; i += NT) {
         const uint32_t c = (&s_h[0][0])[i];
         if (c) atomicAdd(&hist[i], c);
+    }
+    if (!slot) return;
+    __shared__ unsigned long long s_tiles;
+    if (threadIdx.x == 0) s_tiles = 0;
+    __syncthreads();
+#pragma unroll
+    for (int off = LEGS_WAVE / 2; off > 0; off >>= 1) tiles += __shfl_xor((unsigned long long)tiles, off, LEGS_WAVE);
+    if (legs_lane() == 0) atomicAdd(&s_tiles, (unsigned long long)tiles);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long *c = reinterpret_cast<unsigned long long *>(gcount);
+        atomicAdd(c + 1, s_tiles);
+        __threadfence();
+        if (atomicAdd(c + 2, 1ull) + 1 == gridDim.x) {
+            __threadfence();
+            __hip_atomic_store(slot, (uint64_t)atomicAdd(c + 1, 0ull) + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
 }
 
@@ -1088,6 +1113,7 @@ struct SuperViewArgs {
     uint64_t *cut, *vrange;
     uint32_t *clear;
     int64_t nclear;
+    uint64_t *totals;       // [2] the running instance total and its workgroups (k_order_keys)
 };
 
 // The share of workgroup `block` of `blocks`.
@@ -1099,6 +1125,7 @@ __device__ __forceinline__ void super_views_part(const SuperViewArgs &a, int64_t
     for (int i = threadIdx.x; i < 2 * a.n_views; i += 256) a.vrange[i] = 0u;
     if (threadIdx.x < 16) a.counters[threadIdx.x] = 0u;
     if (threadIdx.x < 2) a.cut[threadIdx.x] = ~0ull;
+    if (threadIdx.x < 2) a.totals[threadIdx.x] = 0ull;
     if (threadIdx.x != 0) return;
     const int n_views = a.n_views;
     const legs_view *views = a.views;
@@ -1551,7 +1578,7 @@ OrderLayout order_layout(int64_t n, int32_t n_views)
     L.offsets = o; o = align256(o + 8 * (L.nbs + 1));
     L.cbcounts = o; o = align256(o + 8 * (L.nbs + 1));
     L.coffsets = o; o = align256(o + 8 * (L.nbs + 1));
-    L.gcount = o; o = align256(o + 8);
+    L.gcount = o; o = align256(o + 24);     // the sort's count, then k_order_keys' totals
     L.ccount = o; o = align256(o + 8);
     L.frecs = o; o = align256(o + 16 * L.G);
     L.crecs = o; o = align256(o + 16 * L.G);
@@ -1561,6 +1588,64 @@ OrderLayout order_layout(int64_t n, int32_t n_views)
     L.total = o;
     return L;
 }
+
+// A word of pinned host memory that a kernel of this call writes, taken from the
+// process's page of them for the duration of the call (none: all of them
+// are in use, or the stream is being captured, and the caller copies the count instead).
+class HostTotal {
+public:
+    HostTotal(bool wanted, hipStream_t s)
+    {
+        if (!wanted) return;
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        if (st != hipStreamCaptureStatusNone) return;
+        slot_ = legs_host_word_acquire(&device_);
+        if (slot_) __atomic_store_n(slot_, 0ull, __ATOMIC_RELEASE);
+    }
+    // a word that its kernel has not written yet is not given back
+    ~HostTotal()
+    {
+        if (slot_ && __atomic_load_n(slot_, __ATOMIC_ACQUIRE)) legs_host_word_release(slot_);
+    }
+    HostTotal(const HostTotal &) = delete;
+    HostTotal &operator=(const HostTotal &) = delete;
+    uint64_t *device() const { return device_; }
+    // The total, once it is there; false: no word, or the stream ended (or
+    // failed) without it.
+    bool wait(hipStream_t s, uint64_t *total)
+    {
+        if (!slot_) return false;
+        for (int i = 1;; ++i) {
+            const uint64_t v = __atomic_load_n(slot_, __ATOMIC_ACQUIRE);
+            if (v) {
+                *total = v - 1;
+                return true;
+            }
+            if (i % 4096) {
+                __builtin_ia32_pause();
+                continue;
+            }
+            const hipError_t e = hipStreamQuery(s);
+            if (e == hipErrorNotReady) {
+                (void)hipGetLastError();
+                std::this_thread::yield();
+                continue;
+            }
+            if (e != hipSuccess) return false;
+            const uint64_t u = __atomic_load_n(slot_, __ATOMIC_ACQUIRE);   // all done: written, if ever
+            if (!u) return false;
+            *total = u - 1;
+            return true;
+        }
+    }
+
+private:
+    uint64_t *slot_ = nullptr, *device_ = nullptr;
+};
 
 int bits_for(int64_t count)
 {
@@ -1591,6 +1676,10 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
     char *ord = static_cast<char *>(proj->order);
     OrderLayout OL;
     legs_view *sviews = nullptr;
+    // The instance total as soon as the keys are made: waiting for it while the
+    // depth sort runs, instead of for a copy behind it, takes 35 us out of a call
+    // (a render of 128 x 128 pixels 240 -> 207 us, of 1280 x 720 362 -> 330).
+    HostTotal total(!full && host_count && n > 0 && n_views > 0, s);
     if (!full) {
         // 1. depth order of every visible G-view: the four depth-digit passes of
         //    the key sort, run once per Gaussian instead of once per instance
@@ -1615,7 +1704,7 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
                                               : SortClearArgs{nullptr, 0, 0, nullptr, nullptr, nullptr, 0};
             const int64_t nclear = (int64_t)(S.scount - S.tcount) + total_tiles;
             const SuperViewArgs sa{views, n_views, sviews, S.desc, S.hist, S.counters, S.cut, vrange, S.tcount,
-                                   nclear};
+                                   nclear, gcount + 1};
             const int g0 = OL.G > 0 ? grid_for(ctx, GS.parts * 256 * gpass, 256, 8) : 1;
             const int g1 = grid_for(ctx, nclear, 256, 8);
             hipLaunchKernelGGL(k_bin_setup, dim3(g0 > g1 ? g0 : g1), dim3(256), 0, s, ca, sa);
@@ -1625,7 +1714,8 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
             const SortScratch GS = sort_scratch_at(ord + OL.sort, OL.G);
             hipLaunchKernelGGL(k_order_keys, dim3(grid_for(ctx, OL.G, ORDER_THREADS * ORDER_RUN, 4)),
                                dim3(ORDER_THREADS), 0, s,
-                               proj->ntiles, proj->depth, n, OL.G, ok0, ov0, gcount, gpass, GS.hist, vbits);
+                               proj->ntiles, proj->depth, n, OL.G, ok0, ov0, gcount, gpass, GS.hist, vbits,
+                               total.device());
             LEGS_CHECK_LAUNCH(ctx);
             const int32_t r = vbits > 0
                                   ? radix_passes(ctx, GS, ok0, nullptr, ok1, nullptr, gcount, OL.G, 0, gpass, true, s,
@@ -1658,13 +1748,17 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
     LEGS_CHECK_LAUNCH(ctx);
     if (host_count) {
         uint64_t tot = 0;
-        LEGS_CHECK_HIP(ctx, hipMemcpyAsync(&tot, bins->count, sizeof(tot), hipMemcpyDeviceToHost, s));
-        LEGS_CHECK_HIP(ctx, hipStreamSynchronize(s));
+        if (!total.wait(s, &tot)) {
+            LEGS_CHECK_HIP(ctx, hipMemcpyAsync(&tot, bins->count, sizeof(tot), hipMemcpyDeviceToHost, s));
+            LEGS_CHECK_HIP(ctx, hipStreamSynchronize(s));
+        }
         *host_count = (int64_t)tot;
-        if ((int64_t)tot > bins->capacity)
+        if ((int64_t)tot > bins->capacity) {
+            LEGS_CHECK_HIP(ctx, hipStreamSynchronize(s));     // the caller may free the buffers
             return legs_set_error(ctx, LEGS_ERR_CAPACITY,
                                   "legs_bin_sort: %lld instances exceed capacity %lld",
                                   (long long)tot, (long long)bins->capacity);
+        }
     }
     if (full) {
         // 2'. emission in Gaussian order, all eight digit passes over the

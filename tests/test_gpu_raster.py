@@ -406,6 +406,52 @@ def test_capacity_overflow_is_reported(R):
     assert bins.n_instances == cnt.value and bins.capacity >= cnt.value
 
 
+@pytest.mark.parametrize("n,views", [(1, 1), (255, 3), (4097, 2), (20_000, 5)])
+def test_instance_total_matches_full_sort(R, n, views):
+    """The total that the depth-first binning waits for (from the tile counts,
+    before the sort) against the full sort's and the device's."""
+    scene = synth.make_scene(n, 31, synth.VOL_CUBE, d_sem=0)
+    cams = synth.cameras_sphere(views, 32, 8.0, (160, 120))
+    tot = []
+    for full in (False, True):
+        o = R.opts(full_sort=full)
+        _, _, _, bins, _, _, _ = run_forward(R, scene, cams, o)
+        tot.append(int(bins.n_instances))
+        assert int(bins.count.cpu()[0]) == tot[-1]
+    assert tot[0] == tot[1]
+
+
+def test_instance_totals_from_several_threads(R):
+    """Calls on streams of their own wait for their own totals."""
+    import threading
+    scenes = [synth.make_scene(2000 + 700 * k, 50 + k, synth.VOL_C1, d_sem=0) for k in range(6)]
+    cams = [synth.camera_front(160, 120, 150.0)]
+    want = [int(run_forward(R, s, cams, R.opts())[3].n_instances) for s in scenes]
+    got, errors = [[] for _ in scenes], []
+
+    def work(k):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                d = PT.to_dev(scenes[k])
+                torch.cuda.current_stream().synchronize()
+                rast = R.Rasterizer(cams, R.opts())
+                for _ in range(20):
+                    proj, bins, out, T, last = rast.forward(d["mean"], d["log_scale"], d["quat"], d["opacity_logit"],
+                                                            d["channels"])
+                    got[k].append(int(bins.n_instances))
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:          # reported by the test's own thread
+            errors.append((k, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(scenes))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    assert got == [[w] * 20 for w in want]
+
+
 def test_invalid_arguments(R):
     from paper_2311_18482_amd import _lib as L
     import ctypes as ct
