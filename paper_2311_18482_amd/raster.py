@@ -279,6 +279,17 @@ class Rasterizer:
         self._pool.append(bins)
 
 
+def _zero(tensors):
+    """Zeroes the tensors: together up to 2^26 elements, where launches count
+    (six gradients of 25,000 Gaussians 35 -> 15 us, of 1M 34 -> 21), beyond that
+    each by its own fill (1M Gaussians in 16 views: 99 us, together 117)."""
+    if sum(t.numel() for t in tensors) <= 1 << 26:
+        torch._foreach_zero_(tensors)
+    else:
+        for t in tensors:
+            t.zero_()
+
+
 class RasterizeFn(torch.autograd.Function):
     """out (planar, views concatenated), T_final = rasterize(...).
     Saves only the projected records, the tile lists, T_final and last; each
@@ -296,10 +307,13 @@ class RasterizeFn(torch.autograd.Function):
     def backward(fctx, d_out, d_T):
         mean, log_scale, quat, opacity_logit, channels, T, last = fctx.saved_tensors
         r = fctx.rast
-        grad2d, d_ch = render_backward(r.ctx, fctx.proj, fctx.bins, r.views, channels, r.o, T, last,
-                                       d_out)
-        g = project_backward(r.ctx, mean, log_scale, quat, opacity_logit, r.views, r.o, fctx.proj,
-                             grad2d)
+        g = dict(mean=torch.empty_like(mean), log_scale=torch.empty_like(log_scale), quat=torch.empty_like(quat),
+                 opacity_logit=torch.empty_like(opacity_logit))
+        grad2d = torch.empty((channels.shape[0] * r.views.n_views, 8), dtype=torch.float32, device=channels.device)
+        d_ch = torch.empty(channels.shape, dtype=torch.float32, device=channels.device)
+        _zero([grad2d, d_ch, *g.values()])
+        render_backward(r.ctx, fctx.proj, fctx.bins, r.views, channels, r.o, T, last, d_out, grad2d, d_ch)
+        project_backward(r.ctx, mean, log_scale, quat, opacity_logit, r.views, r.o, fctx.proj, grad2d, g)
         # the lists are no longer read after the kernels enqueued above (same stream)
         r.release(fctx.bins)
         fctx.bins = None
