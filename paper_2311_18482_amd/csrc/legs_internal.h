@@ -111,7 +111,6 @@ legs_sort_layout legs_sort_layout_for(int64_t capacity, int64_t total_tiles = 0)
 #define LEGS_SORT_MAX_PASSES 8
 #define LEGS_TILE_CHUNKS 256
 #define LEGS_SEG_MAX 1024
-#define LEGS_COMPACT_UNIT 256
 // counter slots (u32) in the sort scratch's counter block: 0..15 sort passes
 #define LEGS_BLEND_COUNTER_FWD 32
 #define LEGS_BLEND_COUNTER_BWD 33

@@ -759,8 +759,6 @@ k_order_keys(const uint32_t *__restrict__ ntiles, const float *__restrict__ dept
 // Super-tile edge in tiles: 8 x 4 tiles, one bit each of a 32-bit mask.
 constexpr int SX = 8, SY = 4, SUPER_TILES = SX * SY;
 static_assert(SUPER_TILES == 32, "one mask bit per tile of a super-tile");
-// Entries of the coarse lists per unit of the compaction (one wave each).
-constexpr int UNIT = LEGS_COMPACT_UNIT;
 
 // Tile and super-tile records and the per-view position ranges of the
 // depth-ordered G-views, and the tile and super-tile instance counts of each
@@ -1061,14 +1059,14 @@ __device__ __forceinline__ int64_t list_cell(int64_t t, const uint32_t *__restri
 // List ranges [start, start + count) of every cell, one workgroup per grid:
 // grid 0's cells in order, grid 1's in list order (list_cell) with the digit
 // histograms of the coarse passes; a third workgroup numbers the units of the
-// super-tile lists, ceil(count / UNIT) per super-tile in id order (uoff[T] =
+// super-tile lists, ceil(count / unit) per super-tile in id order (uoff[T] =
 // their number).
 __global__ void __launch_bounds__(1024)
-k_count_lists(int64_t T, CountGrid g0, CountGrid g1, uint32_t *__restrict__ uoff)
+k_count_lists(int64_t T, CountGrid g0, CountGrid g1, uint32_t *__restrict__ uoff, int unit)
 {
     if (blockIdx.x == 2) {
         const uint32_t t = scan_rounds<uint32_t>(
-            T, [&](int64_t c) { return (g1.count[c] + UNIT - 1) / UNIT; },
+            T, [&](int64_t c) { return (g1.count[c] + unit - 1) / unit; },
             [&](int64_t c, uint32_t e, uint32_t) { uoff[c] = e; });
         if (threadIdx.x == 0) uoff[T] = t;
         return;
@@ -1183,7 +1181,7 @@ struct UnitCtx {
 __device__ __forceinline__ UnitCtx unit_ctx(uint32_t u, const uint32_t *__restrict__ uoff, int64_t n,
                                             const uint32_t *__restrict__ cranges,
                                             const legs_view *__restrict__ sviews,
-                                            const legs_view *__restrict__ views, int n_views)
+                                            const legs_view *__restrict__ views, int n_views, int unit)
 {
     int64_t lo = 0, hi = n - 1;   // the last super-tile whose first unit is <= u
     while (lo < hi) {
@@ -1197,9 +1195,9 @@ __device__ __forceinline__ UnitCtx unit_ctx(uint32_t u, const uint32_t *__restri
     UnitCtx c;
     c.ty0 = (local / stx) * SY;
     c.tx0 = (local - (local / stx) * stx) * SX;
-    c.e0 = cranges[2 * st] + (u - uoff[st]) * UNIT;
+    c.e0 = cranges[2 * st] + (u - uoff[st]) * unit;
     const uint32_t end = cranges[2 * st + 1];
-    c.e1 = c.e0 + UNIT < end ? c.e0 + UNIT : end;
+    c.e1 = c.e0 + unit < end ? c.e0 + unit : end;
     c.tiles_x = views[v].tiles_x;
     c.tiles_y = views[v].tiles_y;
     c.toff = views[v].tile_offset;
@@ -1211,11 +1209,11 @@ __device__ __forceinline__ UnitCtx unit_ctx(uint32_t u, const uint32_t *__restri
 __global__ void __launch_bounds__(256)
 k_unit_desc(const uint32_t *__restrict__ uoff, int64_t n, const uint32_t *__restrict__ cranges,
             const legs_view *__restrict__ sviews, const legs_view *__restrict__ views, int n_views,
-            UnitCtx *__restrict__ udesc)
+            int unit, UnitCtx *__restrict__ udesc)
 {
     const uint32_t nunits = uoff[n];
     for (uint32_t u = blockIdx.x * 256 + threadIdx.x; u < nunits; u += gridDim.x * 256)
-        udesc[u] = unit_ctx(u, uoff, n, cranges, sviews, views, n_views);
+        udesc[u] = unit_ctx(u, uoff, n, cranges, sviews, views, n_views, unit);
 }
 
 // Tiles of the super-tile at (tx0, ty0) that the record's rectangle covers:
@@ -1345,6 +1343,7 @@ k_compact_scan(const uint32_t *__restrict__ uoff, int64_t n, const legs_view *__
 // depth) pairs are placed in rank order in an LDS row of the wave, which is
 // then stored as one contiguous run of the tile's list with all lanes (ids,
 // and the keys unless keys is NULL). Four tiles are staged per LDS round trip.
+template <int UNIT>
 __global__ void __launch_bounds__(256)
 k_compact_write(const uint32_t *__restrict__ clist0, const uint32_t *__restrict__ clist1,
                 const uint32_t *__restrict__ desc, const uint32_t *__restrict__ uoff, int64_t n,
@@ -1441,6 +1440,11 @@ k_ranges(const uint64_t *__restrict__ keys, const uint64_t *__restrict__ count, 
 
 } // namespace
 
+// Entries of the coarse lists per unit of the compaction (one wave each): half
+// as many where that many more waves fill the chip (binning of 10k Gaussians 120
+// -> 114 us, of 300k 183 -> 178, of 1M in one view the same, in three 490 -> 500).
+static int compact_unit(int64_t capacity) { return capacity <= (1 << 23) ? 128 : 256; }
+
 legs_sort_layout legs_sort_layout_for(int64_t capacity, int64_t total_tiles)
 {
     auto up = [](int64_t x) { return (x + 255) & ~(int64_t)255; };
@@ -1453,7 +1457,7 @@ legs_sort_layout legs_sort_layout_for(int64_t capacity, int64_t total_tiles)
     int64_t o = up(L.status_off + 8 * (int64_t)LEGS_SORT_MAX_PASSES * L.parts * 256);
     const int64_t T = total_tiles > 0 ? total_tiles : 0;   // the G-view sort needs none of these
     L.ccap = T > 0 ? capacity + T : 0;
-    const int64_t units = T > 0 ? L.ccap / LEGS_COMPACT_UNIT + T : 0;
+    const int64_t units = T > 0 ? L.ccap / compact_unit(capacity) + T : 0;
     L.tcount_off = o; o = up(o + 4 * T);
     L.scount_off = o; o = up(o + 4 * T);     // right after tcount: both are cleared at once
     L.cranges_off = o; o = up(o + 8 * T);
@@ -1792,8 +1796,11 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
     const GRec *crecs = reinterpret_cast<const GRec *>(ord + OL.crecs);
     const uint64_t *vrange = reinterpret_cast<const uint64_t *>(ord + OL.vrange);
     const int64_t T = total_tiles;
+    const int unit = compact_unit(bins->capacity);
     // enough workgroups per view to spread the G-views, at most LEGS_TILE_CHUNKS
-    int nch = (int)(((OL.G / (n_views > 0 ? n_views : 1)) + 4095) / 4096);
+    // (two position blocks each: with sixteen, the binning of 10k to 60k Gaussians
+    // takes 9 to 15 us longer)
+    int nch = (int)(((OL.G / (n_views > 0 ? n_views : 1)) + 511) / 512);
     nch = nch < 1 ? 1 : (nch > LEGS_TILE_CHUNKS ? LEGS_TILE_CHUNKS : nch);
 
     // 2. per-cell counts of the tile stream (cut at the capacity) and of the
@@ -1809,7 +1816,7 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
     hipLaunchKernelGGL(k_count_merge, dim3((unsigned)((2 * T + 255) / 256), 32), dim3(256), 0, s, nch, T, n_views,
                        cg0, cg1);
     hipLaunchKernelGGL(k_count_prefix, dim3((unsigned)n_views, 2), dim3(1024), 0, s, cg0, cg1);
-    hipLaunchKernelGGL(k_count_lists, dim3(3), dim3(1024), 0, s, T, cg0, cg1, S.uoff);
+    hipLaunchKernelGGL(k_count_lists, dim3(3), dim3(1024), 0, s, T, cg0, cg1, S.uoff, unit);
     LEGS_CHECK_LAUNCH(ctx);
     // passes for the most super-tiles there can be (one per tile); the ones
     // the actual count does not need return at once
@@ -1841,17 +1848,17 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
     }
 
     // 5. compaction of the super-tile lists into the tile lists, in units of
-    //    LEGS_COMPACT_UNIT list entries per wave
-    const int64_t max_units = S.ccap / LEGS_COMPACT_UNIT + T;
+    //    `unit` list entries per wave
+    const int64_t max_units = S.ccap / unit + T;
     const int gu = grid_for(ctx, max_units, 256 / LEGS_WAVE, 8);
     UnitCtx *udesc = reinterpret_cast<UnitCtx *>(S.udesc);
     hipLaunchKernelGGL(k_unit_desc, dim3(grid_for(ctx, max_units, 256, 4)), dim3(256), 0, s, S.uoff, T, S.cranges,
-                       sviews, views, n_views, udesc);
+                       sviews, views, n_views, unit, udesc);
     hipLaunchKernelGGL(k_compact_count, dim3(gu), dim3(256), 0, s, cv[0], cv[1], S.desc, S.uoff, T, udesc, P.pay,
                        OL.G, S.cut, S.ucnt);
     hipLaunchKernelGGL(k_compact_scan, dim3(grid_for(ctx, T, 256 / LEGS_WAVE, 4)), dim3(256), 0, s, S.uoff, T,
                        sviews, views, n_views, bins->ranges, S.ucnt);
-    hipLaunchKernelGGL(k_compact_write, dim3(gu), dim3(256), 0, s, cv[0], cv[1], S.desc, S.uoff, T, udesc, P.pay,
+    hipLaunchKernelGGL(unit == 128 ? k_compact_write<128> : k_compact_write<256>, dim3(gu), dim3(256), 0, s, cv[0], cv[1], S.desc, S.uoff, T, udesc, P.pay,
                        OL.G, S.cut, S.ucnt, bins->capacity,
                        (o->flags & LEGS_FLAG_IDS_ONLY) ? nullptr : bins->keys, bins->ids);
     LEGS_CHECK_LAUNCH(ctx);

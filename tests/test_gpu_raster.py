@@ -421,6 +421,24 @@ def test_instance_total_matches_full_sort(R, n, views):
     assert tot[0] == tot[1]
 
 
+def test_lists_identical_for_either_compaction_unit(R):
+    """Capacities on both sides of the line where the compaction's units double,
+    over lists that end inside units of both sizes."""
+    scene = synth.make_scene(30_000, 61, synth.VOL_CUBE, d_sem=0)
+    cams = synth.cameras_sphere(2, 62, 8.0, (300, 200))
+    o = R.opts()
+    rast = R.Rasterizer(cams, o)
+    d = PT.to_dev(scene)
+    proj = R.project(rast.ctx, d["mean"], d["log_scale"], d["quat"], d["opacity_logit"], rast.views, o)
+    got = []
+    for capacity in (1 << 23, (1 << 23) + 1):
+        bins = R.bin_sort(rast.ctx, proj, rast.views, o, R.BinsBuf(capacity, rast.views.total_tiles, d["mean"].device))
+        k = bins.n_instances
+        got.append((k, bins.keys[:k].cpu(), bins.ids[:k].cpu(), bins.ranges.cpu()))
+    assert got[0][0] == got[1][0] > 0
+    assert all(torch.equal(x, y) for x, y in zip(got[0][1:], got[1][1:]))
+
+
 def test_instance_totals_from_several_threads(R):
     """Calls on streams of their own wait for their own totals."""
     import threading
