@@ -146,11 +146,14 @@ k_dmlp_top1(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LEGS_WAVE);
     const int64_t groups = (P + 32 * NT - 1) / (32 * NT);
     const int64_t stride = (int64_t)gridDim.x * 8;
+    MlpInputs64<VEC8, NORM> in;
+    in.load(feat, P, cs, ps, ((int64_t)blockIdx.x * 8 + wave) * NT * 32);
     for (int64_t g = (int64_t)blockIdx.x * 8 + wave; g < groups; g += stride) {
         int off = 0;
         asm volatile("" : "+s"(off));
         legs_bf16x8 x[NT];
-        mlp_inputs64<VEC8, NORM>(feat, P, cs, ps, g * NT * 32, x);
+        in.operands(x);
+        in.load(feat, P, cs, ps, (g + stride) * NT * 32);
         legs_bf16x8 h2[NT][S3];
         dmlp_hidden<KB, NT>(L, off, x, h2);
         float best[NT];
@@ -219,11 +222,14 @@ k_dmlp_probs(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LEGS_WAVE);
     const int64_t groups = (P + 32 * NT - 1) / (32 * NT);
     const int64_t stride = (int64_t)gridDim.x * 4;
+    MlpInputs64<VEC8, NORM> in;
+    in.load(feat, P, cs, ps, ((int64_t)blockIdx.x * 4 + wave) * NT * 32);
     for (int64_t g = (int64_t)blockIdx.x * 4 + wave; g < groups; g += stride) {
         int off = 0;
         asm volatile("" : "+s"(off));
         legs_bf16x8 x[NT];
-        mlp_inputs64<VEC8, NORM>(feat, P, cs, ps, g * NT * 32, x);
+        in.operands(x);
+        in.load(feat, P, cs, ps, (g + stride) * NT * 32);
         legs_bf16x8 h2[NT][S3];
         dmlp_hidden<KB, NT>(L, off, x, h2);
         f32x16 z[KB][NT];
@@ -234,14 +240,22 @@ k_dmlp_probs(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
             const int64_t p = (g * NT + t) * 32 + (lane & 31);
             float best = -INFINITY;
             int bidx = 0x7fffffff;
+            if (top1) {
 #pragma unroll
-            for (int b = 0; b < KB; ++b)
+                for (int b = 0; b < KB; ++b)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float sc = z[b][t][r];
-                    if (sc > best) { best = sc; bidx = 32 * b + legs_drow(r, h); }
-                }
-            argmax_pair(best, bidx);
+                    for (int r = 0; r < 16; ++r) {
+                        const float sc = z[b][t][r];
+                        if (sc > best) { best = sc; bidx = 32 * b + legs_drow(r, h); }
+                    }
+                argmax_pair(best, bidx);
+            } else {                    // the maximum alone
+#pragma unroll
+                for (int b = 0; b < KB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) best = fmaxf(best, z[b][t][r]);
+                best = fmaxf(best, __shfl_xor(best, 32, LEGS_WAVE));
+            }
             float sum = 0.0f;
 #pragma unroll
             for (int b = 0; b < KB; ++b)
@@ -317,6 +331,13 @@ __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
+template <bool LINES, typename V>
+__device__ __forceinline__ void store_feature(V *p, V v)
+{
+    if constexpr (LINES) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // Grid: x = pixel groups (grid-stride), y = chunk of FCHUNK feature
 // dimensions. A group is 32 NT consecutive pixels whose NT tiles interleave:
 // column c of tile t is pixel 32 NT g + NT c + t, so each lane ends with NT
@@ -326,8 +347,13 @@ __device__ __forceinline__ f32x16 mfma16(f16x8 a, f16x8 b, f32x16 c)
 // k-step ks for pixel p: classes 16 ks + 8 (lane / 32) + e, one 16-byte load
 // from the row M[p]. Sixteen waves per workgroup: the S fragments of 512
 // dimensions fill the LDS (one workgroup per CU) and a wave fits in 128
-// registers. vec: P % NT == 0 and F 16-byte aligned, else element stores.
-template <int KB, int NT, bool OUT16>
+// registers. vec: P % NT == 0 and F 16-byte aligned, else element stores. LINES:
+// the rows of F start at 128-byte lines, so that every half-wave's store is whole
+// lines; they are then written past the caches, which leaves those to M (0.78
+// Mpx, N = 128, d = 512 in half, this kernel and k_dmlp_probs together: 397 ->
+// 343 us). Where a row starts inside a line the same stores would write parts of
+// lines (0.72 Mpx: 581 -> 750 us).
+template <int KB, int NT, bool OUT16, bool LINES>
 __global__ void __launch_bounds__(1024)
 k_lang_features(const _Float16 *__restrict__ M, int64_t P, const float *__restrict__ S, int d,
                 void *__restrict__ F, int vec)
@@ -382,13 +408,13 @@ k_lang_features(const _Float16 *__restrict__ M, int64_t P, const float *__restri
                             hv v;
 #pragma unroll
                             for (int t = 0; t < NT; ++t) v[t] = (_Float16)acc[t][r];
-                            *reinterpret_cast<hv *>(reinterpret_cast<_Float16 *>(F) + o) = v;
+                            store_feature<LINES>(reinterpret_cast<hv *>(reinterpret_cast<_Float16 *>(F) + o), v);
                         } else {
                             typedef float fv __attribute__((ext_vector_type(NT)));
                             fv v;
 #pragma unroll
                             for (int t = 0; t < NT; ++t) v[t] = acc[t][r];
-                            *reinterpret_cast<fv *>(reinterpret_cast<float *>(F) + o) = v;
+                            store_feature<LINES>(reinterpret_cast<fv *>(reinterpret_cast<float *>(F) + o), v);
                         }
                     }
                 } else {
@@ -460,14 +486,18 @@ int32_t legs_launch_language_features(legs_ctx *ctx, const uint16_t *probs16, in
     const dim3 grid((unsigned)gx, (unsigned)((d + FCHUNK - 1) / FCHUNK));
     const _Float16 *M = reinterpret_cast<const _Float16 *>(probs16);
     const int vec = P % NT == 0 && (reinterpret_cast<uintptr_t>(F) & 15) == 0;
-#define LEGS_FEAT(KB) if (out_f16) hipLaunchKernelGGL((k_lang_features<KB, NT, true>), grid, dim3(1024), 0, s, M, P, S, d, F, vec); \
-                      else hipLaunchKernelGGL((k_lang_features<KB, NT, false>), grid, dim3(1024), 0, s, M, P, S, d, F, vec)
+    const bool lines = P % (out_f16 ? 64 : 32) == 0 && (reinterpret_cast<uintptr_t>(F) & 127) == 0;
+#define LEGS_FEAT_L(KB, O, L) hipLaunchKernelGGL((k_lang_features<KB, NT, O, L>), grid, dim3(1024), 0, s, M, P, S, d, F, vec)
+#define LEGS_FEAT_O(KB, O) if (lines) LEGS_FEAT_L(KB, O, true); else LEGS_FEAT_L(KB, O, false)
+#define LEGS_FEAT(KB) if (out_f16) { LEGS_FEAT_O(KB, true); } else { LEGS_FEAT_O(KB, false); }
     switch (N) {
     case 32: LEGS_FEAT(1); break;
     case 64: LEGS_FEAT(2); break;
     default: LEGS_FEAT(4); break;
     }
 #undef LEGS_FEAT
+#undef LEGS_FEAT_O
+#undef LEGS_FEAT_L
     LEGS_CHECK_LAUNCH(ctx);
     return LEGS_OK;
 }

@@ -142,7 +142,7 @@ struct __attribute__((packed, aligned(4))) legs_float4u {
 // fragments a thread are built before any is stored, so that their loads are
 // in flight together. (Element by element, each conversion waited for its own
 // load: the top-1 decode of 2.07 Mpx from planes took 99.7 us, of which the 32
-// KB of weights about 25; with this and mlp_inputs64 it takes 58.9. The Table 3
+// KB of weights about 25; with this and MlpInputs64 it takes 58.9. The Table 3
 // decoder with F = M S, 144 + 128 KB, over 0.78 Mpx went from 465 to 388 us.)
 template <int N, int NT, int U, class F>
 __device__ __forceinline__ void legs_stage_frags(legs_bf16x8 *dst, F frag)
@@ -254,45 +254,51 @@ inline bool legs_feat_rows(const float *feat, int64_t cs, int64_t ps)
 }
 
 // Inputs of two 32-pixel tiles, the 64 pixels from p0 (wave-uniform): every
-// lane reads and normalises one pixel, then four lane-half swaps leave tile 0's
-// in x[0] and tile 1's in x[1] (lower halves), the bias ones in the upper
-// halves. (One tile per lane half at a time, as mlp_input does, takes twice
-// the loads and normalisations, with half of the lanes idle, and its 64-bit
-// lane addresses cost the strided decode a third of its waves: 252 registers
-// against 164.) VEC8: legs_feat_rows.
+// lane reads (load) and normalises one pixel, then four lane-half swaps leave
+// tile 0's in x[0] and tile 1's in x[1] (lower halves), the bias ones in the
+// upper halves. (One tile per lane half at a time, as mlp_input does, takes
+// twice the loads and normalisations, with half of the lanes idle, and its
+// 64-bit lane addresses cost the strided decode a third of its waves: 252
+// registers against 164.) load and operands are apart for kernels with one or
+// two waves per SIMD, which load their next 64 pixels before they work on these.
+// VEC8: legs_feat_rows.
 template <bool VEC8, bool NORM>
-__device__ __forceinline__ void mlp_inputs64(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps,
-                                             int64_t p0, legs_bf16x8 (&x)[2])
-{
-    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-    const int lane = __lane_id();
+struct MlpInputs64 {
     float v[LEGS_MLP_IN];
-    if (p0 + lane < P) {
-        if constexpr (VEC8) {
-            const float4 *src = reinterpret_cast<const float4 *>(feat) + 2 * p0;
-            const float4 a = src[2 * lane], b = src[2 * lane + 1];
-            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-            v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    __device__ __forceinline__ void load(const float *__restrict__ feat, int64_t P, int64_t cs, int64_t ps, int64_t p0)
+    {
+        const int lane = __lane_id();
+        if (p0 + lane < P) {
+            if constexpr (VEC8) {
+                const float4 *src = reinterpret_cast<const float4 *>(feat) + 2 * p0;
+                const float4 a = src[2 * lane], b = src[2 * lane + 1];
+                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+                v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = legs_ldfeat(feat, p0 + lane, e, cs, ps);
+            }
         } else {
 #pragma unroll
-            for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = legs_ldfeat(feat, p0 + lane, e, cs, ps);
+            for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = 0.0f;
         }
-    } else {
-#pragma unroll
-        for (int e = 0; e < LEGS_MLP_IN; ++e) v[e] = 0.0f;
     }
-    const u32x4 w = __builtin_bit_cast(u32x4, mlp_input<NORM>(v, 0));
-    const u32x4 ones = __builtin_bit_cast(u32x4, mlp_bias_ones(1));
-    u32x4 t0, t1;
+    __device__ __forceinline__ void operands(legs_bf16x8 (&x)[2]) const
+    {
+        typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+        const u32x4 w = __builtin_bit_cast(u32x4, mlp_input<NORM>(v, 0));
+        const u32x4 ones = __builtin_bit_cast(u32x4, mlp_bias_ones(1));
+        u32x4 t0, t1;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const auto r = __builtin_amdgcn_permlane32_swap(w[i], ones[i], false, false);
-        t0[i] = r[0];
-        t1[i] = r[1];
+        for (int i = 0; i < 4; ++i) {
+            const auto r = __builtin_amdgcn_permlane32_swap(w[i], ones[i], false, false);
+            t0[i] = r[0];
+            t1[i] = r[1];
+        }
+        x[0] = __builtin_bit_cast(legs_bf16x8, t0);
+        x[1] = __builtin_bit_cast(legs_bf16x8, t1);
     }
-    x[0] = __builtin_bit_cast(legs_bf16x8, t0);
-    x[1] = __builtin_bit_cast(legs_bf16x8, t1);
-}
+};
 
 // Hidden layers of NT 32-pixel tiles at once: every weight fragment read from
 // LDS feeds NT independent MFMAs. lds_off is an opaque zero the caller

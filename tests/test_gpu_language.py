@@ -104,6 +104,14 @@ def test_language_features_match_oracle(ctx, N, d, out_f16, n, misalign):
     note(f"max rel err vs exact {float((np.abs(Fg - o['F']) / np.maximum(o['F_abs'], 1e-30))[~amb].max()):.3g}")
 
 
+# rows of F that start at 128-byte lines and others, F off the line
+@pytest.mark.parametrize("N,d,out_f16,n,misalign", [(128, 512, True, 3008, 0), (64, 96, False, 3008, 0),
+                                                    (32, 544, False, 3104, 1), (128, 96, True, 64, 0),
+                                                    (64, 512, False, 32, 0), (32, 96, True, 3040, 0)])
+def test_language_features_whole_lines(ctx, N, d, out_f16, n, misalign):
+    test_language_features_match_oracle(ctx, N, d, out_f16, n, misalign)
+
+
 def test_paper_decoder_and_features_at_bench_size(ctx):
     """The Table 3 decoder and F = M S at the size the bench times them (four
     1920x1080 views of 8-d rendered features, N = 128, d = 512, float32 F),
