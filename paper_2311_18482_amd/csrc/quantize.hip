@@ -413,11 +413,18 @@ k_quant_pass(QuantArgs A)
     vm_wait<0>();                            // the loads of the round that does not come
     float *s_p = reinterpret_cast<float *>(frag1);
     block_sums<KB * 16, QTHREADS / LEGS_WAVE>(psum, s_p, lane, wave);
-    // (in float64: thousands of waves add to the one loss)
+    // (one addition per workgroup to the one loss, in float64)
+    __shared__ double s_loss[QTHREADS / LEGS_WAVE];
     double lsum = lcos;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, LEGS_WAVE);
-    if (lane == 0 && lsum != 0.0) atomicAdd(A.lsum, lsum);
+    if (lane == 0) s_loss[wave] = lsum;
+    __syncthreads();
+    if (tid == 0) {
+        lsum = 0.0;
+        for (int w = 0; w < QTHREADS / LEGS_WAVE; ++w) lsum += s_loss[w];
+        if (lsum != 0.0) atomicAdd(A.lsum, lsum);
+    }
     for (int j = tid; j < N; j += QTHREADS) {
         if (s_p[j] != 0.0f) atomicAdd(A.psum + j, s_p[j]);
         if (s_cnt[j]) atomicAdd(A.counts + j, s_cnt[j]);

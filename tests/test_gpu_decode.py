@@ -260,6 +260,13 @@ def test_l1_loss_gradient(ctx, DEC, sizes):
     assert loss.item() == pytest.approx(loss_ref, rel=1e-5)
 
 
+# one pixel, a plane of one workgroup and one more pixel, more pixels than the
+# workgroups of a plane hold at once
+@pytest.mark.parametrize("sizes", [((1, 1),), ((64, 64),), ((241, 17), (64, 64)), ((640, 401), (3, 2))])
+def test_l1_loss_workgroup_edges(ctx, DEC, sizes):
+    test_l1_loss_gradient(ctx, DEC, sizes)
+
+
 @pytest.mark.parametrize("K,normalize", [(128, True), (64, False), (32, True)])
 def test_top1_inputs_at_tile_edges(ctx, DEC, K, normalize):
     """The top-1 decoders read 64 pixels a wave: row-major features, planes and
