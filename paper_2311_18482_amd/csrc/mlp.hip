@@ -113,8 +113,10 @@ __device__ __forceinline__ bf16x8 cvt8(const f32x16 &z, int first)
 // A 32-unit x 32-pixel block held as two B fragments (lane = pixel, k-slots =
 // units in accumulator order) turned into two fragments with lane = unit and
 // k-slots = pixels: as the A operand against the identity, the matrix unit
-// returns the block transposed and exact (every product is by 1 or 0). id: this
-// lane's identity fragments in LDS.
+// returns the block transposed and exact (every product is by 1 or 0; a pixel
+// with an infinity or a NaN spreads it over its block's units, but has made the
+// last layer's gradient NaN before that). id: this lane's identity fragments in
+// LDS.
 __device__ __forceinline__ f32x16 transpose_block(const bf16x8 &f0, const bf16x8 &f1, const bf16x8 *id)
 {
     return legs_mfma(f1, id[LEGS_WAVE], legs_mfma(f0, id[0], (f32x16){}));

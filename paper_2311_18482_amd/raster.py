@@ -147,7 +147,7 @@ def project(ctx: Context, mean, log_scale, quat, opacity_logit, views: Views, o:
 
 def bin_sort(ctx: Context, proj: ProjectedBuf, views: Views, o: L.Opts,
              bins: BinsBuf | None = None, sync_count: bool = True) -> BinsBuf:
-    """Bin and sort. With sync_count the instance total is read back and the
+    """Bin and sort. With sync_count the instance total is waited for and the
     buffers grown (and the call repeated) if it exceeds their capacity."""
     device = proj.mean2d.device
     if bins is None:
