@@ -1833,13 +1833,15 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
                            OL.G, S.ccap, ck[1], cv[1]);
     const CoarsePay P{frecs, reinterpret_cast<FRec *>(S.cpay), OL.G};
     // one partition per segment up to LEGS_SEG_MAX segments (segments past the
-    // last partition return at once)
-    const int nseg = LEGS_SEG_MAX;
+    // last partition return at once; no more of them than the lists can have
+    // partitions: binning of 25k Gaussians 138 -> 135 us, of 60k in two views 160 -> 156)
+    const int64_t cparts = (S.ccap + LEGS_SORT_PART - 1) / LEGS_SORT_PART;
+    const int nseg = (int)(cparts < LEGS_SEG_MAX ? cparts : LEGS_SEG_MAX);
     for (int p = 0; p < cpasses; ++p) {
         const int wo = p % 2, ri = 1 - wo;
         hipLaunchKernelGGL(k_coarse_upsweep, dim3(nseg), dim3(LEGS_SORT_THREADS), 0, s, ck[ri], ccount, S.ccap,
                            S.desc, p, S.seg_hist);
-        hipLaunchKernelGGL(k_seg_scan, dim3(256), dim3(LEGS_SEG_MAX), 0, s, S.seg_hist, nseg, S.hist, S.desc,
+        hipLaunchKernelGGL(k_seg_scan, dim3(256), dim3(nseg <= 256 ? 256 : LEGS_SEG_MAX), 0, s, S.seg_hist, nseg, S.hist, S.desc,
                            p, S.seg_off);
         hipLaunchKernelGGL((k_onesweep<uint32_t, true>), dim3(nseg), dim3(LEGS_SORT_THREADS), 0, s, ck[ri], cv[ri],
                            ck[wo], cv[wo], ccount, S.ccap, p, 0, 0, S.desc, nullptr, nullptr, nullptr, P,
