@@ -291,6 +291,25 @@ def test_top1_inputs_at_tile_edges(ctx, DEC, K, normalize):
             assert torch.equal(dec(ctx, (rows, P, 1, 8), shifted, K, normalize=normalize)[0], want)
 
 
+@pytest.mark.parametrize("K", [32, 64, 128])
+def test_distributions_on_and_off_a_line(ctx, DEC, K):
+    """The distribution is the same whether its rows start at 128-byte lines
+    (stored past the caches) or 16 bytes off them."""
+    from paper_2311_18482_amd import _lib as L, raster as R
+    ws, bs = synth.mlp_init((8, 64, 64, K), 71)
+    p = DEC.mlp_pack(ws, bs).cuda()
+    for P in (1, 33, 700):
+        f = torch.from_numpy(features(P, 72 + K)).cuda()
+        src = DEC.rowmajor_features(f)
+        want = DEC.decode_mlp(ctx, src, p, K, probs=True)[1]
+        got = torch.empty(P * K + 4, device="cuda")[4:]
+        assert want.data_ptr() % 128 == 0 and got.data_ptr() % 128 == 16
+        t1 = torch.empty(P, dtype=torch.int32, device="cuda")
+        ctx.check(L.lib().legs_decode_mlp(ctx.handle, f.data_ptr(), P, 1, 8, p.data_ptr(), K, DEC.mlp_flags(True),
+                                          got.data_ptr(), t1.data_ptr(), R._stream()))
+        assert torch.equal(got.view(P, K), want)
+
+
 @pytest.mark.parametrize("K,B", [(32, 1), (64, 33), (128, 128), (128, 129), (32, 4097), (64, 32768 + 1), (128, 40000)])
 def test_mlp_gradient_sizes(ctx, DEC, K, B):
     """Batches around the training kernel's tiles (32 pixels), workgroups (128)
