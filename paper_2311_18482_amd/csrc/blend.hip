@@ -25,13 +25,13 @@
 // misses the quadrant is skipped by a scalar test; early exit per wave (ballot)
 // and per workgroup (__syncthreads_count).
 // Backward: each wave owns a 16 x 16 block with 4 pixels per lane (16 x 8 with
-// 2 for 17-32 channels, 8 x 8 with 1 for wider sets or 8-pixel tiles; 8 x 8
-// where there are few of them), and replays them back to front from
-// (T_final, last): T_k = T_{k+1} / (1 - alpha_k).
+// 2 for 17-32 channels, 8 x 8 with 1 for wider sets or 8-pixel tiles; four waves
+// with 8 x 8 pixels each where there are few of them), and replays them back to
+// front from (T_final, last): T_k = T_{k+1} / (1 - alpha_k).
 // Per Gaussian, a lane first sums its own pixels in registers, then the wave
 // sums the 6 + C values with a transpose reduction (lane swaps and DPP moves
 // that leave each total in one lane), and one atomic instruction adds all of
-// them, one lane per value.
+// them, one lane per value (of four waves that share 16 x 16 pixels, their sum).
 #include "legs_internal.h"
 #include "wave_reduce.h"
 
@@ -179,7 +179,7 @@ struct Stage {
         box = reinterpret_cast<uint32_t *>(qy + (size_t)B * NQ);
         id = box + B;
     }
-    static size_t bytes(int B) { return (size_t)B * (16 + 4 * CP + 8 * NQ + 4 + 4); }
+    static constexpr size_t bytes(int B) { return (size_t)B * (16 + 4 * CP + 8 * NQ + 4 + 4); }
 };
 
 // Stages nb list entries starting at list position lo: each thread takes
@@ -454,14 +454,16 @@ k_blend_fwd(BlendParams P, float *__restrict__ out, float *__restrict__ Tf,
 // ---- backward ----------------------------------------------------------------------
 
 // Per-wave block of the backward: SW x SH pixels, PPL = SW * SH / 64 per lane.
-// WPG of a tile's blocks make a workgroup.
-template <int TILE, int PPLV, int WPG> struct BwdShape {
+// WPG of a tile's blocks make a workgroup. SUM: the workgroup's four 8 x 8 blocks
+// are a 16 x 16 one, and their sums are added before they go to memory.
+template <int TILE, int PPLV, int WPG, bool SUM> struct BwdShape {
     static constexpr int PPL = PPLV;
     static constexpr int SW = PPL == 1 ? 8 : 16;
     static constexpr int SH = PPL == 4 ? 16 : 8;
     static constexpr int NT = LEGS_WAVE * WPG;
     static constexpr int NP = TILE * TILE / (PPL * NT);    // workgroups per tile
     static constexpr int ROWSTEP = LEGS_WAVE / SW;
+    static_assert(!SUM || (PPL == 1 && WPG == 4 && TILE >= 16), "four 8 x 8 blocks are summed");
 };
 
 // The block that takes the least work: one reduction and one set of atomics for
@@ -479,12 +481,16 @@ constexpr int bwd_ppl() { return TILE == 8 || CP > 32 ? 1 : (CP <= 16 ? 4 : 2); 
 // and dL/do = exp(power) dL/dalpha when not clamped. The power's derivatives
 // (mean offset and conic) are summed per lane as moments of (dx, dy) and
 // turned into gradients once per Gaussian (the map is linear).
-template <int TILE, int CP, int PPLV, int WPG>
-__global__ void __launch_bounds__((BwdShape<TILE, PPLV, WPG>::NT), 4)
+// SUM: a wave leaves its sums of an entry in LDS (slots, behind the staged batch),
+// and at the end of the batch the workgroup adds the four waves' in a fixed order:
+// memory receives one partial sum per entry and 16 x 16 pixels, as from whole
+// blocks, so the gradients are as close to the exact ones as those.
+template <int TILE, int CP, int PPLV, int WPG, bool SUM>
+__global__ void __launch_bounds__((BwdShape<TILE, PPLV, WPG, SUM>::NT), 4)
 k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restrict__ last,
             const float *__restrict__ d_out, float *__restrict__ grad2d, float *__restrict__ d_ch)
 {
-    using Shp = BwdShape<TILE, PPLV, WPG>;
+    using Shp = BwdShape<TILE, PPLV, WPG, SUM>;
     constexpr int NT = Shp::NT, PPL = Shp::PPL, NQ = TILE / 8;
     constexpr int NV = 6 + CP;                          // values summed per Gaussian
     constexpr int KF = legs_tr::final_k(NV);
@@ -492,9 +498,12 @@ k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restr
     Stage<TILE, CP> S(s_dyn, P.batch);
     __shared__ int64_t s_tile;
     __shared__ uint32_t s_maxlast;
+    __shared__ uint64_t s_vis[SUM ? WPG : 1][4];        // SUM: the waves' entries of each 64 of a batch
     const int B = P.batch;
+    float *slots = reinterpret_cast<float *>(S.id + B);   // SUM: [WPG][B][NV]
     const float amax = P.amax;
     const int l = threadIdx.x % LEGS_WAVE;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LEGS_WAVE);
     constexpr int BX = TILE / Shp::SW;                 // wave blocks per tile row
     // which summed value this lane adds to memory after the wave reduction
     int vidx[NV];
@@ -514,8 +523,9 @@ k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restr
     for (int64_t item = next_item(P, -1, items, &s_tile); item < items; item = next_item(P, item, items, &s_tile)) {
         const int64_t q = item / NP;
         const int64_t tile = P.counter ? (int64_t)P.order[q] : q;
-        const int w = __builtin_amdgcn_readfirstlane((int)(item - q * NP) * WPG + threadIdx.x / LEGS_WAVE);
-        const int bx0 = (w % BX) * Shp::SW, by0 = (w / BX) * Shp::SH;
+        const int part = __builtin_amdgcn_readfirstlane((int)(item - q * NP)), w = part * WPG + wave;
+        const int bx0 = SUM ? part % (TILE / 16) * 16 + (wave & 1) * 8 : (w % BX) * Shp::SW;
+        const int by0 = SUM ? part / (TILE / 16) * 16 + (wave >> 1) * 8 : (w / BX) * Shp::SH;
         const int lx = bx0 + (l % Shp::SW);
         const int ly0 = by0 + (l / Shp::SW);           // pixel p of this lane: row ly0 + ROWSTEP p
         const float fx = (float)(lx & 7);
@@ -565,6 +575,7 @@ k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restr
                   const int x0 = sext8(pkl, 0), x1 = sext8(pkl, 8), y0 = sext8(pkl, 16), y1 = sext8(pkl, 24);
                   hit = !(x1 < bx0 || x0 > bx0 + Shp::SW - 1 || y1 < by0 || y0 > by0 + Shp::SH - 1);
               }
+              uint64_t vis = 0;
               for (uint64_t rel = legs_ballot(hit); rel; rel &= rel - 1) {
                 const int hl = (int)__builtin_ctzll(rel);           // the lowest lane: the last entry first
                 const int j = c1 - 1 - hl;
@@ -638,6 +649,13 @@ k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restr
                 acc[4] = -0.5f * syy;
                 acc[5] = sop;
                 legs_tr::reduce<NV>(acc, l);
+                if constexpr (SUM) {
+                    vis |= 1ull << hl;
+#pragma unroll
+                    for (int r = 0; r < KF; ++r)
+                        if (vidx[r] >= 0) slots[(wave * B + j) * NV + vidx[r]] = acc[r];
+                    continue;
+                }
                 const uint32_t gid = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.id[j]);   // scalar addressing
                 float *g2d = grad2d + 8 * ((int64_t)ti.v * P.n + gid);
                 float *dc = d_ch + (int64_t)gid * P.C;
@@ -645,6 +663,23 @@ k_blend_bwd(BlendParams P, const float *__restrict__ Tf, const uint32_t *__restr
                 for (int r = 0; r < KF; ++r)
                     if (vok[r] && acc[r] != 0.0f) atomicAdd((vgeo[r] ? g2d : dc) + voff[r], acc[r]);
               }
+              if constexpr (SUM) {
+                  if (l == 0) s_vis[wave][(nb - c1) / LEGS_WAVE] = vis;
+              }
+            }
+            if constexpr (SUM) {
+                __syncthreads();
+                for (int e = threadIdx.x; e < nb * NV; e += NT) {
+                    const int j = e / NV, i = e - j * NV, hl = nb - 1 - j;
+                    float x[WPG];
+#pragma unroll
+                    for (int k = 0; k < WPG; ++k)
+                        x[k] = (s_vis[k][hl / LEGS_WAVE] >> (hl % LEGS_WAVE)) & 1 ? slots[k * B * NV + e] : 0.0f;
+                    const float t = (x[0] + x[1]) + (x[2] + x[3]);
+                    if (t == 0.0f) continue;
+                    if (i < 6) atomicAdd(grad2d + 8 * ((int64_t)ti.v * P.n + S.id[j]) + i, t);
+                    else if (i - 6 < P.C) atomicAdd(d_ch + (int64_t)S.id[j] * P.C + i - 6, t);
+                }
             }
             hi = lo_rel;
             __syncthreads();
@@ -769,22 +804,27 @@ int64_t blend_grid(legs_ctx *ctx, const BlendParams &P, int64_t items, int threa
     return items < cap ? items : cap;
 }
 
-template <int TILE, int CP, int PPL, int WPG = TILE * TILE / (PPL * LEGS_WAVE)>
+template <int TILE, int CP, int PPL, int WPG, bool SUM>
 int32_t launch_bwd(legs_ctx *ctx, const BlendParams &P0, const float *Tf, const uint32_t *last, const float *d_out,
                    float *grad2d, float *d_ch, hipStream_t s)
 {
-    using Shp = BwdShape<TILE, PPL, WPG>;
+    using Shp = BwdShape<TILE, PPL, WPG, SUM>;
     constexpr int NT = Shp::NT;
     BlendParams P = P0;
     // single-wave workgroups stage at most 128 entries: a 256-entry batch would
-    // let LDS, not registers, cap the waves per CU
-    if (NT == LEGS_WAVE && P.batch > 128) P.batch = 128;
-    const size_t lds = Stage<TILE, CP>::bytes(P.batch);
+    // let LDS, not registers, cap the waves per CU; summed blocks at most what
+    // the waves' slots leave of 64 KB (of which two workgroups fit on a CU, as many
+    // as there are)
+    constexpr int slot = SUM ? WPG * (6 + CP) * 4 : 0;
+    constexpr int most = SUM ? (CP <= 16 ? 128 : 64) : (NT == LEGS_WAVE ? 128 : 256);
+    static_assert(!SUM || Stage<TILE, CP>::bytes(most) + most * slot <= 65536 - 256, "LDS of a batch with slots");
+    if (P.batch > most) P.batch = most;
+    const size_t lds = Stage<TILE, CP>::bytes(P.batch) + (size_t)P.batch * slot;
     if (lds > 65536) return legs_set_error(ctx, LEGS_ERR_UNSUPPORTED, "LDS batch too large for C");
     if (P.total_tiles <= 0) return LEGS_OK;
     const int64_t grid = blend_grid(ctx, P, P.total_tiles * Shp::NP, NT, s);
-    hipLaunchKernelGGL((k_blend_bwd<TILE, CP, PPL, WPG>), dim3((unsigned)grid), dim3(NT), lds, s, P, Tf, last, d_out,
-                       grad2d, d_ch);
+    hipLaunchKernelGGL((k_blend_bwd<TILE, CP, PPL, WPG, SUM>), dim3((unsigned)grid), dim3(NT), lds, s, P, Tf, last,
+                       d_out, grad2d, d_ch);
     LEGS_CHECK_LAUNCH(ctx);
     return LEGS_OK;
 }
@@ -810,20 +850,20 @@ int32_t launch_tile_cp(legs_ctx *ctx, bool fwd, const BlendParams &P, float *out
     if (!fwd) {
         // Few blocks leave the chip idle for as long as the longest list takes:
         // up to two of 16 x 16 pixels per CU (one wave for every second SIMD) they
-        // are cut to 8 x 8, four to a workgroup. In us, whole / cut: 12 channels,
-        // 16-pixel tiles, 64 blocks 501 / 187, 294: 296 / 140, 512: 375 / 181;
-        // 32-pixel tiles 557 / 196 and 371 / 189; 20 channels (16 x 8 whole) 333 /
-        // 222 and 318 / 223. Beyond the line a cut still pays (900 blocks 250 / 171,
-        // in halves 2040: 295 / 272; 3600: 363 / 415), but it multiplies the partial
-        // sums that arrive in no fixed order, and from about 600 blocks gradients
-        // that cancel to 1e-3 of their terms then differ between two runs by more
-        // than 1e-4 of themselves (whole blocks: by half of that).
+        // are cut to 8 x 8, the four of a block to a workgroup that adds their sums.
+        // In us, whole / cut: 12 channels, 16-pixel tiles, 64 blocks 500 / 203, 294:
+        // 299 / 146, 512: 255 / 139; 32-pixel tiles 557 / 245 and 275 / 144; 20
+        // channels (16 x 8 whole) 327 / 267 and 242 / 196. (Without the sums, one
+        // atomic per 8 x 8 pixels, 3 to 20 % less, but the quaternions' gradients
+        // came out up to 7 times further from the exact ones.) Up to the line every
+        // workgroup runs at once: the slots let two onto a CU. Past it a cut still
+        // pays for a while (900 blocks 394 / 273, 2025: 314 / 350).
         constexpr int PPL = bwd_ppl<TILE, CP>();
         if constexpr (PPL > 1) {
             if (P.total_tiles * (TILE * TILE) / 256 <= 2 * (int64_t)ctx->num_cus)
-                return launch_bwd<TILE, CP, 1, 4>(ctx, P, cTf, clast, d_out, grad2d, d_ch, s);
+                return launch_bwd<TILE, CP, 1, 4, true>(ctx, P, cTf, clast, d_out, grad2d, d_ch, s);
         }
-        return launch_bwd<TILE, CP, PPL>(ctx, P, cTf, clast, d_out, grad2d, d_ch, s);
+        return launch_bwd<TILE, CP, PPL, TILE * TILE / (PPL * LEGS_WAVE), false>(ctx, P, cTf, clast, d_out, grad2d, d_ch, s);
     }
     // With few pixels, two or four lanes share one (each with its part of the
     // channels), so that more waves walk shorter lists. The lines lie at 3/2 and

@@ -140,6 +140,34 @@ def test_cut_backward_blocks_from_the_persistent_queue(R, tile):
     PT.compare_grads(got[1], got[0], scene.n)
 
 
+@pytest.mark.parametrize("persistent", [False, True])
+@pytest.mark.parametrize("tile,d_sem", [(16, 0), (16, 8), (16, 28), (32, 8), (32, 16)])
+def test_cut_backward_blocks_add_one_sum_per_16_pixels(R, tile, d_sem, persistent):
+    """Memory receives one partial sum per Gaussian and 16 x 16 pixels, also where
+    the backward's blocks are cut to 8 x 8. One Gaussian over a whole tile and a
+    gradient buffer that holds 2^24, where float32 has steps of 2: a quarter's sum
+    of 3/4 would be lost, the 16 x 16 pixels' 3 moves it by 2 or 4."""
+    C = 4 + d_sem
+    scene = synth.Scene(np.array([[0.0, 0.0, 4.0]], np.float32), np.full((1, 3), 1.0, np.float32),
+                        np.array([[1.0, 0.0, 0.0, 0.0]], np.float32), np.zeros(1, np.float32),
+                        np.ones((1, C), np.float32), d_sem)
+    rast, d, proj, bins, out, T, last = run_forward(R, scene, [synth.camera_front(tile, tile, float(tile))],
+                                                    R.opts(tile=tile, persistent=persistent))
+    image = out.cpu().numpy().reshape(C, tile, tile).astype(np.float64)
+    assert image.min() > 0                                 # it reaches every pixel
+    blocks = (tile // 16) ** 2
+    G = np.zeros((C, tile, tile), np.float32)
+    for y in range(0, tile, 8):
+        for x in range(0, tile, 8):
+            G[:, y:y + 8, x:x + 8] = 0.75 / image[0, y:y + 8, x:x + 8].sum()
+    start = 2.0 ** 24
+    d_ch = torch.full((1, C), start, device="cuda")
+    R.render_backward(rast.ctx, proj, bins, rast.views, d["channels"], rast.o, T, last,
+                      torch.from_numpy(G.reshape(-1)).cuda(), torch.zeros((1, 8), device="cuda"), d_ch)
+    moved = d_ch.cpu().numpy().astype(np.float64) - start
+    assert (moved >= 2.0 * blocks).all() and (moved <= 4.0 * blocks).all(), moved
+
+
 def test_many_views_index_apart_from_depth_keys(R):
     """520 small views: the G-view depth keys need 6 digit passes (10 view bits
     above the 32 depth bits) and the G-view index 17 bits, more than 64 in all,
