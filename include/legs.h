@@ -168,7 +168,8 @@ int32_t legs_views_build(const legs_camera *cams, int32_t n_views, const legs_op
 int64_t legs_projected_blocks(int64_t n, int32_t n_views);
 /* Bytes of legs_projected.order for n Gaussians x n_views. */
 int64_t legs_order_scratch_bytes(int64_t n, int32_t n_views);
-/* Bytes of legs_bins.scratch for a given instance capacity and tile count. */
+/* Bytes of legs_bins.scratch for a given instance capacity and tile count; more
+ * for more of either, so scratch for one capacity serves every smaller one. */
 int64_t legs_sort_scratch_bytes(int64_t capacity, int64_t total_tiles);
 /* Radix passes the sort runs for total_tiles tiles (8-bit digits over the
  * 32 depth bits plus ceil(log2 total_tiles) tile bits). */

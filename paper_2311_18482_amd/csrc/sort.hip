@@ -24,6 +24,7 @@
 // partitions (partition ids handed out by an atomic counter in launch order,
 // so every partition waited on belongs to a running workgroup) or, for the
 // segment passes, from per-segment digit counts scanned beforehand.
+#include <algorithm>
 #include <thread>
 
 #include "legs_internal.h"
@@ -1443,7 +1444,8 @@ k_ranges(const uint64_t *__restrict__ keys, const uint64_t *__restrict__ count, 
 // Entries of the coarse lists per unit of the compaction (one wave each): half
 // as many where that many more waves fill the chip (binning of 10k Gaussians 120
 // -> 114 us, of 300k 183 -> 178, of 1M in one view the same, in three 490 -> 500).
-static int compact_unit(int64_t capacity) { return capacity <= (1 << 23) ? 128 : 256; }
+constexpr int64_t kSmallCapacity = 1 << 23;
+static int compact_unit(int64_t capacity) { return capacity <= kSmallCapacity ? 128 : 256; }
 
 legs_sort_layout legs_sort_layout_for(int64_t capacity, int64_t total_tiles)
 {
@@ -1457,7 +1459,11 @@ legs_sort_layout legs_sort_layout_for(int64_t capacity, int64_t total_tiles)
     int64_t o = up(L.status_off + 8 * (int64_t)LEGS_SORT_MAX_PASSES * L.parts * 256);
     const int64_t T = total_tiles > 0 ? total_tiles : 0;   // the G-view sort needs none of these
     L.ccap = T > 0 ? capacity + T : 0;
-    const int64_t units = T > 0 ? L.ccap / compact_unit(capacity) + T : 0;
+    // the most units of this or a smaller capacity, so that scratch for one capacity
+    // holds the arrays of every smaller one
+    const auto units_at = [T](int64_t c) { return (c + T) / compact_unit(c) + T; };
+    const int64_t small = capacity < kSmallCapacity ? capacity : kSmallCapacity;
+    const int64_t units = T > 0 ? std::max(units_at(capacity), units_at(small)) : 0;
     L.tcount_off = o; o = up(o + 4 * T);
     L.scount_off = o; o = up(o + 4 * T);     // right after tcount: both are cleared at once
     L.cranges_off = o; o = up(o + 8 * T);

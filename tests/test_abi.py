@@ -76,3 +76,17 @@ def test_null_context_is_rejected(L):
     lib = L.lib()
     assert lib.legs_project(None, None, None, None, None, 0, None, 1, None, None, None) == L.LEGS_ERR_ARG
     assert lib.legs_create(0, None) == L.LEGS_ERR_ARG
+
+
+@pytest.mark.parametrize("tiles", [1, 64, 8160, 40_000])
+def test_sort_scratch_grows_with_the_capacity(L, tiles):
+    """Scratch that serves a capacity serves every smaller one: the size never
+    falls as the capacity grows, also where the compaction's units change (at
+    2^23 instances) and for some way beyond, in steps down to one instance."""
+    size = L.lib().legs_sort_scratch_bytes
+    line = 1 << 23
+    caps = sorted({0, 1, 4096} | {line + d for d in (-4097, -1, 0, 1, 2, 4097, 100_000, 140_000, 200_000, line)} |
+                  {c << 16 for c in range(1, 400, 3)})
+    sizes = [size(c, tiles) for c in caps]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:])), [
+        (c, a, b) for c, a, b in zip(caps, sizes, sizes[1:]) if a > b]
