@@ -267,6 +267,35 @@ def test_l1_loss_workgroup_edges(ctx, DEC, sizes):
     test_l1_loss_gradient(ctx, DEC, sizes)
 
 
+# pieces (32,768 elements at the largest) that span views and planes of one
+# element, begin and end inside a group of four, and outnumber the workgroups
+@pytest.mark.parametrize("sizes", [((1, 1),) * 40 + ((513, 401),) + ((1, 1), (3, 1)) * 20,
+                                   ((64, 32), (1, 1), (64, 32), (127, 129)), ((1025, 1023), (5, 1))])
+def test_l1_loss_pieces_across_views(ctx, DEC, sizes):
+    test_l1_loss_gradient(ctx, DEC, sizes)
+
+
+def test_l1_loss_of_uneven_views_is_spread_evenly(ctx, DEC):
+    """15 small views beside a large one take no longer than as many pixels in one
+    view: the same bytes; with whole planes to single workgroups five times as
+    long (bound: twice)."""
+    from paper_2311_18482_amd import raster as R
+    C, us = 20, []
+    for sizes in (((1920, 1240),), ((160, 120),) * 15 + ((1920, 1080),)):
+        views = R.views_build([synth.camera_front(w, h, float(w)) for w, h in sizes], R.opts(), ctx.device)
+        out, tgt = (torch.rand(C * views.total_pixels, device="cuda") for _ in range(2))
+        t = []
+        for _ in range(15):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            DEC.l1_loss_grad(ctx, out, tgt, views, C, C - 1, 1.0)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        us.append(sorted(t)[7] * 1e3)
+    assert us[1] < 2 * us[0], us
+
+
 @pytest.mark.parametrize("K,normalize", [(128, True), (64, False), (32, True)])
 def test_top1_inputs_at_tile_edges(ctx, DEC, K, normalize):
     """The top-1 decoders read 64 pixels a wave: row-major features, planes and
