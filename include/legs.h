@@ -350,11 +350,16 @@ int32_t legs_language_features(legs_ctx *ctx, const uint16_t *probs_f16, int64_t
  * float32 = (L_cos, L_lb, L_q) (nullable), grad [N][d] float32 = dL_q/dS
  * (nullable: no gradient pass), straight through the half rounding of S;
  * the index and r are piecewise constant (no gradient). A zero part of a
- * feature or code has cosine 0. workspace: legs_quantize_workspace_bytes(K,
- * N, d) bytes (16-byte aligned). Dot products accumulate in float32 on FP16
- * MFMA; features whose two best distances lie within float32 rounding of each
- * other may take either index. */
+ * feature or code has cosine 0. workspace (16-byte aligned):
+ * legs_quantize_workspace_bytes(K, N, d) bytes, most of them the gradient's, 8 N
+ * bytes of cosines per feature for up to 2^22 features at once (1.1 GB for 2^20
+ * features and at most 4.3 GB at N = 128); without a gradient (grad NULL)
+ * legs_quantize_index_workspace_bytes(K, N, d) bytes are enough (2 N d and some
+ * KB, whatever K). Dot products accumulate in float32 on FP16 MFMA; features
+ * whose two best distances lie within float32 rounding of each other may take
+ * either index. */
 int64_t legs_quantize_workspace_bytes(int64_t K, int32_t N, int32_t d);
+int64_t legs_quantize_index_workspace_bytes(int64_t K, int32_t N, int32_t d);
 int32_t legs_quantize(legs_ctx *ctx, const uint16_t *feat, int64_t K, int32_t d, int32_t d_clip,
                       const float *S, int32_t N, float lambda_dino, float lambda_cos, float lambda_lb,
                       void *workspace, int32_t *index, uint32_t *counts, float *prob_mean, float *losses,

@@ -106,6 +106,7 @@ _SIGS = {
     "legs_smooth_workspace_bytes": (I64, [I64]),
     "legs_smooth_loss_grad": (I32, [P, P, P, I32, I32, I32, I64, P, ct.c_float, ct.c_float, P, P, P, P, P]),
     "legs_quantize_workspace_bytes": (I64, [I64, I32, I32]),
+    "legs_quantize_index_workspace_bytes": (I64, [I64, I32, I32]),
     "legs_quantize": (I32, [P, P, I64, I32, I32, P, I32, ct.c_float, ct.c_float, ct.c_float, P, P, P, P, P,
                             P, P]),
     "legs_decode_dmlp": (I32, [P, P, I64, I64, I64, P, I32, I32, P, P, P, P]),

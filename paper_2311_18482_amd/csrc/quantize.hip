@@ -50,6 +50,8 @@
 //                    chunk per group 660; one workgroup per CU makes the call
 //                    35 % slower, four 9 %, one chunk per group 19 %.
 //  k_quant_finish    the column-sum term, the losses, r and p.
+#include <algorithm>
+
 #include "legs_internal.h"
 #include "legs_decode_internal.h"
 #include "wave_reduce.h"
@@ -161,7 +163,8 @@ k_quant_prep(const float *__restrict__ S, int d, int dC, f16x8 *__restrict__ img
 
 struct QuantArgs {
     const _Float16 *F;
-    int64_t K, Kp;
+    int64_t K, Kp;              // the launch's features, and padded to whole rounds
+    int64_t Kall;               // the call's
     int d, dC;
     const f16x8 *img;
     const float *invS;          // [2][N]
@@ -446,10 +449,10 @@ k_quant_weights(QuantArgs A)
     const int i8 = lane & 7;
     const bool b1 = (lane & 2) != 0;
     const uint32_t psel = (lane & 1) ? 0x03020706u : 0x05040100u;
-    const float invK = 1.0f / (float)A.K;
+    const float invK = 1.0f / (float)A.Kall;
     for (int j = threadIdx.x; j < N; j += 256) s_r[j] = (float)A.counts[j] * invK;
     __syncthreads();
-    const float scale = (float)A.K * WSCALE;
+    const float scale = (float)A.Kall * WSCALE;
     float col[2][legs_tr::final_k(KB * 16, 5)] = {};
     for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < A.Kp / 32; tile += (int64_t)gridDim.x * 4) {
         const int64_t i = 32 * tile + (lane & 31);
@@ -533,7 +536,7 @@ constexpr int WG_FEAT = 64;          // features per LDS step
 
 template <int KB, int NC>
 __global__ void __launch_bounds__(256, 2)
-k_quant_wgrad(const _Float16 *__restrict__ F, int64_t K, int64_t Kp, int d, int dC, int64_t per_block,
+k_quant_wgrad(const _Float16 *__restrict__ F, int64_t K, int64_t Kp, int64_t Kall, int d, int dC, int64_t per_block,
               const void *__restrict__ weights, const float *__restrict__ invF, const float *__restrict__ invS,
               float lam_d, float *__restrict__ grad)
 {
@@ -629,7 +632,7 @@ k_quant_wgrad(const _Float16 *__restrict__ F, int64_t K, int64_t Kp, int d, int 
     for (int n = 0; n < NC; ++n) {
         if (n >= nc) continue;
         const bool clip = c0 + n * QCH < dC;
-        const float sc = (clip ? 1.0f : lam_d) / ((float)K * WSCALE);
+        const float sc = (clip ? 1.0f : lam_d) / ((float)Kall * WSCALE);
         const float *is = invS + (clip ? 0 : N);
 #pragma unroll
         for (int q = 0; q < DB; ++q)
@@ -679,42 +682,111 @@ k_quant_finish(const float *__restrict__ S, int d, int dC, int64_t K, const floa
     }
 }
 
+// Features whose cosines a call keeps at once (a multiple of QGROUP; 4 GB at N =
+// 128). A larger call with a gradient reads the features past the first so many
+// once more, piece by piece, when the histogram is there, instead of asking for 8 N
+// bytes for every one of them.
+constexpr int64_t QKEEP = 1 << 22;
+static_assert(QKEEP % QGROUP == 0, "pieces are whole rounds");
+
 struct QuantLayout {
-    int64_t img, invS, psum, col, lsum, cos, invF, total, Kp;
+    int64_t img, invS, psum, col, lsum, spare, cos, invF, total, Kp;
 };
 
-QuantLayout quant_layout(int64_t K, int32_t N, int32_t d)
+QuantLayout quant_layout(int64_t K, int32_t N, int32_t d, bool grad)
 {
     QuantLayout L;
     auto up = [](int64_t x) { return (x + 255) & ~(int64_t)255; };
-    L.Kp = (K + QGROUP - 1) / QGROUP * QGROUP;
+    L.Kp = (std::min(K, QKEEP) + QGROUP - 1) / QGROUP * QGROUP;
     int64_t o = 0;
     L.img = o;  o = up(o + (int64_t)N * d * 2);
     L.invS = o; o = up(o + 2 * (int64_t)N * 4);
     L.psum = o; o = up(o + (int64_t)N * 4);
     L.col = o;  o = up(o + 2 * (int64_t)N * 4);
     L.lsum = o; o = up(o + 8);
-    L.cos = o;  o = up(o + 2 * (int64_t)N * L.Kp * 4);
-    L.invF = o; o = up(o + 2 * L.Kp * 4);
+    // the gradient's alone
+    L.spare = o; o = up(o + (grad && K > QKEEP ? 8 + 2 * (int64_t)N * 4 : 0));
+    L.cos = o;  o = up(o + (grad ? 2 * (int64_t)N * L.Kp * 4 : 0));
+    L.invF = o; o = up(o + (grad ? 2 * L.Kp * 4 : 0));
     L.total = o;
     return L;
 }
 
+template <int KB>
+void quantize_kernels(legs_ctx *ctx, const QuantArgs &all, const QuantLayout &Lw, char *ws, const float *S,
+                      float *prob_mean, float *losses, float *grad, hipStream_t s)
+{
+    constexpr int N = 32 * KB;
+    const int d = all.d, dC = all.dC;
+    const int64_t cus = ctx->num_cus;
+    // the features [i0, i0 + n) of the call
+    const auto piece = [&](int64_t i0, int64_t n) {
+        QuantArgs A = all;
+        A.F += i0 * d;
+        A.index += i0;
+        A.K = n;
+        A.Kp = (n + QGROUP - 1) / QGROUP * QGROUP;
+        return A;
+    };
+    const auto pass = [&](const QuantArgs &A, bool keep) {
+        const dim3 g((unsigned)std::min(A.Kp / QGROUP, cus));
+        if (keep) hipLaunchKernelGGL((k_quant_pass<KB, true>), g, dim3(QTHREADS), 0, s, A);
+        else hipLaunchKernelGGL((k_quant_pass<KB, false>), g, dim3(QTHREADS), 0, s, A);
+    };
+    // psum, col and lsum are contiguous (up to padding) in the workspace
+    hipLaunchKernelGGL(k_quant_prep<KB>, dim3(64), dim3(256), 0, s, S, d, dC, reinterpret_cast<f16x8 *>(ws + Lw.img),
+                       reinterpret_cast<float *>(ws + Lw.invS), all.counts,
+                       reinterpret_cast<uint32_t *>(ws + Lw.psum), (int)((Lw.spare - Lw.psum) / 4), grad);
+    if (!grad) pass(piece(0, all.K), false);
+    else pass(piece(0, std::min(all.K, QKEEP)), true);
+    if (grad && all.K > QKEEP) pass(piece(QKEEP, all.K - QKEEP), false);
+    for (int64_t i0 = 0; grad && i0 < all.K; i0 += QKEEP) {
+        const QuantArgs A = piece(i0, std::min(all.K - i0, QKEEP));
+        if (i0 > 0) {                  // its cosines; the sums are in already
+            QuantArgs again = A;
+            again.lsum = reinterpret_cast<double *>(ws + Lw.spare);
+            again.psum = reinterpret_cast<float *>(ws + Lw.spare + 8);
+            again.counts = reinterpret_cast<uint32_t *>(again.psum + N);
+            pass(again, true);
+        }
+        hipLaunchKernelGGL(k_quant_weights<KB>, dim3((unsigned)std::min((A.Kp / 32 + 3) / 4, cus * 8)), dim3(256), 0, s,
+                           A);
+        // feature ranges of the weight gradient: two workgroups per CU over all of
+        // the dimension groups, in steps of WG_FEAT
+        constexpr int NC = 2;
+        const int gy = (d / QCH + NC - 1) / NC;
+        int64_t per_block = (A.Kp * gy / (2 * cus) + WG_FEAT - 1) / WG_FEAT * WG_FEAT;
+        per_block = per_block < 512 ? 512 : per_block;
+        hipLaunchKernelGGL((k_quant_wgrad<KB, NC>), dim3((unsigned)((A.Kp + per_block - 1) / per_block), (unsigned)gy),
+                           dim3(256), 0, s, A.F, A.K, A.Kp, A.Kall, d, dC, per_block, A.cos, A.invF, A.invS, A.lam_d,
+                           grad);
+    }
+    const int64_t gz = ((int64_t)N * d + 255) / 256;
+    hipLaunchKernelGGL(k_quant_finish<KB>, dim3((unsigned)(grad ? std::min<int64_t>(gz, 1024) : 1)), dim3(256), 0, s, S,
+                       d, dC, all.K, all.invS, all.col, grad, all.counts, all.psum, all.lsum, all.lam_cos, all.lam_lb,
+                       prob_mean, losses);
+}
+
 } // namespace
 
-int64_t legs_quantize_workspace_bytes(int64_t K, int32_t N, int32_t d) { return quant_layout(K, N, d).total; }
+int64_t legs_quantize_workspace_bytes(int64_t K, int32_t N, int32_t d) { return quant_layout(K, N, d, true).total; }
+
+int64_t legs_quantize_index_workspace_bytes(int64_t K, int32_t N, int32_t d)
+{
+    return quant_layout(K, N, d, false).total;
+}
 
 int32_t legs_launch_quantize(legs_ctx *ctx, const uint16_t *feat, int64_t K, int32_t d, int32_t dC,
                              const float *S, int32_t N, float lam_d, float lam_cos, float lam_lb,
                              void *workspace, int32_t *index, uint32_t *counts, float *prob_mean,
                              float *losses, float *grad, hipStream_t s)
 {
-    const QuantLayout Lw = quant_layout(K, N, d);
+    const QuantLayout Lw = quant_layout(K, N, d, grad != nullptr);
     char *ws = static_cast<char *>(workspace);
     QuantArgs A;
     A.F = reinterpret_cast<const _Float16 *>(feat);
-    A.K = K;
-    A.Kp = Lw.Kp;
+    A.K = A.Kall = K;
+    A.Kp = 0;                          // (set per launch)
     A.d = d;
     A.dC = dC;
     A.img = reinterpret_cast<const f16x8 *>(ws + Lw.img);
@@ -729,42 +801,12 @@ int32_t legs_launch_quantize(legs_ctx *ctx, const uint16_t *feat, int64_t K, int
     A.cos = reinterpret_cast<f32x4 *>(ws + Lw.cos);
     A.col = reinterpret_cast<float *>(ws + Lw.col);
     A.invF = reinterpret_cast<float *>(ws + Lw.invF);
-    // psum, col and lsum are contiguous (up to padding) in the workspace
-    const int nsums = (int)((Lw.cos - Lw.psum) / 4);
-    const int KB = N / 32;
-    const int64_t rounds = (K + QGROUP - 1) / QGROUP;
-    const int gq = (int)(rounds < ctx->num_cus ? (rounds < 1 ? 1 : rounds) : ctx->num_cus);
-    constexpr int NC = 2;
-    // feature ranges of the weight gradient: two workgroups per CU over all of
-    // the dimension groups, in steps of WG_FEAT
-    const int gy = (d / QCH + NC - 1) / NC;
-    int64_t per_block = (Lw.Kp * gy / (2 * ctx->num_cus) + WG_FEAT - 1) / WG_FEAT * WG_FEAT;
-    per_block = per_block < 512 ? 512 : per_block;
-    const dim3 gw((unsigned)((Lw.Kp + per_block - 1) / per_block), (unsigned)gy);
-    const int gz = (int)((((int64_t)N * d + 255) / 256) < 1024 ? ((int64_t)N * d + 255) / 256 : 1024);
-    const int64_t wt = (Lw.Kp / 32 + 3) / 4, wtc = (int64_t)ctx->num_cus * 8;
-    const int gt = (int)(wt < wtc ? wt : wtc);
-#define LEGS_QUANT(KBV)                                                                                              \
-    hipLaunchKernelGGL(k_quant_prep<KBV>, dim3(64), dim3(256), 0, s, S, d, dC,                                     \
-                       reinterpret_cast<f16x8 *>(ws + Lw.img), reinterpret_cast<float *>(ws + Lw.invS), counts,    \
-                       reinterpret_cast<uint32_t *>(ws + Lw.psum), nsums, grad);                                    \
-    if (!grad) {                                                                                                     \
-        hipLaunchKernelGGL((k_quant_pass<KBV, false>), dim3(gq), dim3(QTHREADS), 0, s, A);                         \
-    } else {                                                                                                         \
-        hipLaunchKernelGGL((k_quant_pass<KBV, true>), dim3(gq), dim3(QTHREADS), 0, s, A);                          \
-        hipLaunchKernelGGL(k_quant_weights<KBV>, dim3(gt), dim3(256), 0, s, A);                                    \
-        hipLaunchKernelGGL((k_quant_wgrad<KBV, NC>), gw, dim3(256), 0, s, A.F, K, Lw.Kp, d, dC, per_block, A.cos,   \
-                           A.invF, A.invS, lam_d, grad);                                                            \
-    }                                                                                                                \
-    hipLaunchKernelGGL(k_quant_finish<KBV>, dim3(grad ? gz : 1), dim3(256), 0, s, S, d, dC, K, A.invS, A.col,      \
-                       grad, counts, A.psum, A.lsum, lam_cos, lam_lb, prob_mean, losses);
-    switch (KB) {
-    case 1: LEGS_QUANT(1) break;
-    case 2: LEGS_QUANT(2) break;
-    case 4: LEGS_QUANT(4) break;
+    switch (N) {
+    case 32: quantize_kernels<1>(ctx, A, Lw, ws, S, prob_mean, losses, grad, s); break;
+    case 64: quantize_kernels<2>(ctx, A, Lw, ws, S, prob_mean, losses, grad, s); break;
+    case 128: quantize_kernels<4>(ctx, A, Lw, ws, S, prob_mean, losses, grad, s); break;
     default: return legs_set_error(ctx, LEGS_ERR_ARG, "N must be 32, 64 or 128");
     }
-#undef LEGS_QUANT
     LEGS_CHECK_LAUNCH(ctx);
     return LEGS_OK;
 }

@@ -135,8 +135,8 @@ def quantize(ctx: Context, feat, S, d_clip, lambda_dino=0.5, lambda_cos=1.0, lam
     N = S.shape[0]
     dev = ctx.device
     if workspace is None:
-        workspace = torch.empty(max(int(L.lib().legs_quantize_workspace_bytes(K, N, d)), 16), dtype=torch.uint8,
-                                device=dev)
+        size = L.lib().legs_quantize_workspace_bytes if grad else L.lib().legs_quantize_index_workspace_bytes
+        workspace = torch.empty(max(int(size(K, N, d)), 16), dtype=torch.uint8, device=dev)
     out = dict(index=torch.empty(max(K, 1), dtype=torch.int32, device=dev),
                counts=torch.empty(N, dtype=torch.int32, device=dev),
                prob_mean=torch.empty(N, dtype=torch.float32, device=dev),

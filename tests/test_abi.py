@@ -90,3 +90,18 @@ def test_sort_scratch_grows_with_the_capacity(L, tiles):
     sizes = [size(c, tiles) for c in caps]
     assert all(a <= b for a, b in zip(sizes, sizes[1:])), [
         (c, a, b) for c, a, b in zip(caps, sizes, sizes[1:]) if a > b]
+
+
+@pytest.mark.parametrize("N", [32, 64, 128])
+def test_quantisation_workspace(L, N):
+    """Without a gradient the workspace holds the codebook image and sums only,
+    whatever the number of features; with one it holds cosines of at most 2^22
+    features."""
+    lib, d = L.lib(), 896
+    image = 2 * N * d
+    for K in (1, 1000, 1 << 20, 1 << 30):
+        assert image <= lib.legs_quantize_index_workspace_bytes(K, N, d) <= image + 16 * N + (1 << 12)
+    most = (8 * N + 8) << 22
+    full = lib.legs_quantize_workspace_bytes(1 << 22, N, d)
+    assert most <= full <= most + image + 16 * N + (1 << 12)
+    assert full <= lib.legs_quantize_workspace_bytes(1 << 30, N, d) <= full + 16 * N + (1 << 12)

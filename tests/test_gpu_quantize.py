@@ -94,6 +94,55 @@ def test_quantize_chunk_and_round_edges(ctx, N, d, d_clip, K):
     test_quantize_matches_oracle(ctx, N, d, d_clip, K)
 
 
+def test_quantize_in_pieces(ctx):
+    """2^22 + 700 features, more than a call keeps the cosines of: index, histogram,
+    probabilities, losses and gradient against plain PyTorch in float64 along the
+    kernel's indices. Bounds as at the bench's size."""
+    from paper_2311_18482_amd import decode as DEC
+    K, N, d, dc = (1 << 22) + 700, 32, 256, 128
+    g = torch.Generator(device="cuda").manual_seed(23)
+    S = torch.randn((N, d), generator=g, device="cuda")
+    F = torch.empty((K, d), dtype=torch.float16, device="cuda")
+    for lo in range(0, K, 1 << 19):
+        at = torch.randint(0, N, (min(1 << 19, K - lo),), generator=g, device="cuda")
+        F[lo:lo + (1 << 19)] = S[at] + 1.5 * torch.randn((at.numel(), d), generator=g, device="cuda")
+    out = DEC.quantize(ctx, F, S, dc)
+    plain = DEC.quantize(ctx, F, S, dc, grad=False)
+    m = out["index"].long()
+    assert torch.equal(out["index"], plain["index"]) and torch.equal(out["counts"], plain["counts"])
+    assert torch.equal(out["counts"].long(), torch.bincount(m, minlength=N))
+    S16 = S.half().double()
+    parts = ((slice(0, dc), 1.0), (slice(dc, d), 0.5))
+    inv = [1.0 / S16[:, q].norm(dim=1) for q, _ in parts]
+    r = out["counts"].double() / K
+    psum, lcos = torch.zeros(N, device="cuda", dtype=torch.float64), 0.0
+    grads = [torch.zeros((N, dc), device="cuda", dtype=torch.float64) for _ in parts]
+    mag = torch.zeros(N, device="cuda", dtype=torch.float64)
+    for lo in range(0, K, 1 << 18):
+        x, at = F[lo:lo + (1 << 18)].double(), m[lo:lo + (1 << 18), None]
+        us = [x[:, q] / x[:, q].norm(dim=1, keepdim=True) for q, _ in parts]
+        cos = [u @ (S16[:, q] * i[:, None]).t() for u, (q, _), i in zip(us, parts, inv)]
+        D = cos[0] + 0.5 * cos[1]
+        assert (D.gather(1, at)[:, 0] >= D.max(1).values - 1e-4).all()
+        sm = torch.softmax(D, 1)
+        psum += sm.sum(0)
+        lcos += float((1.5 - D.gather(1, at)).sum())
+        dD = 0.5 / K * sm * (r - (sm @ r)[:, None])
+        dD.scatter_add_(1, at, torch.full_like(D[:, :1], -1.0 / K))
+        mag += dD.abs().sum(0)
+        for a, u, c, (q, lam), i in zip(grads, us, cos, parts, inv):
+            a += lam * (dD.t() @ u - (dD * c).sum(0)[:, None] * S16[:, q] * i[:, None]) * i[:, None]
+    L = out["losses"].double()
+    assert torch.allclose(out["prob_mean"].double(), psum / K, rtol=2e-4, atol=1e-7)
+    lc, lb = lcos / K, float((r * psum).sum() / K)
+    for got, want in zip(L.tolist(), (lc, lb, lc + 0.5 * lb)):
+        assert got == pytest.approx(want, rel=2e-4)
+    for a, (q, lam), i in zip(grads, parts, inv):
+        bound = (2.0 ** -10 + 4e-5) * lam * mag * i + 2.0 ** -34 * i
+        err = (out["grad"][:, q].double() - a).norm(dim=1)
+        assert (err <= bound).all(), float((err / bound).max())
+
+
 def test_quantize_rejects_bad_shapes(ctx):
     from paper_2311_18482_amd import decode as DEC
     F = torch.zeros((10, 200), dtype=torch.float16, device="cuda")
