@@ -751,12 +751,14 @@ void quantize_kernels(legs_ctx *ctx, const QuantArgs &all, const QuantLayout &Lw
         }
         hipLaunchKernelGGL(k_quant_weights<KB>, dim3((unsigned)std::min((A.Kp / 32 + 3) / 4, cus * 8)), dim3(256), 0, s,
                            A);
-        // feature ranges of the weight gradient: two workgroups per CU over all of
-        // the dimension groups, in steps of WG_FEAT
+        // feature ranges of the weight gradient, in steps of WG_FEAT: at most two
+        // workgroups per CU over all of the dimension groups, so that all run at once
+        // (rounded up instead, 515 of them at 1,280 dimensions left three for a
+        // round of their own: 1M features x 128 codes 2,128 us, now 1,678)
         constexpr int NC = 2;
-        const int gy = (d / QCH + NC - 1) / NC;
-        int64_t per_block = (A.Kp * gy / (2 * cus) + WG_FEAT - 1) / WG_FEAT * WG_FEAT;
-        per_block = per_block < 512 ? 512 : per_block;
+        const int64_t gy = (d / QCH + NC - 1) / NC, gx = std::max<int64_t>(2 * cus / gy, 1);
+        const int64_t per_block =
+            std::max<int64_t>(((A.Kp + gx - 1) / gx + WG_FEAT - 1) / WG_FEAT * WG_FEAT, 512);
         hipLaunchKernelGGL((k_quant_wgrad<KB, NC>), dim3((unsigned)((A.Kp + per_block - 1) / per_block), (unsigned)gy),
                            dim3(256), 0, s, A.F, A.K, A.Kp, A.Kall, d, dC, per_block, A.cos, A.invF, A.invS, A.lam_d,
                            grad);

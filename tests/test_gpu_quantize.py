@@ -143,6 +143,30 @@ def test_quantize_in_pieces(ctx):
         assert (err <= bound).all(), float((err / bound).max())
 
 
+def test_quantize_gradient_runs_in_one_round_of_workgroups(ctx):
+    """The gradient at 1,280 dimensions (five groups of 256, which do not divide the
+    workgroups of two per compute unit) takes no longer per dimension than at 1,024
+    (four groups, which do); with three workgroups left over for a second round it
+    took 1.36 times as long in all, 1.10 without."""
+    from paper_2311_18482_amd import decode as DEC
+    from paper_2311_18482_amd import _lib as L
+    K, N, us = 1 << 18, 128, []
+    for d in (1024, 1280):
+        F = torch.randn((K, d), device="cuda").half()
+        S = torch.randn((N, d), device="cuda")
+        ws = torch.empty(int(L.lib().legs_quantize_workspace_bytes(K, N, d)), dtype=torch.uint8, device="cuda")
+        t = []
+        for _ in range(15):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            DEC.quantize(ctx, F, S, 512, workspace=ws)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        us.append(sorted(t)[7] * 1e3)
+    assert us[1] < 1280 / 1024 * us[0], us
+
+
 def test_quantize_rejects_bad_shapes(ctx):
     from paper_2311_18482_amd import decode as DEC
     F = torch.zeros((10, 200), dtype=torch.float16, device="cuda")
