@@ -400,7 +400,8 @@ int32_t legs_smooth_loss_grad(legs_ctx *ctx, const float *mean, const float *cha
 /* Gradient of the mean cross-entropy (Eq. 9) of B pixels against labels
  * [B] int32 in [0, K): grad [legs_mlp_param_count(K)] is overwritten, loss [1]
  * receives the mean loss. Straight-through for the bf16 roundings.
- * workspace: legs_mlp_workspace_bytes(B, K) bytes of device memory. */
+ * workspace: legs_mlp_workspace_bytes(B, K) bytes of device memory, one partial
+ * result per 128 pixels and at most 256 of them (13.8 MB at K = 128). */
 int64_t legs_mlp_workspace_bytes(int64_t B, int32_t K);
 int32_t legs_mlp_grad(legs_ctx *ctx, const float *feat, int64_t B, int64_t c_stride,
                       int64_t p_stride, const int32_t *labels, int32_t K, int32_t mlp_flags,
@@ -430,7 +431,7 @@ int32_t legs_semantic_loss_grad(legs_ctx *ctx, const float *feat, const float *r
 /* legs_semantic_loss_grad without a workspace argument, for callers that
  * cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc). It allocates nothing: its
- * workspace is a fixed array of 21,495,808 bytes inside the library's device
+ * workspace is a fixed array of 6,914,560 bytes inside the library's device
  * code, one per GPU, held from the first legs_create on that GPU until the
  * process ends. P <= LEGS_NOALLOC_MAX_PIXELS, else LEGS_ERR_ARG (nothing
  * launched); the loss and the decoder gradient accumulate, so a larger view

@@ -11,13 +11,15 @@
 #include "legs_internal.h"
 #include "legs_decode_internal.h"
 
-// Workspace of legs_semantic_loss_grad_noalloc: LEGS_NOALLOC_MAX_PIXELS rows of
-// the decoder-training workspace at the largest K (21,495,808 bytes). Every GPU
+// Workspace of legs_semantic_loss_grad_noalloc: the partial results of
+// LEGS_NOALLOC_MAX_PIXELS pixels at the largest K (6,914,560 bytes). Every GPU
 // that loads the library holds its own copy until the process ends. In host
 // code `scratch` is only a stand-in for the symbol: the device address of a
 // GPU's copy comes from hipGetSymbolAddress with that GPU current, once per
 // device (in legs_create), and only that address is handed to kernels.
-static __device__ __align__(256) float scratch[(size_t)LEGS_NOALLOC_MAX_PIXELS * LEGS_MLP_WS_PER_PIXEL(128)];
+static __device__ __align__(256) float scratch[(size_t)(LEGS_NOALLOC_MAX_PIXELS / 128) * LEGS_MLP_PART_FLOATS(4)];
+static_assert(LEGS_NOALLOC_MAX_PIXELS % 128 == 0 && LEGS_NOALLOC_MAX_PIXELS / 128 <= LEGS_MLP_MAX_PARTS,
+              "one partial result per 128 pixels");
 
 namespace {
 

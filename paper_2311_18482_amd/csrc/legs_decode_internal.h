@@ -42,9 +42,13 @@
 #define LEGS_SMOOTH_OFF_B4 (LEGS_SMOOTH_OFF_W4 + LEGS_SMOOTH_OUT * LEGS_SMOOTH_H)
 #define LEGS_SMOOTH_NPARAMS (LEGS_SMOOTH_OFF_B4 + LEGS_SMOOTH_OUT)
 
-// Training workspace per pixel (of B rounded up to 64), in floats: it holds the
-// training kernel's partial results, one per 128 pixels at most
-#define LEGS_MLP_WS_PER_PIXEL(K) (200 + (K))
+// Decoder training: the workspace holds one partial result per workgroup of the
+// training kernel, in floats 2 KB + 4 + 1 blocks of weight gradients, KB + 2 of
+// biases and the loss; a workgroup takes at least 128 pixels, and there are at most
+// LEGS_MLP_MAX_PARTS of them (one per CU of this GPU).
+#define LEGS_MLP_MAX_PARTS 256
+#define LEGS_MLP_PART_BLOCKS(KB) (2 * (KB) + 4 + 1)
+#define LEGS_MLP_PART_FLOATS(KB) (LEGS_MLP_PART_BLOCKS(KB) * 1024 + ((KB) + 2) * 32 + 1)
 
 typedef __attribute__((ext_vector_type(8))) __bf16 legs_bf16x8;
 typedef __attribute__((ext_vector_type(16))) float legs_f32x16;

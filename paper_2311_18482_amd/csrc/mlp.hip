@@ -24,6 +24,8 @@
 // semantic loss of 1080 x 720 pixels at K = 128 and 163 us for a decoder step
 // of 65,536; this takes 224 and 43.
 // Workspace: the partial results, 53 KB a workgroup at K = 128.
+#include <algorithm>
+
 #include "legs_internal.h"
 #include "legs_decode_internal.h"
 
@@ -165,8 +167,8 @@ __device__ __forceinline__ void bias_add(float4 *bias, const f32x16 &z)
 // A workgroup's partial result: the weight-gradient accumulators in register
 // order, [16-value block][4 float4][lane], then the biases of layers 3 and 2,
 // then the loss.
-constexpr int mlp_acc_blocks(int KB) { return 2 * KB + 4 + 1; }
-constexpr int mlp_part_floats(int KB) { return mlp_acc_blocks(KB) * 1024 + (KB + 2) * 32 + 1; }
+constexpr int mlp_acc_blocks(int KB) { return LEGS_MLP_PART_BLOCKS(KB); }
+constexpr int mlp_part_floats(int KB) { return LEGS_MLP_PART_FLOATS(KB); }
 
 template <int KB>
 __device__ __forceinline__ f32x16 &mlp_acc(MlpGrad<KB> &G, int i)
@@ -200,7 +202,7 @@ __device__ __forceinline__ int mlp_part_param(int i)
 // each (see the top of the file). Bound by the matrix unit and the VALU work
 // between the layers, so nothing but the features, labels and input gradients
 // touches memory: the weight gradients accumulate in registers over all of a
-// wave's tiles (14 blocks of 32 x 32 at K = 128), which takes one wave per
+// wave's tiles (13 blocks of 32 x 32 at K = 128), which takes one wave per
 // SIMD; the bias sums accumulate in LDS. part: the workgroups' partial results.
 template <int KB, bool NORM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
@@ -498,10 +500,10 @@ k_zero_f32(float *__restrict__ p, int64_t n, float *__restrict__ q)
 
 } // namespace
 
-int64_t legs_mlp_workspace_floats(int64_t B, int32_t K)
-{
-    return (B + 63) / 64 * 64 * (int64_t)LEGS_MLP_WS_PER_PIXEL(K);
-}
+// Workgroups of the training kernel for B pixels, at most.
+static int64_t mlp_parts(int64_t B) { return std::min<int64_t>((B + 127) / 128, LEGS_MLP_MAX_PARTS); }
+
+int64_t legs_mlp_workspace_floats(int64_t B, int32_t K) { return mlp_parts(B) * LEGS_MLP_PART_FLOATS(K / 32); }
 
 namespace {
 
@@ -518,15 +520,24 @@ int32_t mlp_train_kernels(legs_ctx *ctx, const float *feat, int64_t B, int64_t c
         LEGS_CHECK_LAUNCH(ctx);
         return LEGS_OK;
     }
-    // one workgroup per CU (one wave per SIMD), each with at least one tile: its
-    // partial result fits in the workspace rows of 64 pixels
-    static_assert(mlp_part_floats(4) <= 64 * LEGS_MLP_WS_PER_PIXEL(128) &&
-                  mlp_part_floats(2) <= 64 * LEGS_MLP_WS_PER_PIXEL(64) &&
-                  mlp_part_floats(1) <= 64 * LEGS_MLP_WS_PER_PIXEL(32), "workspace layout");
-    int64_t g = (B + 127) / 128;
-    if (g > ctx->num_cus) g = ctx->num_cus;
+    // one workgroup per CU (one wave per SIMD), each with at least one tile per wave
+    // but the last
+    const int64_t g = std::min<int64_t>(mlp_parts(B), ctx->num_cus);
     const bool norm = (mlp_flags & LEGS_MLP_NORMALIZE_INPUT) != 0;
-#define LEGS_MLP_TRAIN(KBV)                                                                                                {                                                                                                                          if (norm) hipLaunchKernelGGL((k_mlp_train<KBV, true>), dim3((unsigned)g), dim3(256), 0, s, feat, B, cs, ps,                                         labels, params, workspace, cw, ig);                                                      else hipLaunchKernelGGL((k_mlp_train<KBV, false>), dim3((unsigned)g), dim3(256), 0, s, feat, B, cs, ps,                                        labels, params, workspace, cw, ig);                                                            const dim3 gr((mlp_part_floats(KBV) + 63) / 64);                                                                       if (add) hipLaunchKernelGGL((k_mlp_reduce<KBV, true>), gr, dim3(256), 0, s, workspace, (int)g, grad, loss);            else hipLaunchKernelGGL((k_mlp_reduce<KBV, false>), gr, dim3(256), 0, s, workspace, (int)g, grad, loss);           }
+#define LEGS_MLP_TRAIN(KBV)                                                                                          \
+    {                                                                                                                \
+        if (norm)                                                                                                    \
+            hipLaunchKernelGGL((k_mlp_train<KBV, true>), dim3((unsigned)g), dim3(256), 0, s, feat, B, cs, ps,        \
+                               labels, params, workspace, cw, ig);                                                   \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_mlp_train<KBV, false>), dim3((unsigned)g), dim3(256), 0, s, feat, B, cs, ps,       \
+                               labels, params, workspace, cw, ig);                                                   \
+        const dim3 gr((mlp_part_floats(KBV) + 63) / 64);                                                             \
+        if (add)                                                                                                     \
+            hipLaunchKernelGGL((k_mlp_reduce<KBV, true>), gr, dim3(256), 0, s, workspace, (int)g, grad, loss);       \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_mlp_reduce<KBV, false>), gr, dim3(256), 0, s, workspace, (int)g, grad, loss);      \
+    }
     switch (K) {
     case 32: LEGS_MLP_TRAIN(1) break;
     case 64: LEGS_MLP_TRAIN(2) break;

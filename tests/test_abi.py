@@ -105,3 +105,15 @@ def test_quantisation_workspace(L, N):
     full = lib.legs_quantize_workspace_bytes(1 << 22, N, d)
     assert most <= full <= most + image + 16 * N + (1 << 12)
     assert full <= lib.legs_quantize_workspace_bytes(1 << 30, N, d) <= full + 16 * N + (1 << 12)
+
+
+@pytest.mark.parametrize("K", [32, 64, 128])
+def test_decoder_training_workspace(L, K):
+    """A partial parameter gradient per workgroup, at most 256 of them whatever the
+    number of pixels; never less for more pixels."""
+    lib = L.lib()
+    n = lib.legs_mlp_param_count(K)
+    sizes = [lib.legs_mlp_workspace_bytes(B, K) for B in (0, 1, 128, 129, 32_768, 32_769, 1 << 20, 1 << 31)]
+    assert sizes[0] == 0 and all(a <= b for a, b in zip(sizes, sizes[1:]))
+    assert 4 * (n + 1) <= sizes[1] == sizes[2] <= 4 * (n + 1024) and sizes[3] == 2 * sizes[1]
+    assert sizes[-1] == 256 * sizes[1]
