@@ -304,6 +304,56 @@ struct MlpInputs64 {
     }
 };
 
+// A 32-row x 32-column block held as two B fragments (lane = column, k-slots = rows
+// in accumulator order) turned into the two fragments with lane = row, 8 columns
+// each (columns in accumulator order): as the A operand against the identity the
+// matrix unit returns the block transposed. In bytes, the low and the high ones of
+// the values apart, so that every bit pattern comes through (against a bf16
+// identity an infinity or a NaN would spread over its column's other rows). 28
+// instructions for a block where lane swaps took 52.
+namespace legs_turn {
+
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(16))) int i32x16;
+
+// Identity fragments, one of [low, high byte][k-step] per part.
+__device__ __forceinline__ i32x4 identity(int part, int lane)
+{
+    union {
+        int8_t b[16];
+        i32x4 v;
+    } f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+        f.b[k] = (k & 1) == (part >> 1) && (lane & 31) == legs_khid(part & 1, lane >> 5, k >> 1);
+    return f.v;
+}
+
+__device__ __forceinline__ i32x16 mfma_i8(const legs_bf16x8 &a, i32x4 b, i32x16 c)
+{
+    return __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, a), b, c, 0, 0, 0);
+}
+
+// lo0 .. hi1: this lane's identity fragments of the low and the high byte, k-steps 0
+// and 1.
+__device__ __forceinline__ void turn(const legs_bf16x8 &f0, const legs_bf16x8 &f1, i32x4 lo0, i32x4 lo1, i32x4 hi0,
+                                     i32x4 hi1, legs_bf16x8 (&out)[2])
+{
+    const i32x16 lo = mfma_i8(f1, lo1, mfma_i8(f0, lo0, (i32x16){}));
+    const i32x16 hi = mfma_i8(f1, hi1, mfma_i8(f0, hi0, (i32x16){}));
+    i32x4 w[2];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const uint32_t a = __builtin_amdgcn_perm(lo[2 * q + 1], lo[2 * q], 0x0c040c00u);
+        const uint32_t b = __builtin_amdgcn_perm(hi[2 * q + 1], hi[2 * q], 0x0c040c00u);
+        w[q >> 2][q & 3] = (int)(b << 8 | a);
+    }
+    out[0] = __builtin_bit_cast(legs_bf16x8, w[0]);
+    out[1] = __builtin_bit_cast(legs_bf16x8, w[1]);
+}
+
+} // namespace legs_turn
+
 // Hidden layers of NT 32-pixel tiles at once: every weight fragment read from
 // LDS feeds NT independent MFMAs. lds_off is an opaque zero the caller
 // refreshes per iteration so that the compiler keeps the fragments in LDS

@@ -14,7 +14,7 @@
 //                forward ones; straight through the bf16 roundings. The weight
 //                gradients dW_l = sum_p dz_l h_(l-1)^T contract over the
 //                pixels, which lie along the lanes: both operands are turned
-//                by an MFMA against the identity (exact) and the products
+//                by MFMAs against the identity (exact) and the products
 //                accumulate in registers over all of a wave's tiles; the bias
 //                sums accumulate in LDS in float32.
 //   k_mlp_reduce the sum of the workgroups' partial results.
@@ -22,7 +22,7 @@
 // Writing the layer inputs and dz to memory for a second kernel that contracts
 // them (1.3 KB a pixel each way, then float atomics) took 740 us for the
 // semantic loss of 1080 x 720 pixels at K = 128 and 163 us for a decoder step
-// of 65,536; this takes 224 and 43.
+// of 65,536; this takes 237 and 44.
 // Workspace: the partial results, 53 KB a workgroup at K = 128.
 #include <algorithm>
 
@@ -104,6 +104,21 @@ __device__ __forceinline__ void split8(const f32x16 &z, int first, bf16x8 &hi, b
     }
 }
 
+using legs_turn::i32x4;
+
+// Blocks turned for the weight gradients (legs_turn::turn). EXACT: byte by byte, any
+// bit pattern. Otherwise by a bf16 identity, half of the MFMAs and a third of the
+// VALU work, where an infinity or a NaN of a pixel spreads over its block's units:
+// only for the last layer, whose gradient is NaN throughout at a pixel where it or
+// its input is not finite. In the layers below a ReLU may stand between (a NaN
+// feature beside closed units). (The semantic loss of 1080 x 720 pixels at K = 128
+// takes 224 us with the bf16 identity in all layers, 237 so, 251 byte by byte in all.)
+// bf: the bf16 identity's two k-steps; i8: the low bytes', the high ones' one up.
+struct TurnId {
+    const bf16x8 *bf;
+    const i32x4 *i8;
+};
+
 __device__ __forceinline__ bf16x8 cvt8(const f32x16 &z, int first)
 {
     bf16x8 f;
@@ -112,21 +127,24 @@ __device__ __forceinline__ bf16x8 cvt8(const f32x16 &z, int first)
     return f;
 }
 
-// A 32-unit x 32-pixel block held as two B fragments (lane = pixel, k-slots =
-// units in accumulator order) turned into two fragments with lane = unit and
-// k-slots = pixels: as the A operand against the identity, the matrix unit
-// returns the block transposed and exact (every product is by 1 or 0; a pixel
-// with an infinity or a NaN spreads it over its block's units, but has made the
-// last layer's gradient NaN before that). id: this lane's identity fragments in
-// LDS.
-__device__ __forceinline__ f32x16 transpose_block(const bf16x8 &f0, const bf16x8 &f1, const bf16x8 *id)
+template <bool EXACT>
+__device__ __forceinline__ void turn_block(const bf16x8 &f0, const bf16x8 &f1, const TurnId &id, bf16x8 (&out)[2])
 {
-    return legs_mfma(f1, id[LEGS_WAVE], legs_mfma(f0, id[0], (f32x16){}));
+    if constexpr (EXACT) {
+        const i32x4 l0 = id.i8[0], l1 = id.i8[LEGS_WAVE];
+        legs_turn::turn(f0, f1, l0, l1, l0 << 8, l1 << 8, out);
+    } else {
+        const f32x16 t = legs_mfma(f1, id.bf[LEGS_WAVE], legs_mfma(f0, id.bf[0], (f32x16){}));
+        out[0] = cvt8(t, 0);
+        out[1] = cvt8(t, 8);
+    }
 }
 
 // Accumulators of the weight gradients, 32 x 32 blocks (row = unit of the
 // layer, column = its input). Layer 1 has 8 inputs and the bias: its two unit
-// blocks share one accumulator, in columns 0 .. 8 and 16 .. 24.
+// blocks share one accumulator, the first with inputs 0 .. 3 in columns 0 .. 3, the
+// bias in 4 and inputs 4 .. 7 in 8 .. 11 (the order of the identity's rows), the
+// second the same from column 16.
 template <int KB>
 struct MlpGrad {
     f32x16 w3[KB][2], w2[2][2], w1;
@@ -134,19 +152,19 @@ struct MlpGrad {
 
 // dW block += dz (hi + lo parts) times the transposed layer input, over the
 // tile's 32 pixels.
-template <int NB>
+template <bool EXACT, int NB>
 __device__ __forceinline__ void wgrad_block(const bf16x8 (&hi)[2], const bf16x8 (&lo)[2], const bf16x8 (&in)[NB][2],
-                                            const bf16x8 *id, f32x16 *acc)
+                                            const TurnId &id, f32x16 *acc)
 {
 #pragma unroll
     for (int part = 0; part < 2; ++part) {
-        const f32x16 t = part ? transpose_block(lo[0], lo[1], id) : transpose_block(hi[0], hi[1], id);
+        bf16x8 a[2];
+        if (part) turn_block<EXACT>(lo[0], lo[1], id, a);
+        else turn_block<EXACT>(hi[0], hi[1], id, a);
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            const bf16x8 a = cvt8(t, 8 * g);
+        for (int g = 0; g < 2; ++g)
 #pragma unroll
-            for (int n = 0; n < NB; ++n) acc[n] = legs_mfma(a, in[n][g], acc[n]);
-        }
+            for (int n = 0; n < NB; ++n) acc[n] = legs_mfma(a[g], in[n][g], acc[n]);
     }
     __builtin_amdgcn_sched_barrier(0);   // one block's operands live at a time
 }
@@ -193,9 +211,9 @@ __device__ __forceinline__ int mlp_part_param(int i)
         const int k = blk - 2 * KB;
         return LEGS_MLP_OFF_W2 + (32 * (k >> 1) + row) * MH + 32 * (k & 1) + col;
     }
-    const int unit = 32 * (col >> 4) + row, in = col & 15;
-    return in < LEGS_MLP_IN ? LEGS_MLP_OFF_W1 + unit * LEGS_MLP_IN + in
-                            : in == LEGS_MLP_IN ? LEGS_MLP_OFF_B1 + unit : -1;
+    const int unit = 32 * (col >> 4) + row, c = col & 15;
+    if (c == 4) return LEGS_MLP_OFF_B1 + unit;
+    return (c & 7) < 4 ? LEGS_MLP_OFF_W1 + unit * LEGS_MLP_IN + (c & 3) + 4 * (c >> 3) : -1;
 }
 
 // Forward, loss, backward and parameter gradient of 32-pixel tiles, one wave
@@ -210,9 +228,7 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
             const float *__restrict__ params, float *__restrict__ part, CeWeights cw, InputGrad ig)
 {
     constexpr int NACC = mlp_acc_blocks(KB);
-    // id: the identity in accumulator order, then the same for the input layer
-    // (8 inputs, then the bias one), as columns 0 .. 8 and as columns 16 .. 24
-    __shared__ struct { MlpLds L; MlpBwdLds<KB> T; bf16x8 id[4 * 64]; float4 bias[4][(KB + 2) * 4 * 64]; } S;
+    __shared__ struct { MlpLds L; MlpBwdLds<KB> T; bf16x8 id[2 * 64]; i32x4 id8[2 * 64]; float4 bias[4][(KB + 2) * 4 * 64]; } S;
     static_assert(sizeof(S) <= 163840 && sizeof(S) >= 3 * NACC * 4096, "the gradient sums reuse the LDS");
     MlpLds &L = S.L;
     MlpBwdLds<KB> &T = S.T;
@@ -220,13 +236,9 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
     mlp_stage_bwd<KB, 256>(params, T);
     const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
     {
-        bf16x8 f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int c = wave < 2 ? legs_drow(8 * wave + e, h) : (h == 0 ? e : (e == 0 ? LEGS_MLP_IN : -1));
-            f[e] = (__bf16)(c >= 0 && (lane & 31) == c + (wave == 3 ? 16 : 0) ? 1.0f : 0.0f);
-        }
-        S.id[wave * 64 + lane] = f;
+        const i32x4 low = legs_turn::identity(wave & 1, lane);      // ones, as bytes
+        if (wave < 2) S.id8[wave * 64 + lane] = low;
+        else S.id[(wave - 2) * 64 + lane] = __builtin_bit_cast(bf16x8, low * 0x3f80);   // as bf16
     }
     float4 *bias = &S.bias[wave][lane];
 #pragma unroll
@@ -262,7 +274,7 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
         int off = 0;
         asm volatile("" : "+s"(off));   // fragments are re-read from LDS every tile
         const int ln = lane + off;
-        const bf16x8 *id = S.id + ln;
+        const TurnId id = {S.id + ln, S.id8 + ln};
         const int64_t p = tile * 32 + (lane & 31);
         const bool valid = p < B;
         const Inputs in = next;
@@ -303,16 +315,13 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
             if (cw.ru) cw.d_ru[p] = (cw.lu - cw.lce * ce) * cw.inv_hw;
         }
         __builtin_amdgcn_sched_barrier(0);
+        const float pw = inv * wpx;
+        f32x16 dxa = {};
         // the layer inputs transposed: columns of the weight gradients
         bf16x8 h2t[2][2];
 #pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            const f32x16 t = transpose_block(F.h2[2 * n], F.h2[2 * n + 1], id);
-            h2t[n][0] = cvt8(t, 0);
-            h2t[n][1] = cvt8(t, 8);
-        }
+        for (int n = 0; n < 2; ++n) turn_block<false>(F.h2[2 * n], F.h2[2 * n + 1], id, h2t[n]);
         // dz3 = (p - onehot) w_p; dh2 = W3^T dz3, dW3 = dz3 h2^T
-        const float pw = inv * wpx;
         int yh2 = yh;
         asm volatile("" : "+v"(yh2));   // the compares are made again: 64 masks kept from above would be spilled
         f32x16 dh[2] = {};
@@ -333,16 +342,12 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
                     dh[mb] = legs_mfma(a, lo[q], legs_mfma(a, hi[q], dh[mb]));
                 }
             __builtin_amdgcn_sched_barrier(0);
-            wgrad_block<2>(hi, lo, h2t, id, G.w3[b]);
+            wgrad_block<false, 2>(hi, lo, h2t, id, G.w3[b]);
         }
         // dz2 = dh2 gated by h2 > 0; dh1 = W2^T dz2, dW2 = dz2 h1^T
         bf16x8 h1t[2][2];
 #pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            const f32x16 t = transpose_block(F.h1[2 * n], F.h1[2 * n + 1], id);
-            h1t[n][0] = cvt8(t, 0);
-            h1t[n][1] = cvt8(t, 8);
-        }
+        for (int n = 0; n < 2; ++n) turn_block<true>(F.h1[2 * n], F.h1[2 * n + 1], id, h1t[n]);
         f32x16 dg[2] = {};
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -361,10 +366,11 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
                     dg[mb] = legs_mfma(a, lo[q], legs_mfma(a, hi[q], dg[mb]));
                 }
             __builtin_amdgcn_sched_barrier(0);
-            wgrad_block<2>(hi, lo, h1t, id, G.w2[b]);
+            wgrad_block<true, 2>(hi, lo, h1t, id, G.w2[b]);
         }
+        bf16x8 x2t[2];
+        turn_block<true>(F.x, F.x, id, x2t);          // in columns 0 .. 11 and 16 .. 27
         // dz1 = dh1 gated by h1 > 0; dW1 and db1 against the input and its bias one
-        f32x16 dxa = {};
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
 #pragma unroll
@@ -381,9 +387,9 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
                     dxa = legs_mfma(a, lo[q], legs_mfma(a, hi[q], dxa));
                 }
             }
-            const f32x16 t = legs_mfma(F.x, id[(2 + b) * LEGS_WAVE], (f32x16){});
-            const bf16x8 xt[1][2] = {{cvt8(t, 0), cvt8(t, 8)}};
-            wgrad_block<1>(hi, lo, xt, id, &G.w1);
+            const bool mine = ((lane >> 4) & 1) == b;      // the block's columns of the accumulator
+            const bf16x8 xt[1][2] = {{mine ? x2t[0] : (bf16x8){}, mine ? x2t[1] : (bf16x8){}}};
+            wgrad_block<true, 1>(hi, lo, xt, id, &G.w1);
         }
         if (ig.d_feat) {
             float dx[4] = {dxa[0], dxa[1], dxa[2], dxa[3]};

@@ -163,35 +163,13 @@ __device__ __forceinline__ void layer_block(const bf16x8 *__restrict__ wA, const
 // 16 more), the two 16-byte fragments of the planes.
 __device__ __forceinline__ int swap23(int x) { return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1); }
 
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((ext_vector_type(16))) int i32x16;
+using legs_turn::i32x4;
 
-__device__ __forceinline__ i32x16 mfma_i8(const bf16x8 &a, i32x4 b, i32x16 c)
-{
-    return __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, a), b, c, 0, 0, 0);
-}
-
-// A block of 32 rows x the tile's 32 Gaussians, held as two B fragments (lane =
-// Gaussian, k-slots = rows in accumulator order), turned into the two fragments
-// with lane = row, 8 Gaussians each: as the A operand against the identity the
-// matrix unit returns the block transposed. In bytes, the low and the high ones
-// of the values apart, so that every bit pattern comes through (against a bf16
-// identity an infinity would turn its row's other Gaussians into NaN). 28
-// instructions for a block where lane swaps took 52.
-// id: this lane's identity fragments, [low, high byte][k-step].
+// A block of 32 units x the tile's 32 Gaussians turned (legs_turn::turn). id: this
+// lane's identity fragments, [low, high byte][k-step].
 __device__ __forceinline__ void turn(const bf16x8 &f0, const bf16x8 &f1, const i32x4 *id, bf16x8 (&out)[2])
 {
-    const i32x16 lo = mfma_i8(f1, id[LEGS_WAVE], mfma_i8(f0, id[0], (i32x16){}));
-    const i32x16 hi = mfma_i8(f1, id[3 * LEGS_WAVE], mfma_i8(f0, id[2 * LEGS_WAVE], (i32x16){}));
-    i32x4 w[2];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const uint32_t a = __builtin_amdgcn_perm(lo[2 * q + 1], lo[2 * q], 0x0c040c00u);
-        const uint32_t b = __builtin_amdgcn_perm(hi[2 * q + 1], hi[2 * q], 0x0c040c00u);
-        w[q >> 2][q & 3] = (int)(b << 8 | a);
-    }
-    out[0] = __builtin_bit_cast(bf16x8, w[0]);
-    out[1] = __builtin_bit_cast(bf16x8, w[1]);
+    legs_turn::turn(f0, f1, id[0], id[LEGS_WAVE], id[2 * LEGS_WAVE], id[3 * LEGS_WAVE], out);
 }
 
 // Row block mb of a 128-row plane: 1 KB contiguous per fragment.
@@ -227,15 +205,7 @@ k_smooth_fwd_bwd(SmoothArgs A)
     __shared__ float s_loss[4];
     smooth_stage(A.params, L);
     const int lane = __lane_id(), wave = threadIdx.x / LEGS_WAVE, h = lane >> 5;
-    {
-        union {
-            int8_t b[16];
-            i32x4 v;
-        } f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) f.b[k] = (k & 1) == (wave >> 1) && (lane & 31) == legs_khid(wave & 1, h, k >> 1);
-        ident[wave * 64 + lane] = f.v;
-    }
+    ident[wave * LEGS_WAVE + lane] = legs_turn::identity(wave, lane);
     __syncthreads();
     const int64_t groups = (A.n + 32 * SNT - 1) / (32 * SNT);
     const int64_t stride = (int64_t)gridDim.x * 4;

@@ -296,6 +296,40 @@ def test_l1_loss_of_uneven_views_is_spread_evenly(ctx, DEC):
     assert us[1] < 2 * us[0], us
 
 
+@pytest.mark.parametrize("normalize", [False, True])
+@pytest.mark.parametrize("K", [32, 64, 128])
+def test_mlp_gradient_keeps_a_special_feature_apart(ctx, DEC, K, normalize):
+    """A NaN or an infinity in one channel of one pixel reaches that channel's column
+    of dW1, and the columns of dW2 whose hidden units it made infinite: every other
+    gradient of the first two layers stays finite (where the units above the
+    infinite ones are closed, as with these weights)."""
+    P, at, channel = 200, 37, 3
+    ws, bs = synth.mlp_init((8, 64, 64, K), 5)
+    params = DEC.mlp_pack(ws, bs).cuda()
+    rng = np.random.default_rng(9)
+    y = torch.from_numpy(rng.integers(0, K, P).astype(np.int32)).cuda()
+    f0 = rng.normal(0, 1, (P, 8)).astype(np.float32)
+
+    def gradient(value):
+        f = f0.copy()
+        f[at, channel] = value
+        t = DEC.MlpTrainer(ctx, params, K, P, normalize=normalize)
+        g, _ = t.grad_only(DEC.rowmajor_features(torch.from_numpy(f).cuda()), y)
+        g, out = g.cpu().numpy(), []
+        for n in (64 * 8, 64, 64 * 64, 64):
+            out.append(g[:n])
+            g = g[n:]
+        return out[0].reshape(64, 8), out[1], out[2].reshape(64, 64), out[3]
+    for value in (np.nan, np.inf):
+        dW1, db1, dW2, db2 = gradient(value)
+        others = np.arange(8) != channel
+        assert not np.isfinite(dW1[:, channel]).any()
+        assert np.isfinite(dW1[:, others]).all() and np.isfinite(db1).all() and np.isfinite(db2).all()
+        # z1 = W1[:, 3] times an infinity: the units with a positive weight
+        hit = (ws[0][:, channel] > 0) if np.isinf(value) and not normalize else np.zeros(64, bool)
+        assert np.isfinite(dW2[:, ~hit]).all() and not np.isfinite(dW2[:, hit]).any()
+
+
 @pytest.mark.parametrize("K,normalize", [(128, True), (64, False), (32, True)])
 def test_top1_inputs_at_tile_edges(ctx, DEC, K, normalize):
     """The top-1 decoders read 64 pixels a wave: row-major features, planes and
