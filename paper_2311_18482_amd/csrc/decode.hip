@@ -56,10 +56,10 @@ constexpr int SROW = 36;
 // probs[p][K] for the wave's 32 pixels p0 .. p0 + 31 (those below P). Each
 // block of 32 codes goes through this wave's LDS tile stage[32][SROW] and
 // leaves as runs of 128 contiguous bytes per pixel (8 pixels per store
-// instruction) instead of 32-byte pieces of 32 rows; past the caches where the
-// runs are whole lines (LINES; 1 Mpx at K = 128: the learned decode 138 -> 117 us,
-// the folded one 145 -> 123; asked in the loop instead of by the template 130 and
-// 132). Called by the whole wave.
+// instruction) instead of 32-byte pieces of 32 rows; past the caches where those
+// are whole lines of more than the caches hold (LINES: legs_past_caches; 1 Mpx at
+// K = 128: the learned decode 138 -> 132 us, the folded one 146 -> 114; asked in the
+// loop instead of by the template the gain was half). Called by the whole wave.
 template <int KB, bool LINES>
 __device__ __forceinline__ void write_softmax(f32x16 (&s)[KB], float mx, int h, int64_t p0, int64_t P,
                                               float *__restrict__ probs, float *stage)
@@ -437,7 +437,7 @@ int32_t legs_launch_decode_folded(legs_ctx *ctx, const float *feat, int64_t P, i
 {
     if (P == 0) return LEGS_OK;
     const int grid = decode_grid(ctx, P, 32 * 4);
-    const bool lines = (reinterpret_cast<uintptr_t>(probs) & 127) == 0;
+    const bool lines = probs && legs_past_caches(probs, P * K * 4);
     switch (K) {
 #define LEGS_FOLDED(KB)                                                                                              \
     if (lines) hipLaunchKernelGGL((k_decode_folded<KB, true>), dim3(grid), dim3(256), 0, s, feat, P, cs, ps, folded, probs, top1); \
@@ -461,7 +461,7 @@ int32_t legs_launch_decode_mlp(legs_ctx *ctx, const float *feat, int64_t P, int6
     const bool norm = (mlp_flags & LEGS_MLP_NORMALIZE_INPUT) != 0;
     if (probs) {
         const int grid = decode_grid(ctx, P, 32 * 4);
-        const bool lines = (reinterpret_cast<uintptr_t>(probs) & 127) == 0;
+        const bool lines = probs && legs_past_caches(probs, P * K * 4);
 #define LEGS_MLP_L(KB, N, L) hipLaunchKernelGGL((k_decode_mlp<KB, N, L>), dim3(grid), dim3(256), 0, s, feat, P, cs, ps, params, probs, top1)
 #define LEGS_MLP_N(KB, N) if (lines) LEGS_MLP_L(KB, N, true); else LEGS_MLP_L(KB, N, false)
 #define LEGS_MLP_ALL(KB) if (norm) { LEGS_MLP_N(KB, true); } else { LEGS_MLP_N(KB, false); }

@@ -349,10 +349,10 @@ __device__ __forceinline__ void store_feature(V *p, V v)
 // dimensions fill the LDS (one workgroup per CU) and a wave fits in 128
 // registers. vec: P % NT == 0 and F 16-byte aligned, else element stores. LINES:
 // the rows of F start at 128-byte lines, so that every half-wave's store is whole
-// lines; they are then written past the caches, which leaves those to M (0.78
-// Mpx, N = 128, d = 512 in half, this kernel and k_dmlp_probs together: 397 ->
-// 343 us). Where a row starts inside a line the same stores would write parts of
-// lines (0.72 Mpx: 581 -> 750 us).
+// lines, and F is more than the caches hold (legs_past_caches); written past them it
+// leaves those to M (0.78 Mpx, N = 128, d = 512 in half, this kernel and k_dmlp_probs
+// together: 397 -> 343 us). Where a row starts inside a line the same stores would
+// write parts of lines (0.72 Mpx: 581 -> 750 us).
 template <int KB, int NT, bool OUT16, bool LINES>
 __global__ void __launch_bounds__(1024)
 k_lang_features(const _Float16 *__restrict__ M, int64_t P, const float *__restrict__ S, int d,
@@ -486,7 +486,7 @@ int32_t legs_launch_language_features(legs_ctx *ctx, const uint16_t *probs16, in
     const dim3 grid((unsigned)gx, (unsigned)((d + FCHUNK - 1) / FCHUNK));
     const _Float16 *M = reinterpret_cast<const _Float16 *>(probs16);
     const int vec = P % NT == 0 && (reinterpret_cast<uintptr_t>(F) & 15) == 0;
-    const bool lines = P % (out_f16 ? 64 : 32) == 0 && (reinterpret_cast<uintptr_t>(F) & 127) == 0;
+    const bool lines = P % (out_f16 ? 64 : 32) == 0 && legs_past_caches(F, P * d * (out_f16 ? 2 : 4));
 #define LEGS_FEAT_L(KB, O, L) hipLaunchKernelGGL((k_lang_features<KB, NT, O, L>), grid, dim3(1024), 0, s, M, P, S, d, F, vec)
 #define LEGS_FEAT_O(KB, O) if (lines) LEGS_FEAT_L(KB, O, true); else LEGS_FEAT_L(KB, O, false)
 #define LEGS_FEAT(KB) if (out_f16) { LEGS_FEAT_O(KB, true); } else { LEGS_FEAT_O(KB, false); }

@@ -257,6 +257,17 @@ inline bool legs_feat_rows(const float *feat, int64_t cs, int64_t ps)
     return cs == 1 && ps == LEGS_MLP_IN && (reinterpret_cast<uintptr_t>(feat) & 15) == 0;
 }
 
+// Whether an output of whole 128-byte lines is written past the caches: where the 256
+// MB of the last-level cache cannot hold it for its reader. In us, plain / past the
+// caches, with a sum over the output behind it in brackets, K = 128, d = 512: the
+// learned decode's distribution 128 MB 50 (80) / 49 (94), 256 MB 74 (146) / 72
+// (146), 512 MB 138 (309) / 132 (279); F in half 128 MB 65 (119) / 63 (137), 256 MB
+// 88 (184) / 71 (207), 512 MB 167 (457) / 131 (421).
+inline bool legs_past_caches(const void *out, int64_t bytes)
+{
+    return (reinterpret_cast<uintptr_t>(out) & 127) == 0 && bytes > (256ll << 20);
+}
+
 // Inputs of two 32-pixel tiles, the 64 pixels from p0 (wave-uniform): every
 // lane reads (load) and normalises one pixel, then four lane-half swaps leave
 // tile 0's in x[0] and tile 1's in x[1] (lower halves), the bias ones in the

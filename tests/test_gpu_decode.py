@@ -373,6 +373,52 @@ def test_distributions_on_and_off_a_line(ctx, DEC, K):
         assert torch.equal(got.view(P, K), want)
 
 
+@pytest.mark.parametrize("K,how", [(32, "mlp"), (64, "folded"), (128, "mlp"), (128, "folded")])
+def test_distributions_larger_than_the_caches(ctx, DEC, K, how):
+    """Past 256 MB the whole lines of the distribution are stored past the caches: the
+    same values as 16 bytes off a line, where they never are."""
+    from paper_2311_18482_amd import _lib as L, raster as R
+    P = (1 << 26) // K + 33
+    f = torch.randn((P, 8), device="cuda")
+    off = torch.empty(P * K + 4, device="cuda")[4:]
+    t1 = torch.empty(P, dtype=torch.int32, device="cuda")
+    if how == "mlp":
+        p = DEC.mlp_pack(*synth.mlp_init((8, 64, 64, K), 71)).cuda()
+        want = DEC.decode_mlp(ctx, DEC.rowmajor_features(f), p, K, probs=True)[1]
+        ctx.check(L.lib().legs_decode_mlp(ctx.handle, f.data_ptr(), P, 1, 8, p.data_ptr(), K, DEC.mlp_flags(True),
+                                          off.data_ptr(), t1.data_ptr(), R._stream()))
+    else:
+        p = DEC.decode_fold(ctx, torch.randn((64, 8), device="cuda"), torch.randn((K, 64), device="cuda"))
+        want = DEC.decode_folded(ctx, DEC.rowmajor_features(f), p, K, probs=True)[1]
+        ctx.check(L.lib().legs_decode_folded(ctx.handle, f.data_ptr(), P, 1, 8, p.data_ptr(), K, off.data_ptr(),
+                                             t1.data_ptr(), R._stream()))
+    assert want.data_ptr() % 128 == 0 and want.numel() * 4 > 1 << 28
+    assert torch.equal(off.view(P, K), want)
+
+
+def test_distributions_stay_in_the_caches_for_their_reader(ctx, DEC):
+    """128 MB of distribution are in the 256 MB last-level cache for whoever reads them
+    next: the first sum over them takes about as long as the one after it (35 us
+    against 33, bound 1.2 times; 46 against 38 when whole lines of any size went
+    past the caches)."""
+    K, P = 128, 1 << 18
+    f = DEC.rowmajor_features(torch.randn((P, 8), device="cuda"))
+    p = DEC.mlp_pack(*synth.mlp_init((8, 64, 64, K), 71)).cuda()
+    first, again = [], []
+    for _ in range(41):
+        at = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+        probs = DEC.decode_mlp(ctx, f, p, K, probs=True)[1]
+        for k in (0, 2):
+            at[k].record()
+            probs.sum()
+            at[k + 1].record()
+        at[3].synchronize()
+        first.append(at[0].elapsed_time(at[1]))
+        again.append(at[2].elapsed_time(at[3]))
+    us = [sorted(t)[20] * 1e3 for t in (first, again)]
+    assert us[0] < 1.2 * us[1], us
+
+
 @pytest.mark.parametrize("K,B", [(32, 1), (64, 33), (128, 128), (128, 129), (32, 4097), (64, 32768 + 1), (128, 40000)])
 def test_mlp_gradient_sizes(ctx, DEC, K, B):
     """Batches around the training kernel's tiles (32 pixels), workgroups (128)

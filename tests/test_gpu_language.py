@@ -112,6 +112,23 @@ def test_language_features_whole_lines(ctx, N, d, out_f16, n, misalign):
     test_language_features_match_oracle(ctx, N, d, out_f16, n, misalign)
 
 
+@pytest.mark.parametrize("N,out_f16", [(32, True), (128, False), (128, True)])
+def test_language_features_larger_than_the_caches(ctx, N, out_f16):
+    """Past 256 MB the whole lines of F are stored past the caches: the same values as
+    16 bytes off a line, where they never are."""
+    from paper_2311_18482_amd import _lib as L, decode as DEC, raster as R
+    P, d = 1 << 20, 160
+    M = torch.softmax(torch.randn((P, N), device="cuda"), 1).half()
+    S = torch.randn((N, d), device="cuda")
+    want = DEC.language_features(ctx, M, S, out_f16=out_f16)
+    assert want.data_ptr() % 128 == 0 and want.numel() * want.element_size() > 1 << 28
+    pad = 16 // want.element_size()
+    off = torch.empty(P * d + pad, dtype=want.dtype, device="cuda")[pad:]
+    ctx.check(L.lib().legs_language_features(ctx.handle, M.data_ptr(), P, N, S.data_ptr(), d, int(out_f16),
+                                             off.data_ptr(), R._stream()))
+    assert torch.equal(off.view(d, P), want.view(d, P))
+
+
 def test_paper_decoder_and_features_at_bench_size(ctx):
     """The Table 3 decoder and F = M S at the size the bench times them (four
     1920x1080 views of 8-d rendered features, N = 128, d = 512, float32 F),
