@@ -437,7 +437,8 @@ k_quant_pass(QuantArgs A)
 // dL_q/dD of 32 features per wave from their cosines, as half weights in their
 // place (a wave reads its 256 N bytes before it writes the first quarter of
 // them), and the sums over the features of its products with the cosines.
-// Bound by memory: 10 N bytes a feature.
+// Bound by memory: 10 N bytes a feature. (At N = 128 a lane's 128 cosines and their
+// sums take all 256 registers and 13 more values are spilled.)
 template <int KB>
 __global__ void __launch_bounds__(256, 2)
 k_quant_weights(QuantArgs A)
@@ -480,7 +481,6 @@ k_quant_weights(QuantArgs A)
             const float x = __expf(c[k] + A.lam_d * e[k] - best);
             sum += x;
             rs += s_r[8 * (k >> 2) + 4 * h + (k & 3)] * x;
-            if (k % 16 == 15) __builtin_amdgcn_sched_barrier(0);   // (all of the shares at once would spill)
         }
         sum += __shfl_xor(sum, 32, LEGS_WAVE);
         rs += __shfl_xor(rs, 32, LEGS_WAVE);

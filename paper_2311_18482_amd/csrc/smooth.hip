@@ -511,7 +511,7 @@ __device__ __forceinline__ void smooth_product(const SmoothArgs &A, const __bf16
     f32x16 acc[Step::DN][Step::BN] = {};
     float db[Step::DN] = {};
     Step ring[WG_AHEAD];
-        auto at = [&](int64_t s) { return 16 * min(s, steps - 1); };
+    auto at = [&](int64_t s) { return 16 * min(s, steps - 1); };
 #pragma unroll
     for (int k = 0; k < WG_AHEAD; ++k) ring[k].load(D, B, A.Gp, at(s0 + k * stride), lane);
 #pragma unroll 1

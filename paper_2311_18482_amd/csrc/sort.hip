@@ -1847,8 +1847,8 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
         const int wo = p % 2, ri = 1 - wo;
         hipLaunchKernelGGL(k_coarse_upsweep, dim3(nseg), dim3(LEGS_SORT_THREADS), 0, s, ck[ri], ccount, S.ccap,
                            S.desc, p, S.seg_hist);
-        hipLaunchKernelGGL(k_seg_scan, dim3(256), dim3(nseg <= 256 ? 256 : LEGS_SEG_MAX), 0, s, S.seg_hist, nseg, S.hist, S.desc,
-                           p, S.seg_off);
+        hipLaunchKernelGGL(k_seg_scan, dim3(256), dim3(nseg <= 256 ? 256 : LEGS_SEG_MAX), 0, s, S.seg_hist, nseg,
+                           S.hist, S.desc, p, S.seg_off);
         hipLaunchKernelGGL((k_onesweep<uint32_t, true>), dim3(nseg), dim3(LEGS_SORT_THREADS), 0, s, ck[ri], cv[ri],
                            ck[wo], cv[wo], ccount, S.ccap, p, 0, 0, S.desc, nullptr, nullptr, nullptr, P,
                            S.seg_off);
@@ -1866,8 +1866,8 @@ int32_t legs_launch_bin_sort(legs_ctx *ctx, const legs_projected *proj, int64_t 
                        OL.G, S.cut, S.ucnt);
     hipLaunchKernelGGL(k_compact_scan, dim3(grid_for(ctx, T, 256 / LEGS_WAVE, 4)), dim3(256), 0, s, S.uoff, T,
                        sviews, views, n_views, bins->ranges, S.ucnt);
-    hipLaunchKernelGGL(unit == 128 ? k_compact_write<128> : k_compact_write<256>, dim3(gu), dim3(256), 0, s, cv[0], cv[1], S.desc, S.uoff, T, udesc, P.pay,
-                       OL.G, S.cut, S.ucnt, bins->capacity,
+    hipLaunchKernelGGL(unit == 128 ? k_compact_write<128> : k_compact_write<256>, dim3(gu), dim3(256), 0, s, cv[0],
+                       cv[1], S.desc, S.uoff, T, udesc, P.pay, OL.G, S.cut, S.ucnt, bins->capacity,
                        (o->flags & LEGS_FLAG_IDS_ONLY) ? nullptr : bins->keys, bins->ids);
     LEGS_CHECK_LAUNCH(ctx);
     return LEGS_OK;

@@ -94,6 +94,30 @@ def test_quantize_chunk_and_round_edges(ctx, N, d, d_clip, K):
     test_quantize_matches_oracle(ctx, N, d, d_clip, K)
 
 
+# one row: alone in its round, tile and histogram
+@pytest.mark.parametrize("N,d,d_clip", [(32, 128, 128), (128, 384, 256)])
+def test_quantize_single_row(ctx, N, d, d_clip):
+    from paper_2311_18482_amd import decode as DEC
+    rng = np.random.default_rng(31)
+    S = rng.normal(0, 1, (N, d)).astype(np.float32)
+    F = (S[5:6] + 0.5 * rng.normal(0, 1, (1, d))).astype(np.float16)
+    out = DEC.quantize(ctx, torch.from_numpy(F).cuda(), torch.from_numpy(S).cuda(), d_clip)
+    S16 = S.astype(np.float16).astype(np.float64)
+    q = LG.quantize(F.astype(np.float64), S16, d_clip, 0.5, 1.0, 0.5)
+    assert out["index"].tolist() == q["m"].tolist() == [5]
+    assert out["counts"].tolist() == np.bincount([5], minlength=N).tolist()
+    assert np.allclose(out["prob_mean"].cpu().numpy(), q["p"], rtol=1e-4, atol=1e-7)
+    for got, want in zip(out["losses"].tolist(), (q["L_cos"], q["L_lb"], q["L_q"])):
+        assert got == pytest.approx(want, rel=1e-4)
+    # the bound of the other sizes: half-precision weights and unit rows
+    g = out["grad"].cpu().numpy().astype(np.float64)
+    for lo, hi, lam in ((0, d_clip, 1.0), (d_clip, d, 0.5)):
+        if hi > lo:
+            inv = 1.0 / np.linalg.norm(S16[:, lo:hi], axis=1)
+            bound = (2.0 ** -10 + 2e-6) * lam * np.abs(q["dD"]).sum(axis=0) * inv + 2.0 ** -34 * inv
+            assert (np.linalg.norm(g[:, lo:hi] - q["grad"][:, lo:hi], axis=1) <= bound).all()
+
+
 def test_quantize_in_pieces(ctx):
     """2^22 + 700 features, more than a call keeps the cosines of: index, histogram,
     probabilities, losses and gradient against plain PyTorch in float64 along the
