@@ -345,13 +345,12 @@ __device__ __forceinline__ i32x16 mfma_i8(const legs_bf16x8 &a, i32x4 b, i32x16 
     return __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, a), b, c, 0, 0, 0);
 }
 
-// lo0 .. hi1: this lane's identity fragments of the low and the high byte, k-steps 0
-// and 1.
-__device__ __forceinline__ void turn(const legs_bf16x8 &f0, const legs_bf16x8 &f1, i32x4 lo0, i32x4 lo1, i32x4 hi0,
-                                     i32x4 hi1, legs_bf16x8 (&out)[2])
+// id(0 .. 3): this lane's identity fragments, [low, high byte][k-step].
+template <class Id>
+__device__ __forceinline__ void turn(const legs_bf16x8 &f0, const legs_bf16x8 &f1, Id id, legs_bf16x8 (&out)[2])
 {
-    const i32x16 lo = mfma_i8(f1, lo1, mfma_i8(f0, lo0, (i32x16){}));
-    const i32x16 hi = mfma_i8(f1, hi1, mfma_i8(f0, hi0, (i32x16){}));
+    const i32x16 lo = mfma_i8(f1, id(1), mfma_i8(f0, id(0), (i32x16){}));
+    const i32x16 hi = mfma_i8(f1, id(3), mfma_i8(f0, id(2), (i32x16){}));
     i32x4 w[2];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {

@@ -131,8 +131,8 @@ template <bool EXACT>
 __device__ __forceinline__ void turn_block(const bf16x8 &f0, const bf16x8 &f1, const TurnId &id, bf16x8 (&out)[2])
 {
     if constexpr (EXACT) {
-        const i32x4 l0 = id.i8[0], l1 = id.i8[LEGS_WAVE];
-        legs_turn::turn(f0, f1, l0, l1, l0 << 8, l1 << 8, out);
+        legs_turn::turn(f0, f1, [&](int k) { return k < 2 ? id.i8[k * LEGS_WAVE] : id.i8[(k - 2) * LEGS_WAVE] << 8; },
+                        out);
     } else {
         const f32x16 t = legs_mfma(f1, id.bf[LEGS_WAVE], legs_mfma(f0, id.bf[0], (f32x16){}));
         out[0] = cvt8(t, 0);

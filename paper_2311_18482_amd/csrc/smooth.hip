@@ -169,7 +169,7 @@ using legs_turn::i32x4;
 // lane's identity fragments, [low, high byte][k-step].
 __device__ __forceinline__ void turn(const bf16x8 &f0, const bf16x8 &f1, const i32x4 *id, bf16x8 (&out)[2])
 {
-    legs_turn::turn(f0, f1, id[0], id[LEGS_WAVE], id[2 * LEGS_WAVE], id[3 * LEGS_WAVE], out);
+    legs_turn::turn(f0, f1, [&](int k) { return id[k * LEGS_WAVE]; }, out);
 }
 
 // Row block mb of a 128-row plane: 1 KB contiguous per fragment.
