@@ -345,12 +345,9 @@ __device__ __forceinline__ i32x16 mfma_i8(const legs_bf16x8 &a, i32x4 b, i32x16 
     return __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, a), b, c, 0, 0, 0);
 }
 
-// id(0 .. 3): this lane's identity fragments, [low, high byte][k-step].
-template <class Id>
-__device__ __forceinline__ void turn(const legs_bf16x8 &f0, const legs_bf16x8 &f1, Id id, legs_bf16x8 (&out)[2])
+// The block from its low and its high bytes.
+__device__ __forceinline__ void join(const i32x16 &lo, const i32x16 &hi, legs_bf16x8 (&out)[2])
 {
-    const i32x16 lo = mfma_i8(f1, id(1), mfma_i8(f0, id(0), (i32x16){}));
-    const i32x16 hi = mfma_i8(f1, id(3), mfma_i8(f0, id(2), (i32x16){}));
     i32x4 w[2];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -360,6 +357,22 @@ __device__ __forceinline__ void turn(const legs_bf16x8 &f0, const legs_bf16x8 &f
     }
     out[0] = __builtin_bit_cast(legs_bf16x8, w[0]);
     out[1] = __builtin_bit_cast(legs_bf16x8, w[1]);
+}
+
+// id(0 .. 3): this lane's identity fragments, [low, high byte][k-step].
+template <class Id>
+__device__ __forceinline__ void turn(const legs_bf16x8 &f0, const legs_bf16x8 &f1, Id id, legs_bf16x8 (&out)[2])
+{
+    const i32x16 lo = mfma_i8(f1, id(1), mfma_i8(f0, id(0), (i32x16){}));
+    const i32x16 hi = mfma_i8(f1, id(3), mfma_i8(f0, id(2), (i32x16){}));
+    join(lo, hi, out);
+}
+
+// f1 = 0: the block's rows are those of f0.
+template <class Id>
+__device__ __forceinline__ void turn(const legs_bf16x8 &f0, Id id, legs_bf16x8 (&out)[2])
+{
+    join(mfma_i8(f0, id(0), (i32x16){}), mfma_i8(f0, id(2), (i32x16){}), out);
 }
 
 } // namespace legs_turn

@@ -22,7 +22,7 @@
 // Writing the layer inputs and dz to memory for a second kernel that contracts
 // them (1.3 KB a pixel each way, then float atomics) took 740 us for the
 // semantic loss of 1080 x 720 pixels at K = 128 and 163 us for a decoder step
-// of 65,536; this takes 237 and 44.
+// of 65,536; this takes 240 and 45.
 // Workspace: the partial results, 53 KB a workgroup at K = 128.
 #include <algorithm>
 
@@ -112,7 +112,7 @@ using legs_turn::i32x4;
 // only for the last layer, whose gradient is NaN throughout at a pixel where it or
 // its input is not finite. In the layers below a ReLU may stand between (a NaN
 // feature beside closed units). (The semantic loss of 1080 x 720 pixels at K = 128
-// takes 224 us with the bf16 identity in all layers, 237 so, 251 byte by byte in all.)
+// takes 224 us with the bf16 identity in all layers, 240 so, 251 byte by byte in all.)
 // bf: the bf16 identity's two k-steps; i8: the low bytes', the high ones' one up.
 struct TurnId {
     const bf16x8 *bf;
@@ -127,12 +127,16 @@ __device__ __forceinline__ bf16x8 cvt8(const f32x16 &z, int first)
     return f;
 }
 
+__device__ __forceinline__ auto byte_identity(const TurnId &id)
+{
+    return [i8 = id.i8](int k) { return k < 2 ? i8[k * LEGS_WAVE] : i8[(k - 2) * LEGS_WAVE] << 8; };
+}
+
 template <bool EXACT>
 __device__ __forceinline__ void turn_block(const bf16x8 &f0, const bf16x8 &f1, const TurnId &id, bf16x8 (&out)[2])
 {
     if constexpr (EXACT) {
-        legs_turn::turn(f0, f1, [&](int k) { return k < 2 ? id.i8[k * LEGS_WAVE] : id.i8[(k - 2) * LEGS_WAVE] << 8; },
-                        out);
+        legs_turn::turn(f0, f1, byte_identity(id), out);
     } else {
         const f32x16 t = legs_mfma(f1, id.bf[LEGS_WAVE], legs_mfma(f0, id.bf[0], (f32x16){}));
         out[0] = cvt8(t, 0);
@@ -140,11 +144,28 @@ __device__ __forceinline__ void turn_block(const bf16x8 &f0, const bf16x8 &f1, c
     }
 }
 
+// A turned block (lane = row, 2 x 8 pixels each half) as two operands of the
+// 16 x 16 x 32 MFMA: rows 0 .. 15 and 16 .. 31, all 32 pixels.
+__device__ __forceinline__ void halves(const bf16x8 (&f)[2], bf16x8 (&out)[2])
+{
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    const u32x4 a = __builtin_bit_cast(u32x4, f[0]), b = __builtin_bit_cast(u32x4, f[1]);
+    u32x4 x, y;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a[q], b[q], false, false);
+        x[q] = r[0];
+        y[q] = r[1];
+    }
+    out[0] = __builtin_bit_cast(bf16x8, x);
+    out[1] = __builtin_bit_cast(bf16x8, y);
+}
+
 // Accumulators of the weight gradients, 32 x 32 blocks (row = unit of the
-// layer, column = its input). Layer 1 has 8 inputs and the bias: its two unit
-// blocks share one accumulator, the first with inputs 0 .. 3 in columns 0 .. 3, the
-// bias in 4 and inputs 4 .. 7 in 8 .. 11 (the order of the identity's rows), the
-// second the same from column 16.
+// layer, column = its input). Layer 1 has 8 inputs and the bias, four blocks of 16
+// units x 16 columns in the registers of one: inputs 0 .. 3 in columns 0 .. 3, the
+// bias in 4, inputs 4 .. 7 in 8 .. 11 (the order of the identity's rows). Units of
+// two blocks never share a row: zeros do not mask a gradient that is not finite.
 template <int KB>
 struct MlpGrad {
     f32x16 w3[KB][2], w2[2][2], w1;
@@ -167,6 +188,29 @@ __device__ __forceinline__ void wgrad_block(const bf16x8 (&hi)[2], const bf16x8 
             for (int n = 0; n < NB; ++n) acc[n] = legs_mfma(a[g], in[n][g], acc[n]);
     }
     __builtin_amdgcn_sched_barrier(0);   // one block's operands live at a time
+}
+
+// dW1 and db1 of the 32 units of block b: in holds the turned inputs and ones.
+__device__ __forceinline__ void wgrad_input(const bf16x8 (&hi)[2], const bf16x8 (&lo)[2], const bf16x8 &in,
+                                            const TurnId &id, int b, f32x16 &acc)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+        bf16x8 t[2], a[2];
+        if (part) turn_block<true>(lo[0], lo[1], id, t);
+        else turn_block<true>(hi[0], hi[1], id, t);
+        halves(t, a);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int o = 4 * (2 * b + k);
+            f32x4 c = {acc[o], acc[o + 1], acc[o + 2], acc[o + 3]};
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[k], in, c, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[o + r] = c[r];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Bias sums of a dz block: each lane adds its 16 values to its own words of LDS
@@ -211,7 +255,8 @@ __device__ __forceinline__ int mlp_part_param(int i)
         const int k = blk - 2 * KB;
         return LEGS_MLP_OFF_W2 + (32 * (k >> 1) + row) * MH + 32 * (k & 1) + col;
     }
-    const int unit = 32 * (col >> 4) + row, c = col & 15;
+    // 16 x 16 blocks: register r of lane l is row 4 (l / 16) + r, column l % 16
+    const int unit = 16 * q + 4 * (lane >> 4) + (i & 3), c = lane & 15;
     if (c == 4) return LEGS_MLP_OFF_B1 + unit;
     return (c & 7) < 4 ? LEGS_MLP_OFF_W1 + unit * LEGS_MLP_IN + (c & 3) + 4 * (c >> 3) : -1;
 }
@@ -368,8 +413,9 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
             __builtin_amdgcn_sched_barrier(0);
             wgrad_block<true, 2>(hi, lo, h1t, id, G.w2[b]);
         }
-        bf16x8 x2t[2];
-        turn_block<true>(F.x, F.x, id, x2t);          // in columns 0 .. 11 and 16 .. 27
+        bf16x8 xt[2], xh[2];
+        legs_turn::turn(F.x, byte_identity(id), xt);
+        halves(xt, xh);                               // xh[0]: columns 0 .. 15
         // dz1 = dh1 gated by h1 > 0; dW1 and db1 against the input and its bias one
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -387,9 +433,7 @@ k_mlp_train(const float *__restrict__ feat, int64_t B, int64_t cs, int64_t ps, c
                     dxa = legs_mfma(a, lo[q], legs_mfma(a, hi[q], dxa));
                 }
             }
-            const bool mine = ((lane >> 4) & 1) == b;      // the block's columns of the accumulator
-            const bf16x8 xt[1][2] = {{mine ? x2t[0] : (bf16x8){}, mine ? x2t[1] : (bf16x8){}}};
-            wgrad_block<true, 1>(hi, lo, xt, id, &G.w1);
+            wgrad_input(hi, lo, xh[0], id, b, G.w1);
         }
         if (ig.d_feat) {
             float dx[4] = {dxa[0], dxa[1], dxa[2], dxa[3]};

@@ -330,6 +330,37 @@ def test_mlp_gradient_keeps_a_special_feature_apart(ctx, DEC, K, normalize):
         assert np.isfinite(dW2[:, ~hit]).all() and not np.isfinite(dW2[:, hit]).any()
 
 
+@pytest.mark.parametrize("K,normalize", [(32, True), (64, False), (128, True)])
+def test_semantic_gradient_of_a_special_pixel_spares_closed_units(ctx, DEC, K, normalize):
+    """A NaN in the uncertainty of one pixel makes its gradient at the last layer NaN:
+    the gradients of the hidden units that the pixel closes stay finite, those of its
+    open units do not."""
+    P, at = 100, 37
+    ws, bs = synth.mlp_init((8, 64, 64, K), 5)
+    params = DEC.mlp_pack(ws, bs).cuda()
+    rng = np.random.default_rng(9)
+    f = rng.normal(0, 1, (P, 8)).astype(np.float32)
+    ru = rng.uniform(0, 1, P).astype(np.float32)
+    ru[at] = np.nan
+    y = torch.from_numpy(rng.integers(0, K, P).astype(np.int32)).cuda()
+    grad, loss = torch.zeros(params.numel(), device="cuda"), torch.zeros(1, device="cuda")
+    DEC.semantic_loss_grad(ctx, DEC.rowmajor_features(torch.from_numpy(f).cuda()), torch.from_numpy(ru).cuda(), y,
+                           params, K, 1.0 / P, DEC.workspace(ctx, P, K), grad, (torch.empty((P, 8), device="cuda"), 1, 8),
+                           torch.empty(P, device="cuda"), loss, normalize=normalize)
+    g, parts = grad.cpu().numpy(), []
+    for n in (64 * 8, 64, 64 * 64, 64):
+        parts.append(g[:n])
+        g = g[n:]
+    dW1, db1, dW2, db2 = parts[0].reshape(64, 8), parts[1], parts[2].reshape(64, 64), parts[3]
+    hs = D.mlp_forward(f, ws, bs, normalize=normalize)["hs"]
+    for h, dW, db in ((hs[1][at], dW1, db1), (hs[2][at], dW2, db2)):
+        opened = h > 0
+        assert opened.any() and not opened.all()
+        assert np.isfinite(dW[~opened]).all() and np.isfinite(db[~opened]).all()
+        assert np.isnan(dW[opened]).all() and np.isnan(db[opened]).all()
+    assert np.isnan(g).all()
+
+
 @pytest.mark.parametrize("K,normalize", [(128, True), (64, False), (32, True)])
 def test_top1_inputs_at_tile_edges(ctx, DEC, K, normalize):
     """The top-1 decoders read 64 pixels a wave: row-major features, planes and
